@@ -13,20 +13,32 @@ constexpr int kWave = 64;                 // CDNA wavefront width
 constexpr uint32_t kAlways = 0xFFFFFFFFu; // threshold meaning "channel always live"
 constexpr uint32_t kNStrata = 8;
 
+// a ^ b ^ c: one v_bitop3_b32 (truth table 0x96) on the device, where the
+// compiler would issue two v_xor_b32.
+__host__ __device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);
+#else
+    return a ^ b ^ c;
+#endif
+}
+
 // Philox4x32-10 block function: ten S-P rounds over a 128-bit counter, the
 // 64-bit key advanced by the Weyl increments between rounds.  Each round
 // multiplies counter words 0 and 2 by the Philox constants, keeps both halves
 // of the 64-bit products and mixes the high halves with the other words and
-// the key.
+// the key.  VALU-bound: 20 v_mad_u64_u32 and 20 three-input xors per block
+// with the key schedule in scalar registers, 845 Gblocks/s on MI355X at full
+// occupancy (two-input xors: 40 of them, 661-695 Gblocks/s).
 __host__ __device__ __forceinline__ uint4 philox4x32_10(uint4 ctr, uint2 key) {
 #pragma unroll
     for (int round = 0; round < 10; ++round) {
         const uint64_t m0 = (uint64_t)0xD2511F53u * (uint64_t)ctr.x;
         const uint64_t m2 = (uint64_t)0xCD9E8D57u * (uint64_t)ctr.z;
         uint4 next;
-        next.x = (uint32_t)(m2 >> 32) ^ ctr.y ^ key.x;
+        next.x = xor3((uint32_t)(m2 >> 32), ctr.y, key.x);
         next.y = (uint32_t)m2;
-        next.z = (uint32_t)(m0 >> 32) ^ ctr.w ^ key.y;
+        next.z = xor3((uint32_t)(m0 >> 32), ctr.w, key.y);
         next.w = (uint32_t)m0;
         ctr = next;
         key.x += 0x9E3779B9u;
@@ -62,37 +74,69 @@ __device__ __forceinline__ uint32_t lane_rank(uint64_t mask) {
                                      __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
 }
 
+// Scans and reductions move values between lanes with DPP, inside the vector
+// ALU: four shifts within rows of 16 lanes, then lane 15 of each row to the
+// next row and lane 31 to the upper half.  (A shuffle is an LDS access of
+// about 60 cycles, and a scan is a chain of six: with shuffles a range of 777
+// small RR sets took 1.32 ms, with DPP 1.15 ms.)  Every lane of the wave must
+// be active.  `idle` stands in for a lane without a source.
+template <int kCtrl, int kRows>
+__device__ __forceinline__ uint32_t dpp_move(uint32_t idle, uint32_t x) {
+    return (uint32_t)__builtin_amdgcn_update_dpp((int)idle, (int)x, kCtrl, kRows, 0xf, false);
+}
+template <int kCtrl, int kRows, typename T>
+__device__ __forceinline__ T dpp_from(T x) {   // idle = 0
+    static_assert(sizeof(T) == 4 || sizeof(T) == 8, "32- or 64-bit values");
+    if constexpr (sizeof(T) == 4) {
+        return (T)dpp_move<kCtrl, kRows>(0u, (uint32_t)x);
+    } else {
+        const uint32_t lo = dpp_move<kCtrl, kRows>(0u, (uint32_t)(uint64_t)x);
+        const uint32_t hi = dpp_move<kCtrl, kRows>(0u, (uint32_t)((uint64_t)x >> 32));
+        return (T)(((uint64_t)hi << 32) | lo);
+    }
+}
+constexpr int kRowShr1 = 0x111, kRowShr2 = 0x112, kRowShr4 = 0x114, kRowShr8 = 0x118;
+constexpr int kRowBcast15 = 0x142, kRowBcast31 = 0x143;   // rows 1 and 3 / rows 2 and 3 receive
+
+// The inclusive scan of x under `op` (identity 0: unsigned sums, maxima, ors).
+template <typename T, typename Op>
+__device__ __forceinline__ T wave_scan_op(T x, Op op) {
+    x = op(x, dpp_from<kRowShr1, 0xf>(x));
+    x = op(x, dpp_from<kRowShr2, 0xf>(x));
+    x = op(x, dpp_from<kRowShr4, 0xf>(x));
+    x = op(x, dpp_from<kRowShr8, 0xf>(x));
+    x = op(x, dpp_from<kRowBcast15, 0xa>(x));
+    x = op(x, dpp_from<kRowBcast31, 0xc>(x));
+    return x;
+}
+
+// The value of lane `src` (the same on every lane) as a scalar.
+__device__ __forceinline__ uint32_t wave_bcast(uint32_t x, int src) {
+    return (uint32_t)__builtin_amdgcn_readlane((int)x, src);
+}
+__device__ __forceinline__ uint64_t wave_bcast64(uint64_t x, int src) {
+    return ((uint64_t)wave_bcast((uint32_t)(x >> 32), src) << 32) | (uint64_t)wave_bcast((uint32_t)x, src);
+}
+
+template <typename T>
+__device__ __forceinline__ T wave_last(T x) {
+    if constexpr (sizeof(T) == 4) return (T)wave_bcast((uint32_t)x, kWave - 1);
+    else return (T)wave_bcast64((uint64_t)x, kWave - 1);
+}
+
 template <typename T>
 __device__ __forceinline__ T wave_incl_scan(T x) {
-    const uint32_t lane = lane_id();
-#pragma unroll
-    for (int d = 1; d < kWave; d <<= 1) {
-        T y = __shfl_up(x, d, kWave);
-        if (lane >= (uint32_t)d) x += y;
-    }
-    return x;
+    return wave_scan_op(x, [](T a, T b) { return (T)(a + b); });
 }
 
 template <typename T>
 __device__ __forceinline__ T wave_sum(T x) {
-#pragma unroll
-    for (int d = kWave / 2; d > 0; d >>= 1) x += __shfl_xor(x, d, kWave);
-    return x;
+    return wave_last(wave_incl_scan(x));
 }
 
 template <typename T>
 __device__ __forceinline__ T wave_max(T x) {
-#pragma unroll
-    for (int d = kWave / 2; d > 0; d >>= 1) {
-        T y = __shfl_xor(x, d, kWave);
-        x = y > x ? y : x;
-    }
-    return x;
-}
-
-__device__ __forceinline__ uint32_t wave_bcast(uint32_t x, int src) { return __shfl(x, src, kWave); }
-__device__ __forceinline__ uint64_t wave_bcast64(uint64_t x, int src) {
-    return (uint64_t)__shfl((unsigned long long)x, src, kWave);
+    return wave_last(wave_scan_op(x, [](T a, T b) { return a > b ? a : b; }));
 }
 
 // Wave-uniform values kept in scalar registers: the value of the first active
