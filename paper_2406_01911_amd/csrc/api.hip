@@ -159,12 +159,12 @@ void RRWorkspace::release() {
 
 size_t PrepWorkspace::bytes() const {
     size_t b = 0;
-    for (const DevBuf *x : {&k1, &vals, &k2, &wmax, &pc, &tmp, &counts, &base, &isum, &lmax, &hist, &flag, &cnt, &off64, &lists, &bm}) b += x->bytes;
+    for (const DevBuf *x : {&k1, &vals, &k2, &info, &pc, &tmp, &counts, &base, &hist, &flag, &cnt, &off64, &lists, &bm}) b += x->bytes;
     return b;
 }
 
 void PrepWorkspace::release() {
-    for (DevBuf *x : {&k1, &vals, &k2, &wmax, &pc, &tmp, &counts, &base, &isum, &lmax, &hist, &flag, &cnt, &off64, &lists, &bm}) x->release();
+    for (DevBuf *x : {&k1, &vals, &k2, &info, &pc, &tmp, &counts, &base, &hist, &flag, &cnt, &off64, &lists, &bm}) x->release();
 }
 
 size_t GreedyWorkspace::bytes() const {

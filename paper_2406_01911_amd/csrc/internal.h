@@ -133,12 +133,13 @@ struct GreedyWorkspace {
 };
 
 // Workspace of graph building and stratification: one per device, kept
-// between calls (the hash tables take up to 5 GB, and allocating and freeing
-// them per call cost more than a small graph's kernels).
+// between calls (allocating and freeing it per call cost more than a small
+// graph's kernels).
 struct PrepWorkspace {
-    DevBuf k1, vals, k2;                   // (v,u) weight and (v,w) layer hash tables
-    DevBuf wmax, pc, tmp;                  // per-vertex maxima, pair prefix sums, scan blocks
-    DevBuf counts, base, isum, lmax, hist; // strata counts and statistics
+    DevBuf k1, k2;                         // hubs: counter rows, weight marks; build: per-incidence counts, prefixes
+    DevBuf vals, pc;                       // hubs: partial results, chunk prefix
+    DevBuf info, tmp;                      // class counts and sums, scan blocks
+    DevBuf counts, base, hist;             // strata counts and statistics
     DevBuf flag, cnt, off64, lists, bm;    // graph build: checks, degrees, offsets, sort lists and marks
     size_t bytes() const;
     void release();
