@@ -1096,9 +1096,12 @@ __global__ __launch_bounds__(kWG) void k_lt_walk(RRArgs a) {
 // multiply-adds, in the order the recursions state.
 //
 // One wave per set (persistent, phase A's slots, bitmaps and output path):
-// the lanes take the set's queued vertices 64 at a time and each walks its
-// vertex's layers; picked members go through the visited bitmap (atomic or:
-// the lane that sets the bit appends the member at a wave counter in LDS).
+// the (vertex, layer) pairs of the set's queued vertices, 64 vertices at a
+// time, go to the lanes one pair each -- a hub has over a thousand layers, and
+// with one lane per vertex the sets that met one took 9.9 ms a launch (a million
+// vertices, 2048 sets a pool) against 0.58; picked members go through the
+// visited bitmap (atomic or: the lane that sets the bit appends the member at a
+// wave counter in LDS).
 // Picks of a layer of at most 32 members live in a bit mask; larger layers
 // keep their picked indices, ascending, in a per-lane scratch list.
 constexpr uint32_t kMaxPick = 64;
@@ -1135,13 +1138,22 @@ __device__ __forceinline__ uint32_t layer_count(uint32_t n, uint32_t i, uint32_t
     return h;
 }
 
+// The wave's queued vertices: inclusive scan of their layer counts, id, layers,
+// starts of their co-members and of their layer ends.
+struct LayerLds {
+    uint32_t scan[kWave], v[kWave], l[kWave];
+    uint64_t nb[kWave], ly[kWave];
+};
+
 template <bool kLdsBitmap>
 __global__ __launch_bounds__(kWG) void k_layered(RRArgs a, uint32_t *__restrict__ pick_scratch) {
     __shared__ uint32_t sort_s[kWavesPerWG][kSortMax];
     __shared__ uint32_t lbm[kLdsBitmap ? kWavesPerWG : 1][kLdsBitmap ? kLdsBitmapWords : 1];
     __shared__ uint32_t tail_s[kWavesPerWG];
+    __shared__ LayerLds lds[kWavesPerWG];
     const uint32_t lane = lane_id(), wv = uni(threadIdx.x / kWave);
     const uint32_t slot = blockIdx.x * kWavesPerWG + wv;
+    LayerLds &L = lds[wv];
     uint32_t *sortb = sort_s[wv];
     uint32_t *list = a.lists + (uint64_t)slot * a.slot_n;
     uint32_t *picks = pick_scratch + ((uint64_t)slot * kWave + lane) * kMaxPick;
@@ -1183,68 +1195,82 @@ __global__ __launch_bounds__(kWG) void k_layered(RRArgs a, uint32_t *__restrict_
             // queue entries were stored by other lanes of this wave
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
             const uint32_t nbq = min((uint32_t)kWave, size - head);
+            uint32_t qv = 0, ql = 0;
+            uint64_t qb = 0, qy = 0;
             if (lane < nbq) {
-                const uint32_t v = list[head + lane];
-                const uint32_t l = lv_of[v];
-                const uint64_t base = nb_off[v], lb = ly_off[v];
-                uint32_t lo = 0;
-                bytes_done += 20ull + 4ull * l;
-                for (uint32_t i = 1; i <= l; ++i) {
-                    const uint32_t hi = ly_end[lb + i - 1], n = hi - lo;
-                    uint4 w = philox4x32_10(make_uint4((uint32_t)S.j, i, v,
-                                                       (S.pool << 31) | ((uint32_t)(S.j >> 32) << 24)),
-                                            S.key);
-                    ++px;
-                    const double U = (double)((uint64_t)(w.x >> 11) | ((uint64_t)w.y << 21)) * 0x1.0p-53;
-                    const uint32_t h = layer_count(n, i, l, U, ln, expm);
-                    uint32_t mask = 0, np = 0, word = 2, blk = 0;
-                    for (uint32_t r = 0; r < h; ++r) {
-                        if (word == 4) {
-                            w = philox4x32_10(make_uint4((uint32_t)S.j, i, v,
-                                                         (S.pool << 31) | ((uint32_t)(S.j >> 32) << 24) | ++blk),
-                                              S.key);
-                            ++px;
-                            word = 0;
-                        }
-                        const uint32_t x = word == 0 ? w.x : word == 1 ? w.y : word == 2 ? w.z : w.w;
-                        ++word;
-                        const uint32_t aidx = (uint32_t)(((uint64_t)x * (uint64_t)(n - r)) >> 32);
-                        uint32_t pi;
-                        if (n <= 32u) {
-                            // the aidx-th clear bit of the mask
-                            uint32_t c = aidx;
-                            pi = 0;
-                            for (uint32_t t = 0; t < n; ++t) {
-                                if ((mask >> t) & 1u) continue;
-                                if (c == 0) {
-                                    pi = t;
-                                    break;
-                                }
-                                --c;
-                            }
-                            mask |= 1u << pi;
-                        } else {
-                            pi = aidx;
-                            uint32_t t = 0;
-                            for (; t < np; ++t) {
-                                const uint32_t q = picks[t];
-                                if (q <= pi) ++pi;
-                                else break;
-                            }
-                            for (uint32_t z = np; z > t; --z) picks[z] = picks[z - 1];
-                            picks[t] = pi;
-                            ++np;
-                        }
-                        const uint32_t u = nb[base + lo + pi];
-                        const uint32_t bit = 1u << (u & 31);
-                        if ((atomicOr(&bm[u >> 5], bit) & bit) == 0u) {
-                            const uint32_t pos = atomicAdd(&tail_s[wv], 1u);
-                            list[pos] = u;
-                        }
+                qv = list[head + lane];
+                ql = lv_of[qv];
+                qb = nb_off[qv];
+                qy = ly_off[qv];
+                bytes_done += 20ull + 4ull * ql;
+            }
+            const uint32_t lscan = wave_incl_scan(ql);
+            const uint32_t pairs = wave_bcast(lscan, kWave - 1);
+            wave_sync();
+            L.scan[lane] = lscan;
+            L.v[lane] = qv;
+            L.l[lane] = ql;
+            L.nb[lane] = qb;
+            L.ly[lane] = qy;
+            wave_sync();
+            for (uint32_t g = lane; g < pairs; g += kWave) {
+                const uint32_t k = search64(L.scan, g);
+                const uint32_t v = L.v[k], l = L.l[k];
+                const uint32_t i = g - (k ? L.scan[k - 1] : 0u) + 1u;   // layer i of v
+                const uint64_t base = L.nb[k], lb = L.ly[k];
+                const uint32_t lo = i > 1u ? ly_end[lb + i - 2u] : 0u, n = ly_end[lb + i - 1u] - lo;
+                uint4 w = philox4x32_10(make_uint4((uint32_t)S.j, i, v,
+                                                   (S.pool << 31) | ((uint32_t)(S.j >> 32) << 24)),
+                                        S.key);
+                ++px;
+                const double U = (double)((uint64_t)(w.x >> 11) | ((uint64_t)w.y << 21)) * 0x1.0p-53;
+                const uint32_t h = layer_count(n, i, l, U, ln, expm);
+                uint32_t mask = 0, np = 0, word = 2, blk = 0;
+                for (uint32_t r = 0; r < h; ++r) {
+                    if (word == 4) {
+                        w = philox4x32_10(make_uint4((uint32_t)S.j, i, v,
+                                                     (S.pool << 31) | ((uint32_t)(S.j >> 32) << 24) | ++blk),
+                                          S.key);
+                        ++px;
+                        word = 0;
                     }
-                    bytes_done += 8ull + 4ull * h;
-                    lo = hi;
+                    const uint32_t x = word == 0 ? w.x : word == 1 ? w.y : word == 2 ? w.z : w.w;
+                    ++word;
+                    const uint32_t aidx = (uint32_t)(((uint64_t)x * (uint64_t)(n - r)) >> 32);
+                    uint32_t pi;
+                    if (n <= 32u) {
+                        // the aidx-th clear bit of the mask
+                        uint32_t c = aidx;
+                        pi = 0;
+                        for (uint32_t t = 0; t < n; ++t) {
+                            if ((mask >> t) & 1u) continue;
+                            if (c == 0) {
+                                pi = t;
+                                break;
+                            }
+                            --c;
+                        }
+                        mask |= 1u << pi;
+                    } else {
+                        pi = aidx;
+                        uint32_t t = 0;
+                        for (; t < np; ++t) {
+                            const uint32_t q = picks[t];
+                            if (q <= pi) ++pi;
+                            else break;
+                        }
+                        for (uint32_t z = np; z > t; --z) picks[z] = picks[z - 1];
+                        picks[t] = pi;
+                        ++np;
+                    }
+                    const uint32_t u = nb[base + lo + pi];
+                    const uint32_t bit = 1u << (u & 31);
+                    if ((atomicOr(&bm[u >> 5], bit) & bit) == 0u) {
+                        const uint32_t pos = atomicAdd(&tail_s[wv], 1u);
+                        list[pos] = u;
+                    }
                 }
+                bytes_done += 8ull + 4ull * h;
             }
             wave_sync();
             head += nbq;
