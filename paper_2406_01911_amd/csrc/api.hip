@@ -159,12 +159,16 @@ void RRWorkspace::release() {
 
 size_t PrepWorkspace::bytes() const {
     size_t b = 0;
-    for (const DevBuf *x : {&k1, &vals, &k2, &info, &pc, &tmp, &counts, &base, &hist, &flag, &cnt, &off64, &lists, &bm}) b += x->bytes;
+    for (const DevBuf *x : {&k1, &vals, &k2, &info, &pc, &tmp, &counts, &base, &hist, &occ, &occ2, &sort_tmp,
+                            &run_start, &pair_val, &flag, &cnt, &off64, &lists, &bm})
+        b += x->bytes;
     return b;
 }
 
 void PrepWorkspace::release() {
-    for (DevBuf *x : {&k1, &vals, &k2, &info, &pc, &tmp, &counts, &base, &hist, &flag, &cnt, &off64, &lists, &bm}) x->release();
+    for (DevBuf *x : {&k1, &vals, &k2, &info, &pc, &tmp, &counts, &base, &hist, &occ, &occ2, &sort_tmp, &run_start,
+                      &pair_val, &flag, &cnt, &off64, &lists, &bm})
+        x->release();
 }
 
 size_t GreedyWorkspace::bytes() const {
@@ -391,7 +395,7 @@ int hyperim_route(hyperim_graph g, uint32_t on, void *stream, uint32_t *n_r1) {
     uint32_t n1 = 0;
     if (on) {
         DeviceLock lk(g->device);
-        HIM_CHECK(route_build(g, as_stream(stream), &n1));
+        HIM_CHECK(route_build(g, *lk.prep, as_stream(stream), &n1));
         g->route_on = true;
     }
     if (n_r1) *n_r1 = n1;

@@ -140,6 +140,7 @@ struct PrepWorkspace {
     DevBuf vals, pc;                       // hubs: partial results, chunk prefix
     DevBuf info, tmp;                      // class counts and sums, scan blocks
     DevBuf counts, base, hist;             // strata counts and statistics
+    DevBuf occ, occ2, sort_tmp, run_start, pair_val;   // layer tables: occurrences, pairs
     DevBuf flag, cnt, off64, lists, bm;    // graph build: checks, degrees, offsets, sort lists and marks
     size_t bytes() const;
     void release();
@@ -275,12 +276,12 @@ int channel_prefix(hyperim_graph g, DevBuf &cnt, DevBuf &tmp, hipStream_t s);
 // Division of g's RR sets into R1 / R2 (Section 4.1) from its strata and
 // layer tables (built here when missing); sets route_P, force_off, force,
 // route_n1, route_B and routed.  *n1 = the number of R1 vertices.
-int route_build(hyperim_graph g, hipStream_t s, uint32_t *n1);
+int route_build(hyperim_graph g, PrepWorkspace &w, hipStream_t s, uint32_t *n1);
 
 // ---- launchers (stratify.hip) -------------------------------------------------
 int stratify_device(hyperim_graph g, PrepWorkspace &w, hipStream_t s);
 // Stratified-setting tables of a stratified graph (layers.hip); lmax = largest l_v.
-int layers_build_device(hyperim_graph g, uint32_t lmax, hipStream_t s);
+int layers_build_device(hyperim_graph g, PrepWorkspace &w, uint32_t lmax, hipStream_t s);
 
 // ---- launchers (scan.hip) -----------------------------------------------------
 // out[0..count] = exclusive prefix sums of in[0..count) plus init; out[count] = total.

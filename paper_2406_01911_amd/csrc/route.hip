@@ -65,7 +65,7 @@ __global__ void k_route_forced(uint32_t n, uint64_t ilim, uint64_t Fc, uint64_t 
 
 }  // namespace
 
-int route_build(hyperim_graph g, hipStream_t s, uint32_t *n1) {
+int route_build(hyperim_graph g, PrepWorkspace &w, hipStream_t s, uint32_t *n1) {
     *n1 = 0;
     g->routed = false;
     const uint32_t n = g->n;
@@ -75,7 +75,7 @@ int route_build(hyperim_graph g, hipStream_t s, uint32_t *n1) {
             HIM_CHECK(channel_prefix(g, cnt, tmp, s));
             HIM_HIP(hipStreamSynchronize(s));
         }
-        HIM_CHECK(layers_build_device(g, g->strat_lmax, s));
+        HIM_CHECK(layers_build_device(g, w, g->strat_lmax, s));
     }
     const uint64_t Fc = g->info.sum_top, Tc = g->info.sum_deg, ilim = n ? g->info.sum_l / n : 0;
     DevBuf cnt_b;

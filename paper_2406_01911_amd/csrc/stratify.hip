@@ -724,13 +724,13 @@ int stratify_device(hyperim_graph g, PrepWorkspace &w, hipStream_t s) {
     info.beta = n ? (double)info.sum_l / (double)n : 0.0;
     info.theta_l = n ? tl / (double)n : 0.0;
     g->strat_lmax = lmax;
-    if (g->layered()) HIM_CHECK(layers_build_device(g, lmax, s));
+    if (g->layered()) HIM_CHECK(layers_build_device(g, w, lmax, s));
     g->stratified = true;
     // a divided graph keeps its division (the same strata give the same one)
     g->routed = false;
     if (g->route_on) {
         uint32_t n1 = 0;
-        const int rc = route_build(g, s, &n1);
+        const int rc = route_build(g, w, s, &n1);
         if (rc != HYPERIM_OK) {
             g->route_on = false;   // left undivided, as after a failed hyperim_route
             return rc;
