@@ -118,13 +118,8 @@ DeviceLock::DeviceLock(int device) {
 DeviceLock::~DeviceLock() { static_cast<DevCtx *>(lock)->mu.unlock(); }
 
 void GreedyWorkspace::release() {
-    for (DevBuf *x : {&cnt, &inv_off, &cursor, &inv, &covered, &chosen, &best, &out, &big, &cursor_big, &flags,
-                      &counters, &scan_tmp, &params, &topk})
-        x->release();
-    if (rounds_exec) (void)hipGraphExecDestroy(rounds_exec);
-    rounds_exec = nullptr;
-    graph_k = 0;
-    graph_params = nullptr;
+    for (DevBuf *x : {&zeroed, &round, &inv_off, &inv, &out, &big, &flags, &counters, &scan_tmp, &params}) x->release();
+    seeds_dev = nullptr;
 }
 
 size_t RRWorkspace::bytes() const {
@@ -173,9 +168,7 @@ void PrepWorkspace::release() {
 
 size_t GreedyWorkspace::bytes() const {
     size_t b = 0;
-    for (const DevBuf *x : {&cnt, &inv_off, &cursor, &inv, &covered, &chosen, &best, &out, &big, &cursor_big, &flags,
-                            &counters, &scan_tmp, &topk})
-        b += x->bytes;
+    for (const DevBuf *x : {&zeroed, &round, &inv_off, &inv, &out, &big, &flags, &counters, &scan_tmp}) b += x->bytes;
     return b;
 }
 

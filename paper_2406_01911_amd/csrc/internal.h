@@ -107,27 +107,18 @@ struct RRStats {
 
 // Workspace of greedy / coverage: one per device, shared by every graph on it.
 struct GreedyWorkspace {
-    DevBuf cnt;       // n uint32  marginal coverage
+    DevBuf zeroed;    // counts, index cursors, covered stamps, chosen flags
+    DevBuf round;     // what rounds hand on: slots, lists, copy of the counts, directory of the big sets
     DevBuf inv_off;   // (n+1) uint64
-    DevBuf cursor;    // n uint32
-    DevBuf inv;       // entries uint32 (set ids)
-    DevBuf covered;   // theta uint32: 0 or covering round + 1
-    DevBuf chosen;    // n uint8
-    DevBuf best;      // k uint64 argmax keys + per-round counters
-    DevBuf out;       // k seeds (uint32) then k gains (uint64)
+    DevBuf inv;       // set ids of the small sets' entries, by vertex
+    DevBuf out;       // k gains (uint64) then k seeds (uint32)
     DevBuf big;       // sets above the big-set size (whole pool prefix)
-    DevBuf cursor_big; // n uint32: big sets per vertex (inverted index)
-    DevBuf flags;     // n uint8 seed marks (coverage)
-    DevBuf counters;  // coverage counters
+    DevBuf flags;     // coverage: counters, then n uint8 seed marks
+    DevBuf counters;  // big sets of the prefix
     DevBuf scan_tmp;
-    DevBuf topk;      // Equation (8): bin counts and sums, selection state, k + 1 top-k sums
     DevBuf params;    // argument block of the per-round kernels
+    uint32_t *seeds_dev = nullptr;   // seeds of the last greedy call, within out
     alignas(16) unsigned char params_host[256];
-    // captured graph of the k greedy rounds and what it was captured for
-    hipStream_t capture = nullptr;
-    hipGraphExec_t rounds_exec = nullptr;
-    uint32_t graph_k = 0, graph_grid[2] = {0, 0}, graph_levels = 0;
-    void *graph_params = nullptr;
     size_t bytes() const;
     void release();
 };
@@ -323,8 +314,8 @@ struct RRWork {
 int rr_incidences(hyperim_graph g, hyperim_pool p, uint64_t theta, hipStream_t s, RRWork *out);
 
 // ---- launchers (greedy.hip) ---------------------------------------------------
-// Greedy max coverage of the pool's first theta sets; the seeds also stay in
-// w.out (device) for coverage_device.
+// Greedy max coverage of the pool's first theta sets; the seeds also stay on
+// the device (w.seeds_dev, until the workspace's next use) for coverage_device.
 // ub_host (k + 1 entries, may be null): for i = 0..k the sum of the k largest
 // marginal coverages given the first i seeds (Equation (8)'s terms).
 int greedy_device(GreedyWorkspace &w, hyperim_graph g, hyperim_pool p, uint64_t theta, uint32_t k, hipStream_t s,

@@ -298,7 +298,9 @@ struct Engine {
             if (bytes > cur) b += bytes - cur + 4.0 * (double)pp->r[x].total;
             need.stage += 4.0 * 1.3 * add + 24.0 * (double)(theta - pp->have[x]);
         }
-        need.greedy = std::max(need.greedy, 4.0 * 1.1 * (double)theta * m + 17.0 * (double)theta + 21.0 * n);
+        // entries of the index, an eighth more for the big sets' directory; per
+        // set stamps and lists; per vertex counts, their copy, offsets, flags
+        need.greedy = std::max(need.greedy, 4.0 * 1.13 * (double)theta * m + 17.0 * (double)theta + 31.0 * n);
         need.n_max = std::max(need.n_max, q->q.graph->n);
         if (!pp->allocated && !pp->users) b += (double)graph_bytes(q->q.graph);
         return (size_t)b;
@@ -521,7 +523,7 @@ struct Engine {
                 HIM_HIP(hipEventRecord(ev.a, s));
                 HIM_CHECK(greedy_device(*lk.gr, g, &q->pp->r[0], theta, k, s, q->seeds.data(), q->gains.data(),
                                         o.bound == 0 ? ub.data() : nullptr));
-                HIM_CHECK(coverage_device(*lk.gr, g, &q->pp->r[1], theta, lk.gr->out.as<uint32_t>(), k, s,
+                HIM_CHECK(coverage_device(*lk.gr, g, &q->pp->r[1], theta, lk.gr->seeds_dev, k, s,
                                           &lambda2));
                 HIM_HIP(hipEventRecord(ev.b, s));
                 HIM_HIP(hipEventSynchronize(ev.b));
