@@ -149,7 +149,7 @@ void RRWorkspace::release() {
     if (host) (void)hipHostFree(host);
     host = nullptr;
     host_words = 0;
-    grid = waves = slots = grid_b = slot_n = slot_words = 0;
+    grid = grid_lds = waves = slots = grid_b = slot_n = slot_words = 0;
 }
 
 size_t PrepWorkspace::bytes() const {
@@ -343,7 +343,7 @@ int hyperim_build_graph(uint32_t n, uint32_t m, const uint32_t *he_off, const ui
         }
         g->nnz = nnz;
         HIM_CHECK(g->he_off.reserve(sizeof(uint32_t) * ((size_t)m + 1), s));
-        HIM_CHECK(g->he_mem.reserve(sizeof(uint32_t) * std::max<uint64_t>(nnz, 1), s));
+        HIM_CHECK(g->he_mem.reserve(sizeof(uint32_t) * ((uint64_t)nnz + 4), s));   // read 4 at a time
         HIM_HIP(hipMemcpyAsync(g->he_off.ptr, he_off, sizeof(uint32_t) * ((size_t)m + 1), kind, s));
         if (nnz) HIM_HIP(hipMemcpyAsync(g->he_mem.ptr, he_mem, sizeof(uint32_t) * (size_t)nnz, kind, s));
         DeviceLock lk(g->device);

@@ -54,7 +54,7 @@ struct RRWorkspace {
     uint32_t grid_b = 0;         // workgroups of a phase B expansion launch
     uint32_t cus = 0;            // compute units of the device
     uint32_t slot_n = 0, slot_words = 0;  // slot list length / bitmap words (largest graph so far)
-    bool lds = false;            // phase A bitmaps in LDS (every graph small)
+    uint32_t grid_lds = 0;       // ... with bitmaps in LDS (launches of small graphs only)
     DevBuf lists;                // slots * slot_n     : member list / BFS queue per slot
     DevBuf bitmaps;              // slots * slot_words : visited bitmap per slot
     DevBuf def_idx;              // deferred sets: launch index (uint64)

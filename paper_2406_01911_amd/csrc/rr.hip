@@ -173,14 +173,42 @@ struct RRArgs {
 constexpr uint32_t kLiveCap = 256;   // live channels a wave holds before marking them (global marks)
 
 struct WaveLdsCore {
-    uint32_t fr_scan[kWave], fr_v[kWave], fr_e0[kWave];
-    uint32_t in_scan[kWave], in_he[kWave], in_hb[kWave], in_hs[kWave], in_v[kWave], in_thr[kWave];
+    uint32_t fr_scan[kWave];                   // gap models: inclusive scan of the frontier's incidence counts
+    uint4 fr[kWave];                           // frontier vertex: id, first incidence - incidences before, thr
+    uint4 in[kWave];                           // incidence: hyperedge, first position, size, runs before
+    uint2 in_vt[kWave];                        // ... its vertex and threshold
+    uint32_t mark[kWave];                      // owners of a window of slots (window_owner)
     uint32_t cont_u[kWave], cont_pos[kWave];   // phase B: members this wave appended, and where
 };
 // With visited bitmaps in global memory a wave also buffers live channels.
 struct WaveLds : WaveLdsCore {
     uint32_t live[kLiveCap];                   // sources of live channels waiting to be marked
 };
+
+// Lanes own consecutive runs of slots (lane k: [start, start + count), starts
+// ascending).  For the window of slots base .. base + 63 this gives each lane
+// the owner of slot base + lane (a slot that somebody owns; else any lane): the
+// owners that begin inside the window leave their lane number at their first
+// slot, a running maximum over the lanes carries it on.  Three LDS accesses in a
+// row and six DPP moves, where a binary search over the starts was a chain of
+// six LDS reads.  Every lane of the wave calls it.
+__device__ __forceinline__ uint32_t window_owner(uint32_t *mark, uint32_t start, uint32_t count, uint32_t base) {
+    const uint32_t lane = lane_id();
+    const uint64_t first = __ballot(start <= base && base - start < count);   // owner of slot base
+    const uint32_t rel = start - base;                                        // wraps for earlier starts
+    mark[lane] = 0u;
+    wave_sync();
+    if (count != 0u && start >= base && rel < kWave) mark[rel] = lane + 1u;
+    wave_sync();
+    uint32_t x = mark[lane];
+    x = wave_scan_op(x, [](uint32_t a, uint32_t b) { return a > b ? a : b; });
+    return x ? x - 1u : (uint32_t)__ffsll((unsigned long long)first) - 1u;
+}
+
+// Four member positions at once, from an address that is a multiple of 4 bytes
+// (he_mem is allocated 16 bytes longer than its entries).
+typedef uint32_t Quad __attribute__((ext_vector_type(4), aligned(4)));
+__device__ __forceinline__ Quad load_quad(const HIM_GLOBAL uint32_t *p) { return *(const HIM_GLOBAL Quad *)p; }
 
 // The task of launch index idx (first task whose end exceeds idx); idx is
 // wave-uniform.
@@ -400,7 +428,13 @@ __device__ __forceinline__ void test_run(const GraphView &G, uint64_t j, uint32_
                                          Lds &L, uint32_t &nlive) {
     uint32_t u[8];
 #pragma unroll
-    for (uint32_t t = 0; t < 8; ++t) u[t] = (t < kRun && active && t < cm) ? G.he_mem[hb + p0 + t] : ve;
+    for (uint32_t t = 0; t < 8; ++t) u[t] = ve;
+    if (active) {
+        static_assert(kRun == 4, "one load per run");
+        const Quad m = load_quad(G.he_mem + (hb + p0));
+#pragma unroll
+        for (uint32_t t = 0; t < kRun; ++t) u[t] = t < cm ? m[t] : ve;
+    }
     uint32_t seen[kRun];
 #pragma unroll
     for (uint32_t t = 0; t < kRun; ++t) seen[t] = 0u;
@@ -574,11 +608,10 @@ __device__ __forceinline__ uint64_t expand_gaps(const GraphView &G, Lds &L, uint
             if (!more && g < D) {
                 uint32_t e = e0 + (uint32_t)g, th = th_uniform;
                 if constexpr (!kUniform) {
-                    const uint32_t k = search64(L.fr_scan, (uint32_t)g);
-                    const uint32_t start = k ? L.fr_scan[k - 1] : 0u;
-                    vv = L.fr_v[k];
-                    e = L.fr_e0[k] + ((uint32_t)g - start);
-                    th = G.thr[vv];
+                    const uint4 f = L.fr[search64(L.fr_scan, (uint32_t)g)];
+                    vv = f.x;
+                    e = f.y + (uint32_t)g;
+                    th = f.z;
                 }
                 he = G.v_he[e];
                 const unsigned long long bs = G.v_hbs[e];
@@ -631,7 +664,7 @@ __device__ __forceinline__ uint64_t expand_gaps(const GraphView &G, Lds &L, uint
 // Levels 2 and 3 of a frontier expansion.  Each lane brings one vertex v with
 // the incidence range [e0, e0 + d) of v_he to expand (d = 0 for none); with
 // kUniform all lanes pass the same v and e0 and d is the wave's incidence
-// count (one heavy vertex), which needs no owner search.  Every channel
+// count (one heavy vertex), which needs no owner search.  thr: v's threshold.  Every channel
 // (he, u -> v) of those incidences is tested with its coin and newly reached
 // members go to `app`.  Level 3 first tests the first run of kRun member
 // positions of each lane's own incidence, then spreads the remaining runs of
@@ -644,24 +677,21 @@ __device__ __forceinline__ uint64_t expand_gaps(const GraphView &G, Lds &L, uint
 template <bool kLds, bool kUniform, bool kGaps, class App, class Lds>
 __device__ __forceinline__ uint64_t expand(const GraphView &G, Lds &L, uint64_t j, uint32_t pool, uint2 key,
                                            uint32_t *bm, bool prefilter, uint32_t v, uint32_t e0, uint32_t d,
-                                           App &app, uint64_t &px, uint32_t w = 0, uint32_t W = 1) {
+                                           uint32_t thr, App &app, uint64_t &px, uint32_t w = 0, uint32_t W = 1) {
     const uint32_t lane = lane_id();
     uint32_t nlive = 0;   // live channels buffered in L.live (wave-uniform)
-    uint32_t D = d;
-    uint32_t th_uniform = 0;
-    if constexpr (kUniform) {
-        th_uniform = G.thr[v];
-    } else {
+    uint32_t D = d, fstart = 0;
+    if constexpr (!kUniform) {
         const uint32_t dscan = wave_incl_scan(d);
         D = wave_bcast(dscan, kWave - 1);
+        fstart = dscan - d;
         wave_sync();
-        L.fr_scan[lane] = dscan;
-        L.fr_v[lane] = v;
-        L.fr_e0[lane] = e0;
+        if constexpr (kGaps) L.fr_scan[lane] = dscan;
+        L.fr[lane] = make_uint4(v, e0 - fstart, thr, 0u);
         wave_sync();
     }
     if constexpr (kGaps) {
-        const uint64_t bytes = expand_gaps<kLds, kUniform>(G, L, j, pool, key, bm, v, e0, D, th_uniform, app, px,
+        const uint64_t bytes = expand_gaps<kLds, kUniform>(G, L, j, pool, key, bm, v, e0, D, thr, app, px,
                                                            nlive, w, W);
         if constexpr (!kLds) flush_live(bm, L, nlive, app);
         wave_sync();
@@ -681,16 +711,14 @@ __device__ __forceinline__ uint64_t expand(const GraphView &G, Lds &L, uint64_t 
     for (uint32_t base = boff * kWave; base < D; base += bstride * kWave) {
         // level 2: one incidence (v, he) per lane
         const uint32_t g = base + lane;
-        uint32_t he = 0, hb = 0, hs = 0, vv = v, th = th_uniform, no = 0;
+        uint32_t he = 0, hb = 0, hs = 0, vv = v, th = thr, no = 0, e = e0 + g;
+        if constexpr (!kUniform) {
+            const uint4 f = L.fr[window_owner(L.mark, fstart, d, base)];
+            vv = f.x;
+            e = f.y + g;
+            th = f.z;
+        }
         if (g < D) {
-            uint32_t e = e0 + g;
-            if constexpr (!kUniform) {
-                const uint32_t k = search64(L.fr_scan, g);
-                const uint32_t start = k ? L.fr_scan[k - 1] : 0u;
-                vv = L.fr_v[k];
-                e = L.fr_e0[k] + (g - start);
-                th = G.thr[vv];
-            }
             he = G.v_he[e];
             const unsigned long long bs = G.v_hbs[e];
             hb = (uint32_t)bs;
@@ -708,32 +736,23 @@ __device__ __forceinline__ uint64_t expand(const GraphView &G, Lds &L, uint64_t 
         const uint32_t rscan = wave_incl_scan(rem);
         const uint32_t R = wave_bcast(rscan, kWave - 1);
         wave_sync();
-        L.in_scan[lane] = rscan;
-        L.in_he[lane] = he;
-        L.in_hb[lane] = hb;
-        L.in_hs[lane] = hs;
-        if constexpr (!kUniform) {
-            L.in_v[lane] = vv;
-            L.in_thr[lane] = th;
-        }
+        L.in[lane] = make_uint4(he, hb, hs, rscan - rem);
+        if constexpr (!kUniform) L.in_vt[lane] = make_uint2(vv, th);
         wave_sync();
         for (uint32_t qb = sub_w * kWave; qb < R; qb += sub * kWave) {
             const uint32_t qg = qb + lane;
             const bool active = qg < R;
-            uint32_t hee = 0, hbk = 0, p0 = 0, cm = 0, ve = v, the = th_uniform;
-            if (active) {
-                const uint32_t k = search64(L.in_scan, qg);
-                const uint32_t start = k ? L.in_scan[k - 1] : 0u;
-                p0 = (qg - start + 1u) * kRun;
-                hee = L.in_he[k];
-                hbk = L.in_hb[k];
-                cm = min(kRun, L.in_hs[k] - p0);
-                if constexpr (!kUniform) {
-                    ve = L.in_v[k];
-                    the = L.in_thr[k];
-                }
+            const uint32_t k = window_owner(L.mark, rscan - rem, rem, qb);
+            const uint4 in = L.in[k];
+            uint32_t ve = v, the = thr;
+            if constexpr (!kUniform) {
+                const uint2 vt = L.in_vt[k];
+                ve = vt.x;
+                the = vt.y;
             }
-            test_run<kLds>(G, j, pool, key, bm, prefilter, active, hee, hbk, p0, cm, ve, the, app, px, L, nlive);
+            const uint32_t p0 = (qg - in.w + 1u) * kRun;
+            test_run<kLds>(G, j, pool, key, bm, prefilter, active, in.x, in.y, p0, min(kRun, in.z - p0), ve, the, app,
+                           px, L, nlive);
         }
     }
     if constexpr (!kLds) flush_live(bm, L, nlive, app);
@@ -791,7 +810,7 @@ __global__ __launch_bounds__(kWG) void k_rr_light(RRArgs a) {
         bm = a.bitmaps + (uint64_t)slot * a.slot_words;
     }
     wave_sync();
-    bool can_defer = !kLdsBitmap;
+    bool can_defer = true;
     uint64_t bytes_done = 0, px = 0;
 
     for (;;) {
@@ -814,15 +833,17 @@ __global__ __launch_bounds__(kWG) void k_rr_light(RRArgs a) {
         bool deferred = false;
 
         while (head < app.size) {
-            // queue entries were stored by other lanes of this wave: wait for
-            // the stores and drop stale L1 lines before reading them
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+            // queue entries were stored by other lanes of this wave: a wave's
+            // own accesses stay in order, so there is nothing to wait for (and
+            // no L1 line of the graph to drop)
+            wave_sync();
             const uint32_t nb = min((uint32_t)kWave, app.size - head);
-            uint32_t v = 0, e0 = 0, d = 0;
+            uint32_t v = 0, e0 = 0, d = 0, thr = 0;
             if (lane < nb) {
                 v = list[head + lane];
                 e0 = G.v_off[v];
                 d = G.v_off[v + 1] - e0;
+                thr = G.thr[v];
             }
             if (can_defer && (spent > a.budget || __ballot(d > a.heavy) != 0)) {
                 // hand the set over to phase B and continue with a fresh slot
@@ -839,18 +860,33 @@ __global__ __launch_bounds__(kWG) void k_rr_light(RRArgs a) {
                         a.def_size[dd] = app.size;
                         a.def_task[dd] = task;
                     }
+                    if constexpr (kLdsBitmap) {
+                        // the marks move to the slot's bitmap (all zero so far)
+                        uint32_t *gbm = a.bitmaps + (uint64_t)slot * a.slot_words;
+                        wave_sync();
+                        for (uint32_t i = lane; i < G.bm_words; i += kWave) {
+                            gbm[i] = bm[i];
+                            bm[i] = 0u;
+                        }
+                        wave_sync();
+                    } else {
+                        bm = a.bitmaps + (uint64_t)fresh_slot * a.slot_words;
+                    }
                     slot = fresh_slot;
                     list = a.lists + (uint64_t)slot * a.slot_n;
-                    bm = a.bitmaps + (uint64_t)slot * a.slot_words;
                     deferred = true;
                     break;
                 }
                 can_defer = false;   // no spare slot left: this wave finishes its sets itself
             }
             head += nb;
-            spent += wave_bcast(wave_incl_scan(d), kWave - 1);
             bytes_done += 20ull * nb;
-            bytes_done += expand<kLdsBitmap, false, kGaps>(G, L, S.j, S.pool, S.key, bm, false, v, e0, d, app, px);
+            const uint64_t bytes =
+                expand<kLdsBitmap, false, kGaps>(G, L, S.j, S.pool, S.key, bm, false, v, e0, d, thr, app, px);
+            bytes_done += bytes;
+            // incidences read: hyperedges and member positions, from 12 bytes
+            // per hyperedge and 4 per position
+            spent += bytes / 4u - 2ull * wave_sum(d);
         }
         if (deferred) continue;
         const uint32_t size = app.size;
@@ -859,7 +895,7 @@ __global__ __launch_bounds__(kWG) void k_rr_light(RRArgs a) {
         unsigned long long off = 0;
         if (lane == 0) off = atomicAdd(&a.ctr[kBump], (unsigned long long)size);
         off = wave_bcast64(off, 0);
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        wave_sync();
         if (off + size <= a.stage_cap) {
             if (size <= kSortMax) {
                 uint32_t P2 = kWave;
@@ -1470,20 +1506,22 @@ __global__ __launch_bounds__(kWG) void k_expand(const RRArgs *__restrict__ ap, u
             uni(__hip_atomic_load(size_p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) >= a.prefilter_min;
         ContAppend app{list, size_p, G.n, L.cont_u, L.cont_pos, 0u};
         if (!heavy) {
-            uint32_t v = 0, e0 = 0, deg = 0;
+            uint32_t v = 0, e0 = 0, deg = 0, thr = 0;
             const uint32_t raw = lane < item.z ? list[item.y + lane] : kExpanded;
             if ((raw & kExpanded) == 0u) {   // entries marked expanded are done
                 v = raw;
                 e0 = G.v_off[v];
                 deg = G.v_off[v + 1] - e0;
+                thr = G.thr[v];
                 if (heavy_split(deg, a.chunk).count) deg = 0;   // expanded by its heavy items
             }
             if (w == 0) bytes_done += 20ull * (uint64_t)__popcll(__ballot((raw & kExpanded) == 0u));
-            bytes_done += expand<false, false, kGaps>(G, L, S.j, S.pool, S.key, bm, prefilter, v, e0, deg, app, px, w, W);
+            bytes_done += expand<false, false, kGaps>(G, L, S.j, S.pool, S.key, bm, prefilter, v, e0, deg, thr, app, px, w,
+                                                       W);
         } else {
             // one heavy vertex: incidences [item.z, item.w) of vertex item.y
             bytes_done += expand<false, true, kGaps>(G, L, S.j, S.pool, S.key, bm, prefilter, item.y, item.z,
-                                              item.w - item.z, app, px, w, W);
+                                                      item.w - item.z, uni(G.thr[item.y]), app, px, w, W);
         }
         // Continuation: when this wave appended at most 64 members, all light
         // and together under seg incidences, it expands them itself (up to
@@ -1494,12 +1532,13 @@ __global__ __launch_bounds__(kWG) void k_expand(const RRArgs *__restrict__ ap, u
             const uint32_t cn = app.count;
             if (cn == 0 || cn > kWave) break;
             wave_sync();
-            uint32_t v = 0, e0 = 0, deg = 0, pos = 0;
+            uint32_t v = 0, e0 = 0, deg = 0, pos = 0, thr = 0;
             if (lane < cn) {
                 v = L.cont_u[lane];
                 pos = L.cont_pos[lane];
                 e0 = G.v_off[v];
                 deg = G.v_off[v + 1] - e0;
+                thr = G.thr[v];
             }
             const uint32_t tot = wave_bcast(wave_incl_scan(deg), kWave - 1);
             if (__ballot(lane < cn && deg > a.chunk) != 0 || tot > a.seg) break;   // left to k_plan
@@ -1507,7 +1546,8 @@ __global__ __launch_bounds__(kWG) void k_expand(const RRArgs *__restrict__ ap, u
             if (lane < cn) list[pos] = v | kExpanded;
             app.count = 0;
             bytes_done += 20ull * cn;
-            bytes_done += expand<false, false, kGaps>(G, L, S.j, S.pool, S.key, bm, prefilter, v, e0, deg, app, px, 0u, 1u);
+            bytes_done += expand<false, false, kGaps>(G, L, S.j, S.pool, S.key, bm, prefilter, v, e0, deg, thr, app, px,
+                                                       0u, 1u);
         }
     }
     if (lane == 0 && bytes_done) atomicAdd(&a.ctr[kBytesB], bytes_done);
@@ -2307,9 +2347,8 @@ struct LaunchShape {
 // occupancy), slots (phase A waves plus spare slots for deferred sets, within
 // kSlotBudget bytes) and the phase B grid.
 struct SlotLayout {
-    uint64_t grid, waves, slots, grid_b, bytes;
+    uint64_t grid, grid_lds, waves, slots, grid_b, bytes;
     uint32_t cus;
-    bool lds;
 };
 
 int slot_layout(uint32_t n_max, SlotLayout *out) {
@@ -2319,23 +2358,22 @@ int slot_layout(uint32_t n_max, SlotLayout *out) {
     HIM_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu_lds, k_rr_light<true, false>, kWG, 0));
     HIM_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu_glb, k_rr_light<false, false>, kWG, 0));
     HIM_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu_b, k_expand<false>, kWG, 0));
-    const bool lds = n_max <= kLdsBitmapWords * 32u;
     const uint64_t words = ((uint64_t)n_max + 31u) / 32u;
-    const uint64_t per_slot = (uint64_t)n_max * 4u + (lds ? 0u : words * 4u);
+    const uint64_t per_slot = (uint64_t)n_max * 4u + words * 4u;
     const uint64_t max_slots = std::max<uint64_t>(kSlotBudget / std::max<uint64_t>(per_slot, 1), 2 * kWavesPerWG);
-    uint64_t grid = (uint64_t)cus * (uint64_t)std::max(lds ? per_cu_lds : per_cu_glb, 1);
+    uint64_t grid = (uint64_t)cus * (uint64_t)std::max(per_cu_glb, 1);
     // phase A keeps at least half of the slots spare for deferred sets
     grid = std::min<uint64_t>(grid, max_slots / (2 * kWavesPerWG));
     grid = std::max<uint64_t>(grid, 1);
     const uint64_t waves = grid * kWavesPerWG;
-    const uint64_t slots = lds ? waves : std::min<uint64_t>(max_slots, 4 * waves);
+    const uint64_t slots = std::min<uint64_t>(max_slots, 4 * waves);
+    out->grid_lds = std::min<uint64_t>(grid, (uint64_t)cus * (uint64_t)std::max(per_cu_lds, 1));
     out->grid = grid;
     out->waves = waves;
     out->slots = slots;
     out->grid_b = (uint64_t)cus * (uint64_t)std::max(per_cu_b, 1);
     out->bytes = slots * per_slot;
     out->cus = (uint32_t)cus;
-    out->lds = lds;
     return HYPERIM_OK;
 }
 
@@ -2344,7 +2382,7 @@ int slot_layout(uint32_t n_max, SlotLayout *out) {
 int ensure_workspace(RRWorkspace &ws, uint32_t n_max, hipStream_t s, LaunchShape *shape) {
     const bool lds = n_max <= kLdsBitmapWords * 32u;
     const uint32_t words = (uint32_t)(((uint64_t)n_max + 31u) / 32u);
-    if (ws.grid != 0 && (ws.slot_n < n_max || ws.lds != lds)) {
+    if (ws.grid != 0 && ws.slot_n < n_max) {
         HIM_HIP(hipStreamSynchronize(s));
         ws.lists.release();
         ws.bitmaps.release();
@@ -2361,12 +2399,10 @@ int ensure_workspace(RRWorkspace &ws, uint32_t n_max, hipStream_t s, LaunchShape
         ws.cus = L.cus;
         ws.slot_n = std::max<uint32_t>(n_max, 1);
         ws.slot_words = words;
-        ws.lds = lds;
+        ws.grid_lds = (uint32_t)L.grid_lds;
         HIM_CHECK(ws.lists.reserve(sizeof(uint32_t) * (size_t)slots * ws.slot_n, s));
-        if (!lds) {
-            HIM_CHECK(ws.bitmaps.reserve(sizeof(uint32_t) * (size_t)slots * words, s));
-            HIM_HIP(hipMemsetAsync(ws.bitmaps.ptr, 0, sizeof(uint32_t) * (size_t)slots * words, s));
-        }
+        HIM_CHECK(ws.bitmaps.reserve(sizeof(uint32_t) * (size_t)slots * words, s));
+        HIM_HIP(hipMemsetAsync(ws.bitmaps.ptr, 0, sizeof(uint32_t) * (size_t)slots * words, s));
         HIM_CHECK(ws.counters.reserve(sizeof(unsigned long long) * kNumCtr, s));
         // deferred-set arrays for as many sets as there are slots (phase A may
         // run fewer waves than the occupancy allows, leaving more spare slots)
@@ -2376,7 +2412,7 @@ int ensure_workspace(RRWorkspace &ws, uint32_t n_max, hipStream_t s, LaunchShape
         HIM_CHECK(ws.items.reserve(sizeof(uint4) * (size_t)kItemCap, s));
         HIM_CHECK(ws.args_dev.reserve(sizeof(RRArgs), s));
     }
-    shape->grid = ws.grid;
+    shape->grid = lds ? ws.grid_lds : ws.grid;
     shape->slots = ws.slots;
     shape->grid_b = ws.grid_b;
     shape->cus = ws.cus;
@@ -2601,10 +2637,10 @@ int run_launch(RRWorkspace &ws, RRStats &st, const hyperim_tuning &tune, RRArgs 
     HIM_HIP(hipGetLastError());
     st.launches += 1;
 
-    // phase B: supersteps over the deferred sets (LDS-bitmap launches defer none)
-    bool phase_b = !shape.lds;
+    // phase B: supersteps over the deferred sets
+    bool phase_b = true;
     uint64_t ndef = 0;
-    if (phase_b && !expect_defer) {
+    if (!expect_defer) {
         HIM_HIP(hipMemcpyAsync(h + kHostBatch, ctr, sizeof(unsigned long long) * kNumCtr, hipMemcpyDeviceToHost, s));
         HIM_HIP(hipStreamSynchronize(s));
         ndef = h[kHostBatch + kDefCount];
@@ -3241,9 +3277,11 @@ int rr_generate_into(RRWorkspace &ws, RRStats &st, const std::vector<RRTask> &ta
         a.big_ids = ws.big_ids.as<uint64_t>();
         const uint32_t grid =
             form == 0 ? grid_a : (uint32_t)std::min<uint64_t>(grid_a, div_up(a.count, kWavesPerWG));
-        // a graph whose sets were never deferred before is checked after phase A
+        // a graph whose sets were never deferred before is checked after phase
+        // A, a small one (marks in LDS) until one of its sets was
         bool expect_defer = false;
-        for (const Slice &sl : slices) expect_defer |= tasks[sl.task].g->rr_defer != 0.0;
+        for (const Slice &sl : slices)
+            expect_defer |= shape.lds ? tasks[sl.task].g->rr_defer > 0.0 : tasks[sl.task].g->rr_defer != 0.0;
         // compaction offsets of every slice, queued behind the launch so that
         // one wait covers both (a launch whose stage overflowed discards them)
         std::vector<int> scan_rc(slices.size(), HYPERIM_OK);
