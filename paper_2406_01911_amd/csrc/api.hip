@@ -188,7 +188,7 @@ SharedBytes shared_bytes() {
 size_t graph_bytes(hyperim_graph g) {
     size_t b = 0;
     for (const DevBuf *x : {&g->he_off, &g->he_mem, &g->v_off, &g->v_he, &g->thr, &g->c, &g->weight, &g->bytesw,
-                            &g->phiw, &g->v_hbs, &g->chan, &g->l, &g->deg, &g->top, &g->stratum, &g->P,
+                            &g->phiw, &g->vrec, &g->irec, &g->chan, &g->l, &g->deg, &g->top, &g->stratum, &g->P,
                             &g->lay_nb_off, &g->lay_nb, &g->lay_ly_off, &g->lay_ly_end, &g->lay_ln, &g->lay_expm,
                             &g->route_P, &g->force_off, &g->force})
         b += x->bytes;
@@ -197,7 +197,7 @@ size_t graph_bytes(hyperim_graph g) {
 
 void release_graph(hyperim_graph g) {
     for (DevBuf *b : {&g->he_off, &g->he_mem, &g->v_off, &g->v_he, &g->thr, &g->c, &g->weight, &g->bytesw,
-                      &g->phiw, &g->v_hbs, &g->chan, &g->l, &g->deg, &g->top, &g->stratum, &g->P,
+                      &g->phiw, &g->vrec, &g->irec, &g->chan, &g->l, &g->deg, &g->top, &g->stratum, &g->P,
                             &g->lay_nb_off, &g->lay_nb, &g->lay_ly_off, &g->lay_ly_end, &g->lay_ln, &g->lay_expm,
                             &g->route_P, &g->force_off, &g->force})
         b->release();

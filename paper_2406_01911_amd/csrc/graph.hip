@@ -353,31 +353,36 @@ __global__ void k_thresholds(uint32_t n, uint32_t model, float p, const uint32_t
 
 // Philox blocks of a vertex's expansion: sum over its hyperedges of
 // ceil(|he| / 4), from the prefix of those over the incidences.
+// With it the vertex records are complete.
 __global__ void k_philox_weight(uint32_t n, const uint32_t *__restrict__ v_off,
-                                const unsigned long long *__restrict__ pre, unsigned long long *__restrict__ phiw) {
+                                const unsigned long long *__restrict__ pre, const uint32_t *__restrict__ thr,
+                                unsigned long long *__restrict__ phiw, uint4 *__restrict__ vrec) {
     const uint32_t v = blockIdx.x * blockDim.x + threadIdx.x;
-    if (v < n) phiw[v] = pre[v_off[v + 1]] - pre[v_off[v]];
+    if (v >= n) return;
+    const uint32_t e0 = v_off[v], e1 = v_off[v + 1];
+    const unsigned long long q = pre[e1] - pre[e0];
+    phiw[v] = q;
+    vrec[v] = make_uint4(e0, e1 - e0, thr[v], (uint32_t)min(q, 0xFFFFFFFFull));
 }
 
-// Per incidence: first member position and size of its hyperedge, its channels
-// |he| - 1 (the members other than the vertex itself) and its Philox blocks
-// ceil(|he| / 4).
+// Per incidence: its record, its channels |he| - 1 (the members other than the
+// vertex itself) and its Philox blocks ceil(|he| / 4).
 __global__ void k_incidence_spans(uint64_t nnz, const uint32_t *__restrict__ v_he, const uint32_t *__restrict__ he_off,
-                                  uint2 *__restrict__ v_hbs, uint32_t *__restrict__ channels,
+                                  uint4 *__restrict__ irec, uint32_t *__restrict__ channels,
                                   uint32_t *__restrict__ quads) {
     for (uint64_t e = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; e < nnz; e += (uint64_t)gridDim.x * blockDim.x) {
         const uint32_t he = v_he[e];
         const uint32_t b = he_off[he], sz = he_off[he + 1] - b;
-        v_hbs[e] = make_uint2(b, sz);
+        irec[e] = make_uint4(he, b, sz, 0u);
         channels[e] = sz - 1u;
         quads[e] = (sz + 3u) / 4u;
     }
 }
 
 // Channels of each incidence (v, he): |he| - 1.
-__global__ void k_channel_counts(uint64_t nnz, const uint2 *__restrict__ v_hbs, uint32_t *__restrict__ cnt) {
+__global__ void k_channel_counts(uint64_t nnz, const uint4 *__restrict__ irec, uint32_t *__restrict__ cnt) {
     for (uint64_t e = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; e < nnz; e += (uint64_t)gridDim.x * blockDim.x)
-        cnt[e] = v_hbs[e].y - 1u;
+        cnt[e] = irec[e].z - 1u;
 }
 
 uint32_t grid_for(uint64_t items, uint32_t block = kBlock, uint32_t cap = 65535u * 8u) {
@@ -389,7 +394,7 @@ uint32_t grid_for(uint64_t items, uint32_t block = kBlock, uint32_t cap = 65535u
 }  // namespace
 
 // Exclusive prefix over all incidences of their channel counts |he| - 1: the
-// channels into v are chan[v_off[v]] .. chan[v_off[v + 1]] (needs v_hbs).
+// channels into v are chan[v_off[v]] .. chan[v_off[v + 1]] (needs irec).
 // cnt and tmp are scratch the caller keeps alive until the stream has run.
 int channel_prefix(hyperim_graph g, DevBuf &cnt, DevBuf &tmp, hipStream_t s) {
     const uint64_t nnz = g->nnz;
@@ -397,7 +402,7 @@ int channel_prefix(hyperim_graph g, DevBuf &cnt, DevBuf &tmp, hipStream_t s) {
     HIM_CHECK(cnt.reserve(sizeof(uint32_t) * std::max<uint64_t>(nnz, 1), s));
     if (nnz)
         hipLaunchKernelGGL(k_channel_counts, dim3(grid_for(nnz, kBlock, 8192)), dim3(kBlock), 0, s, nnz,
-                           g->v_hbs.as<uint2>(), cnt.as<uint32_t>());
+                           g->irec.as<uint4>(), cnt.as<uint32_t>());
     HIM_HIP(hipGetLastError());
     return scan_u32_to_u64(cnt.as<uint32_t>(), g->chan.as<uint64_t>(), nnz, 0, tmp, s);
 }
@@ -478,7 +483,8 @@ int graph_build_device(hyperim_graph g, PrepWorkspace &w, hipStream_t s) {
     HIM_CHECK(g->weight.reserve(sizeof(uint64_t) * n, s));
     HIM_CHECK(g->bytesw.reserve(sizeof(uint64_t) * n, s));
     HIM_CHECK(g->phiw.reserve(sizeof(uint64_t) * n, s));
-    HIM_CHECK(g->v_hbs.reserve(sizeof(uint2) * std::max<uint64_t>(nnz, 1), s));
+    HIM_CHECK(g->vrec.reserve(sizeof(uint4) * n, s));
+    HIM_CHECK(g->irec.reserve(sizeof(uint4) * std::max<uint64_t>(nnz, 1), s));
     const size_t cnt_words = std::max<uint64_t>(nnz, 1);
     HIM_CHECK(w.k1.reserve(2 * sizeof(uint32_t) * cnt_words, s));
     HIM_CHECK(w.k2.reserve(sizeof(uint64_t) * (nnz + 1), s));
@@ -489,14 +495,15 @@ int graph_build_device(hyperim_graph g, PrepWorkspace &w, hipStream_t s) {
     uint64_t *chan = keep ? g->chan.as<uint64_t>() : w.k2.as<uint64_t>();
     if (nnz)
         hipLaunchKernelGGL(k_incidence_spans, dim3(grid_for(nnz, kBlock, 8192)), dim3(kBlock), 0, s, nnz, v_he,
-                           g->he_off.as<uint32_t>(), g->v_hbs.as<uint2>(), channels, quads);
+                           g->he_off.as<uint32_t>(), g->irec.as<uint4>(), channels, quads);
     HIM_CHECK(scan_u32_to_u64(channels, chan, nnz, 0, tmp_b, s));
     hipLaunchKernelGGL(k_thresholds, dim3(grid_for(n)), dim3(kBlock), 0, s, n, g->prob.model, g->prob.p, v_off,
                        reinterpret_cast<const unsigned long long *>(chan), g->c.as<unsigned long long>(),
                        g->thr.as<uint32_t>(), g->weight.as<unsigned long long>(), g->bytesw.as<unsigned long long>());
     HIM_CHECK(scan_u32_to_u64(quads, w.k2.as<uint64_t>(), nnz, 0, tmp_b, s));
     hipLaunchKernelGGL(k_philox_weight, dim3(grid_for(n)), dim3(kBlock), 0, s, n, v_off,
-                       w.k2.as<unsigned long long>(), g->phiw.as<unsigned long long>());
+                       w.k2.as<unsigned long long>(), g->thr.as<uint32_t>(), g->phiw.as<unsigned long long>(),
+                       g->vrec.as<uint4>());
     HIM_HIP(hipGetLastError());
     HIM_HIP(hipStreamSynchronize(s));
     if (hflag[0] & kDuplicate) {

@@ -167,10 +167,12 @@ struct hyperim_graph_s {
     // weight = d(v) + S(v) incidences read when v is expanded; bytesw = 20 + 12 d(v) + 4 S(v)
     // algorithmic bytes of v as an RR-set member (d = hyperedges of v, S = their total size);
     // phiw = sum over v's hyperedges of ceil(|he| / 4), the Philox blocks of v's expansion
-    // v_hbs[e] = (he_off[v_he[e]], size of that hyperedge), uint2 per incidence
+    // vrec[v] = (first incidence, incidences, threshold, phiw capped at 32 bits)
+    // and irec[e] = (hyperedge, its first member position, its size, 0), uint4:
+    // what an expansion needs of a vertex or an incidence, in one cache line
     // chan (linear-threshold graphs only): exclusive prefix over v_he of the
     // incidences' channel counts |he| - 1, nnz + 1 entries
-    hyperim::DevBuf he_off, he_mem, v_off, v_he, thr, c, weight, bytesw, phiw, v_hbs, chan;
+    hyperim::DevBuf he_off, he_mem, v_off, v_he, thr, c, weight, bytesw, phiw, vrec, irec, chan;
     // stratified setting (built by stratify): A(v) by layers -- members
     // lay_nb[lay_nb_off[v] ..], layer i ending at lay_nb_off[v] +
     // lay_ly_end[lay_ly_off[v] + i - 1] -- and the host-evaluated tables

@@ -38,6 +38,23 @@ __host__ __device__ __forceinline__ HeavySplit heavy_split(uint32_t deg, uint32_
     return h;
 }
 
+// A vertex's incidences differ in size: its expansion reads `quads` runs of four
+// member positions.  Where those are more than kPlanQuads per incidence, chunks
+// are cut shorter, so that they hold about chunk * kPlanQuads runs, and a light
+// vertex weighs its runs.  (Hyperedges of up to 1000 members, chunks by
+// incidences alone: an item took up to a millisecond of one wave.)
+constexpr uint32_t kPlanQuads = 8;
+__host__ __device__ __forceinline__ uint32_t weighted_chunk(uint32_t deg, uint32_t quads, uint32_t chunk) {
+    const uint64_t even = (uint64_t)kPlanQuads * deg;
+    if (quads <= even) return chunk;
+    const uint64_t c = (uint64_t)chunk * even / quads;
+    return c > 1u ? (uint32_t)c : 1u;
+}
+__host__ __device__ __forceinline__ uint32_t light_weight(uint32_t deg, uint32_t quads) {
+    const uint32_t w = plan_div_up(quads, kPlanQuads);
+    return deg > w ? deg : w;
+}
+
 // Bundled mode: an entry's work is its incidences times the sets in its mask;
 // chunks of about `chunk` (incidence, set) pairs, i.e. chunk / sets
 // incidences (at least 1), and at most kPlanItemCap / 128 chunks per entry so

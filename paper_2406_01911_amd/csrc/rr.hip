@@ -89,11 +89,12 @@ enum Ctr {
 };
 
 // One graph of a launch group.
-// v_hbs[e] = (first member position, size) of hyperedge v_he[e], beside the
-// incidence list so that an incidence's hyperedge needs no dependent load.
+// vrec[v] = (first incidence, incidences, threshold, Philox blocks) and irec[e]
+// = (hyperedge, its first member position, its size, 0): one 16-byte read, and
+// one cache line, for all that an expansion needs of a vertex or an incidence.
 struct GraphDesc {
-    const uint32_t *he_off, *he_mem, *v_off, *v_he, *thr, *P;
-    const unsigned long long *v_hbs;   // low word: first position, high word: size
+    const uint32_t *he_mem, *P;
+    const uint4 *vrec, *irec;
     uint32_t n, bm_words;
     // linear-threshold graphs: channels of the incidences before each one
     // (exclusive prefix of |he| - 1 over v_he, nnz + 1 entries); else null
@@ -114,9 +115,10 @@ struct GraphDesc {
 // memory, where the compiler cannot tell their address space and would emit
 // flat loads.
 #define HIM_GLOBAL __attribute__((address_space(1)))
+typedef uint32_t Rec __attribute__((ext_vector_type(4)));
 struct GraphView {
-    const HIM_GLOBAL uint32_t *he_off, *he_mem, *v_off, *v_he, *thr, *P, *rP;
-    const HIM_GLOBAL unsigned long long *v_hbs;
+    const HIM_GLOBAL uint32_t *he_mem, *P, *rP;
+    const HIM_GLOBAL Rec *vrec, *irec;
     uint32_t n, bm_words, rn1;
 };
 
@@ -124,13 +126,10 @@ struct GraphView {
 // registers.
 __device__ __forceinline__ GraphView graph_view(const GraphDesc &d) {
     GraphView v;
-    v.he_off = uni_ptr((const HIM_GLOBAL uint32_t *)d.he_off);
     v.he_mem = uni_ptr((const HIM_GLOBAL uint32_t *)d.he_mem);
-    v.v_off = uni_ptr((const HIM_GLOBAL uint32_t *)d.v_off);
-    v.v_he = uni_ptr((const HIM_GLOBAL uint32_t *)d.v_he);
-    v.thr = uni_ptr((const HIM_GLOBAL uint32_t *)d.thr);
     v.P = uni_ptr((const HIM_GLOBAL uint32_t *)d.P);
-    v.v_hbs = uni_ptr((const HIM_GLOBAL unsigned long long *)d.v_hbs);
+    v.vrec = uni_ptr((const HIM_GLOBAL Rec *)d.vrec);
+    v.irec = uni_ptr((const HIM_GLOBAL Rec *)d.irec);
     v.rP = uni_ptr((const HIM_GLOBAL uint32_t *)d.rP);
     v.n = uni(d.n);
     v.bm_words = uni(d.bm_words);
@@ -613,10 +612,10 @@ __device__ __forceinline__ uint64_t expand_gaps(const GraphView &G, Lds &L, uint
                     e = f.y + (uint32_t)g;
                     th = f.z;
                 }
-                he = G.v_he[e];
-                const unsigned long long bs = G.v_hbs[e];
-                hb = (uint32_t)bs;
-                hs = (uint32_t)(bs >> 32);
+                const Rec ir = G.irec[e];
+                he = ir[0];
+                hb = ir[1];
+                hs = ir[2];
                 bytes += 12u;
                 more = th != 0u && hs != 0u;   // threshold 0: no channel into vv is live
                 cur = 0u;
@@ -719,10 +718,10 @@ __device__ __forceinline__ uint64_t expand(const GraphView &G, Lds &L, uint64_t 
             th = f.z;
         }
         if (g < D) {
-            he = G.v_he[e];
-            const unsigned long long bs = G.v_hbs[e];
-            hb = (uint32_t)bs;
-            hs = (uint32_t)(bs >> 32);
+            const Rec ir = G.irec[e];
+            he = ir[0];
+            hb = ir[1];
+            hs = ir[2];
             no = th ? (hs + kRun - 1u) / kRun : 0u;   // threshold 0: no channel into vv is live
             if (sub_w == 0) bytes += 12u + 4u * hs;
         }
@@ -841,9 +840,10 @@ __global__ __launch_bounds__(kWG) void k_rr_light(RRArgs a) {
             uint32_t v = 0, e0 = 0, d = 0, thr = 0;
             if (lane < nb) {
                 v = list[head + lane];
-                e0 = G.v_off[v];
-                d = G.v_off[v + 1] - e0;
-                thr = G.thr[v];
+                const Rec r = G.vrec[v];
+                e0 = r[0];
+                d = r[1];
+                thr = r[2];
             }
             if (can_defer && (spent > a.budget || __ballot(d > a.heavy) != 0)) {
                 // hand the set over to phase B and continue with a fresh slot
@@ -1007,12 +1007,13 @@ __global__ __launch_bounds__(kWG) void k_lt_walk(RRArgs a) {
         }
         uint32_t size = 1, cur = root;
         for (;;) {
-            const uint32_t e0 = uni(G.v_off[cur]), e1 = uni(G.v_off[cur + 1]);
+            const Rec vr = G.vrec[cur];
+            const uint32_t e0 = uni(vr[0]), e1 = e0 + uni(vr[1]);
             const uint64_t base = uni64(chan[e0]);
             const uint64_t C = uni64(chan[e1]) - base;   // c(v)
             bytes_done += 36ull;
             if (C == 0) break;
-            const uint32_t thr = uni(G.thr[cur]);
+            const uint32_t thr = uni(vr[2]);
             const uint64_t cap = (1ull << 32) / C;
             const uint64_t W = min(thr == kAlways ? (1ull << 32) : (uint64_t)thr, cap);
             const uint32_t x = uni(philox4x32_10(coin_counter(S.j, kLtSlot, cur, S.pool, 0u), S.key).x);
@@ -1034,9 +1035,9 @@ __global__ __launch_bounds__(kWG) void k_lt_walk(RRArgs a) {
             }
             const uint64_t ok = __ballot(lo + lane < hi && chan[lo + lane] <= t);
             const uint32_t e = lo + 63u - (uint32_t)__clzll((long long)ok);
-            const unsigned long long bl = uni64(G.v_hbs[e]);
+            const Rec ir = G.irec[e];
             const uint64_t k = t - uni64(chan[e]);   // rank among e's channels
-            const uint32_t hb = (uint32_t)bl, hs = (uint32_t)(bl >> 32);
+            const uint32_t hb = uni(ir[1]), hs = uni(ir[2]);
             // member k of the hyperedge with cur skipped
             uint32_t pc = hs;
             for (uint32_t p0 = 0; p0 < hs; p0 += kWave) {
@@ -1387,6 +1388,11 @@ __device__ __forceinline__ uint32_t owner_of(uint32_t hscan, uint32_t q) {
 constexpr uint32_t kShareMax = 16;   // waves that may share one item
 constexpr uint32_t kContLevels = 8;  // levels a wave may expand past its item
 
+// Queue entries a planning wave takes per reservation of items, in batches of
+// 64: the reservations of all waves meet at one counter, at 7.5 ns each (sets
+// with frontiers of thousands spent 0.38 ms a superstep on them).
+constexpr uint32_t kPlanBatches = 8;
+
 // k_plan and k_expand read their arguments from device memory, so that a
 // captured batch of supersteps serves every launch group.
 __global__ __launch_bounds__(kWG) void k_plan(const RRArgs *__restrict__ ap, uint32_t parity) {
@@ -1401,40 +1407,60 @@ __global__ __launch_bounds__(kWG) void k_plan(const RRArgs *__restrict__ ap, uin
         const uint32_t size = uni(a.def_size[d]);
         const uint32_t *list = a.lists + (uint64_t)uni(a.def_slot[d]) * a.slot_n;
         const GraphView G = graph_view(a.graphs[uni(a.tasks[uni(a.def_task[d])].graph)]);
+        uint32_t most = kPlanBatches;   // batches of 64 entries planned at once
         while (head < size) {
-            uint32_t nb = min((uint32_t)kWave, size - head);
-            uint32_t v = 0, e0 = 0, deg = 0, hv = 0, light = 0, cv = a.chunk;
-            const uint32_t raw = lane < nb ? list[head + lane] : kExpanded;
-            if (__ballot((raw & kExpanded) == 0u) == 0) {   // all expanded already
-                head += nb;
+            const uint32_t batches = min(most, (size - head + kWave - 1u) / kWave);
+            uint32_t v[kPlanBatches], e0[kPlanBatches], deg[kPlanBatches], cv[kPlanBatches], hv[kPlanBatches],
+                hscan[kPlanBatches];
+            uint64_t firsts[kPlanBatches];
+            uint32_t need = 0;
+#pragma unroll
+            for (uint32_t b = 0; b < kPlanBatches; ++b) {
+                v[b] = b < batches && head + b * kWave + lane < size ? list[head + b * kWave + lane] : kExpanded;
+            }
+#pragma unroll
+            for (uint32_t b = 0; b < kPlanBatches; ++b) {
+                e0[b] = deg[b] = hv[b] = hscan[b] = 0u;
+                firsts[b] = 0ull;
+                cv[b] = a.chunk;
+                const bool fresh = (v[b] & kExpanded) == 0u;
+                if (__ballot(fresh) == 0ull) continue;   // all expanded already, or no such batch
+                uint32_t light = 0;
+                if (fresh) {
+                    const Rec r = G.vrec[v[b]];
+                    e0[b] = r[0];
+                    deg[b] = r[1];
+                    // a heavy vertex is cut into chunks of cv incidences
+                    const HeavySplit hs = heavy_split(r[1], weighted_chunk(r[1], r[3], a.chunk));
+                    cv[b] = hs.len;
+                    hv[b] = hs.count;
+                    light = hs.count ? 0u : light_weight(r[1], r[3]);
+                }
+                // light vertices form segments of consecutive queue entries
+                const uint32_t lscan = wave_incl_scan(light);
+                const uint32_t seg = segment_of(lscan, light, a.seg);
+                const uint32_t prev_seg = __shfl_up(seg, 1, kWave);
+                const bool in = head + b * kWave + lane < size;
+                firsts[b] = __ballot(in && (lane == 0 || seg != prev_seg));
+                hscan[b] = wave_incl_scan(hv[b]);
+                need += (uint32_t)__popcll(firsts[b]) + wave_bcast(hscan[b], kWave - 1);
+            }
+            uint32_t entries = min(batches * kWave, size - head);
+            if (need > kItemCap) {
+                if (batches > 1u) {   // too many heavy chunks at once: plan one batch ...
+                    most = 1u;
+                    continue;
+                }
+                // ... or one vertex
+                entries = 1u;
+                if (lane > 0) hv[0] = 0u;
+                firsts[0] = 1ull;
+                hscan[0] = wave_incl_scan(hv[0]);
+                need = 1u + wave_bcast(hscan[0], kWave - 1);
+            }
+            if (need == 0u) {
+                head += entries;
                 continue;
-            }
-            if ((raw & kExpanded) == 0u) {
-                v = raw;
-                e0 = G.v_off[v];
-                deg = G.v_off[v + 1] - e0;
-                // a heavy vertex is cut into chunks of cv incidences
-                const HeavySplit hs = heavy_split(deg, a.chunk);
-                cv = hs.len;
-                hv = hs.count;
-                light = hv ? 0u : deg;
-            }
-            // light vertices form segments of consecutive queue entries
-            const uint32_t lscan = wave_incl_scan(light);
-            const uint32_t seg = segment_of(lscan, light, a.seg);
-            const uint32_t prev_seg = __shfl_up(seg, 1, kWave);
-            const bool first = lane < nb && (lane == 0 || seg != prev_seg);
-            uint64_t firsts = __ballot(first);
-            uint32_t nseg = (uint32_t)__popcll(firsts);
-            uint32_t hscan = wave_incl_scan(hv);
-            uint32_t need = nseg + wave_bcast(hscan, kWave - 1);
-            if (need > kItemCap) {   // too many heavy chunks at once: plan one vertex
-                nb = 1;
-                if (lane > 0) hv = 0;
-                firsts = 1ull;
-                nseg = 1;
-                hscan = wave_incl_scan(hv);
-                need = 1u + wave_bcast(hscan, kWave - 1);
             }
             unsigned long long base = 0;
             if (lane == 0) base = atomicAdd(&a.ctr[kItems + parity], (unsigned long long)need);
@@ -1443,28 +1469,36 @@ __global__ __launch_bounds__(kWG) void k_plan(const RRArgs *__restrict__ ap, uin
                 for (uint64_t x = base + lane; x < kItemCap; x += kWave) a.items[x].x = kSkipItem;
                 break;
             }
-            if (lane < nb && ((firsts >> lane) & 1ull)) {
-                // segment = this lane up to the next first lane (or nb)
-                const uint64_t above = lane + 1 < 64 ? (firsts >> (lane + 1)) << (lane + 1) : 0ull;
-                const uint32_t next = above ? (uint32_t)__ffsll((unsigned long long)above) - 1u : nb;
-                a.items[base + lane_rank(firsts)] = make_uint4(d, head + lane, min(next, nb) - lane, 0u);
-            }
-            // heavy chunks, spread over the wave (a hub has hundreds)
-            const uint32_t H = wave_bcast(hscan, kWave - 1);
-            for (uint32_t q0 = 0; q0 < H; q0 += kWave) {
-                const uint32_t q = q0 + lane;
-                const uint32_t k = owner_of(hscan, min(q, H - 1u));
-                const uint32_t excl = (uint32_t)__shfl((int)(hscan - hv), (int)k, kWave);
-                const uint32_t vk = (uint32_t)__shfl((int)v, (int)k, kWave);
-                const uint32_t ek = (uint32_t)__shfl((int)e0, (int)k, kWave);
-                const uint32_t ck = (uint32_t)__shfl((int)cv, (int)k, kWave);
-                const uint32_t dk = (uint32_t)__shfl((int)deg, (int)k, kWave);
-                if (q < H) {
-                    const ChunkRange cr = chunk_range(ek, dk, ck, q - excl);
-                    a.items[base + nseg + q] = make_uint4(d | 0x80000000u, vk, cr.lo, cr.hi);
+#pragma unroll
+            for (uint32_t b = 0; b < kPlanBatches; ++b) {
+                if (firsts[b] == 0ull) continue;
+                const uint32_t at = head + b * kWave, nb = min((uint32_t)kWave, entries - b * kWave);
+                if ((firsts[b] >> lane) & 1ull) {
+                    // segment = this lane up to the next first lane (or nb)
+                    const uint64_t above = lane + 1 < 64 ? (firsts[b] >> (lane + 1)) << (lane + 1) : 0ull;
+                    const uint32_t next = above ? (uint32_t)__ffsll((unsigned long long)above) - 1u : nb;
+                    a.items[base + lane_rank(firsts[b])] = make_uint4(d, at + lane, min(next, nb) - lane, 0u);
                 }
+                base += (uint64_t)__popcll(firsts[b]);
+                // heavy chunks, spread over the wave (a hub has hundreds)
+                const uint32_t H = wave_bcast(hscan[b], kWave - 1);
+                for (uint32_t q0 = 0; q0 < H; q0 += kWave) {
+                    const uint32_t q = q0 + lane;
+                    const uint32_t k = owner_of(hscan[b], min(q, H - 1u));
+                    const uint32_t excl = (uint32_t)__shfl((int)(hscan[b] - hv[b]), (int)k, kWave);
+                    const uint32_t vk = (uint32_t)__shfl((int)v[b], (int)k, kWave);
+                    const uint32_t ek = (uint32_t)__shfl((int)e0[b], (int)k, kWave);
+                    const uint32_t ck = (uint32_t)__shfl((int)cv[b], (int)k, kWave);
+                    const uint32_t dk = (uint32_t)__shfl((int)deg[b], (int)k, kWave);
+                    if (q < H) {
+                        const ChunkRange cr = chunk_range(ek, dk, ck, q - excl);
+                        a.items[base + q] = make_uint4(d | 0x80000000u, vk, cr.lo, cr.hi);
+                    }
+                }
+                base += H;
             }
-            head += nb;
+            head += entries;
+            most = kPlanBatches;
         }
         if (lane == 0) a.def_head[d] = head;
         taken += head - head0;
@@ -1490,7 +1524,16 @@ __global__ __launch_bounds__(kWG) void k_expand(const RRArgs *__restrict__ ap, u
     const uint64_t gw = (uint64_t)blockIdx.x * kWavesPerWG + wv, groups = waves / W;
     const uint32_t w = (uint32_t)(gw & (W - 1));
     const uint32_t lane = lane_id();
-    for (uint64_t it = gw / W; it < nitems && gw < groups * W; it += groups) {
+    // Items of one set lie together, and waves that work on one set at a time
+    // queue up at its size counter (a million vertices, gap models: 20 ms a
+    // launch against 14): neighbouring waves take items far apart, by an odd
+    // multiplier near the golden ratio over the next power of two.
+    uint64_t span = 1;
+    while (span < nitems) span <<= 1;
+    const uint64_t mult = ((span * 0x9E37ull) >> 16) | 1ull;
+    for (uint64_t i0 = gw / W; i0 < span && gw < groups * W; i0 += groups) {
+        const uint64_t it = (i0 * mult) & (span - 1u);
+        if (it >= nitems) continue;
         const uint4 ld = a.items[it];
         const uint4 item = make_uint4(uni(ld.x), uni(ld.y), uni(ld.z), uni(ld.w));
         if (item.x == kSkipItem) continue;
@@ -1510,10 +1553,11 @@ __global__ __launch_bounds__(kWG) void k_expand(const RRArgs *__restrict__ ap, u
             const uint32_t raw = lane < item.z ? list[item.y + lane] : kExpanded;
             if ((raw & kExpanded) == 0u) {   // entries marked expanded are done
                 v = raw;
-                e0 = G.v_off[v];
-                deg = G.v_off[v + 1] - e0;
-                thr = G.thr[v];
-                if (heavy_split(deg, a.chunk).count) deg = 0;   // expanded by its heavy items
+                const Rec r = G.vrec[v];
+                e0 = r[0];
+                deg = r[1];
+                thr = r[2];
+                if (heavy_split(deg, weighted_chunk(deg, r[3], a.chunk)).count) deg = 0;   // expanded by its heavy items
             }
             if (w == 0) bytes_done += 20ull * (uint64_t)__popcll(__ballot((raw & kExpanded) == 0u));
             bytes_done += expand<false, false, kGaps>(G, L, S.j, S.pool, S.key, bm, prefilter, v, e0, deg, thr, app, px, w,
@@ -1521,7 +1565,8 @@ __global__ __launch_bounds__(kWG) void k_expand(const RRArgs *__restrict__ ap, u
         } else {
             // one heavy vertex: incidences [item.z, item.w) of vertex item.y
             bytes_done += expand<false, true, kGaps>(G, L, S.j, S.pool, S.key, bm, prefilter, item.y, item.z,
-                                                      item.w - item.z, uni(G.thr[item.y]), app, px, w, W);
+                                                      item.w - item.z, uni(G.vrec[item.y][2]), app, px, w,
+                                                      W);
         }
         // Continuation: when this wave appended at most 64 members, all light
         // and together under seg incidences, it expands them itself (up to
@@ -1532,16 +1577,20 @@ __global__ __launch_bounds__(kWG) void k_expand(const RRArgs *__restrict__ ap, u
             const uint32_t cn = app.count;
             if (cn == 0 || cn > kWave) break;
             wave_sync();
-            uint32_t v = 0, e0 = 0, deg = 0, pos = 0, thr = 0;
+            uint32_t v = 0, e0 = 0, deg = 0, pos = 0, thr = 0, weight = 0;
+            bool heavy_v = false;
             if (lane < cn) {
                 v = L.cont_u[lane];
                 pos = L.cont_pos[lane];
-                e0 = G.v_off[v];
-                deg = G.v_off[v + 1] - e0;
-                thr = G.thr[v];
+                const Rec r = G.vrec[v];
+                e0 = r[0];
+                deg = r[1];
+                thr = r[2];
+                weight = light_weight(r[1], r[3]);
+                heavy_v = deg > weighted_chunk(r[1], r[3], a.chunk);
             }
-            const uint32_t tot = wave_bcast(wave_incl_scan(deg), kWave - 1);
-            if (__ballot(lane < cn && deg > a.chunk) != 0 || tot > a.seg) break;   // left to k_plan
+            const uint64_t tot = wave_sum((uint64_t)weight);
+            if (__ballot(heavy_v) != 0 || tot > a.seg) break;   // left to k_plan
             wave_sync();
             if (lane < cn) list[pos] = v | kExpanded;
             app.count = 0;
@@ -1802,8 +1851,9 @@ __global__ __launch_bounds__(kWG) void k_ms_plan(MsArgs m) {
         if (lane < nb) {
             v = m.cur_v[f];
             sets = (uint32_t)__popcll(m.cur_m[f]);
-            e0 = G.v_off[v];
-            deg = G.v_off[v + 1] - e0;
+            const Rec r = G.vrec[v];
+            e0 = r[0];
+            deg = r[1];
             // work grows with incidences times sets: heavy entries are cut
             // into chunks of about `chunk` (incidence, set) pairs
             const HeavySplit hs = ms_heavy_split(deg, sets, m.chunk);
@@ -1956,17 +2006,17 @@ __device__ __forceinline__ void ms_pair(const MsArgs &m, MsLds &L, uint32_t &nli
 // mean), every lane walks its own quad's sets in registers; otherwise the
 // pairs are spread over the wave through LDS.
 __device__ __forceinline__ void ms_expand(const MsArgs &m, const GraphView &G, MsLds &L, uint32_t &nlive, uint32_t b,
-                                          uint32_t v, unsigned long long mask, uint32_t e0, uint32_t d, uint64_t &px) {
+                                          uint32_t v, unsigned long long mask, uint32_t e0, uint32_t d, uint32_t thr,
+                                          uint64_t &px) {
     const uint32_t lane = lane_id();
     const uint32_t dscan = wave_incl_scan(d);
     const uint32_t D = uni(wave_bcast(dscan, kWave - 1));
-    const uint32_t th = d ? G.thr[v] : 0u;
     wave_sync();
     L.fr_scan[lane] = dscan;
     L.fr_v[lane] = v;
     L.fr_e0[lane] = e0;
     L.fr_b[lane] = b;
-    L.fr_thr[lane] = th;
+    L.fr_thr[lane] = thr;
     L.fr_m[lane] = mask;
     wave_sync();
     for (uint32_t base = 0; base < D; base += kWave) {
@@ -1977,10 +2027,10 @@ __device__ __forceinline__ void ms_expand(const MsArgs &m, const GraphView &G, M
             fk = search64(L.fr_scan, g);
             const uint32_t start = fk ? L.fr_scan[fk - 1] : 0u;
             const uint32_t e = L.fr_e0[fk] + (g - start);
-            he = G.v_he[e];
-            const unsigned long long bs = G.v_hbs[e];
-            hb = (uint32_t)bs;
-            hs = (uint32_t)(bs >> 32);
+            const Rec ir = G.irec[e];
+            he = ir[0];
+            hb = ir[1];
+            hs = ir[2];
             nq = L.fr_thr[fk] ? (hs + 3u) >> 2 : 0u;   // threshold 0: no channel into the vertex is live
         }
         const uint32_t qscan = wave_incl_scan(nq);
@@ -2105,27 +2155,30 @@ __global__ __launch_bounds__(kWG) void k_ms_expand(MsArgs m) {
         if (item.x == kSkipItem) continue;
         if ((item.x >> 31) == 0u) {
             // light segment: entries [item.x, item.x + item.y)
-            uint32_t b = 0, v = 0, e0 = 0, d = 0;
+            uint32_t b = 0, v = 0, e0 = 0, d = 0, thr = 0;
             unsigned long long mask = 0;
             if (lane < item.y) {
                 const uint32_t f = item.x + lane;
                 b = m.cur_b[f];
                 v = m.cur_v[f];
                 mask = m.cur_m[f];
-                e0 = G.v_off[v];
-                d = G.v_off[v + 1] - e0;
+                const Rec r = G.vrec[v];
+                e0 = r[0];
+                d = r[1];
+                thr = r[2];
                 if (ms_heavy_split(d, (uint32_t)__popcll(mask), m.chunk).count) d = 0;   // expanded by its heavy items
             }
-            ms_expand(m, G, L, nlive, b, v, mask, e0, d, px);
+            ms_expand(m, G, L, nlive, b, v, mask, e0, d, thr, px);
         } else {
             // one heavy vertex: incidences [item.y, item.z) of entry item.x
             const uint32_t f = item.x & 0x7FFFFFFFu;
             const uint32_t b = uni(m.cur_b[f]), v = uni(m.cur_v[f]);
             const unsigned long long mask = uni64(m.cur_m[f]);
+            const uint32_t thr = uni(G.vrec[v][2]);
             // the chunk's incidences go to lanes in runs of up to 64 entries
             for (uint32_t e = item.y; e < item.z; e += kWave) {
                 const uint32_t mine = e + lane < item.z ? 1u : 0u;
-                ms_expand(m, G, L, nlive, b, v, mask, e + lane, mine, px);
+                ms_expand(m, G, L, nlive, b, v, mask, e + lane, mine, thr, px);
             }
         }
     }
@@ -2307,13 +2360,10 @@ __global__ __launch_bounds__(kWG) void k_weight_sum(const uint32_t *__restrict__
 // The descriptor of one graph in a launch group.
 GraphDesc graph_desc(hyperim_graph g) {
     GraphDesc d{};   // fields of other models stay null
-    d.he_off = g->he_off.as<uint32_t>();
     d.he_mem = g->he_mem.as<uint32_t>();
-    d.v_off = g->v_off.as<uint32_t>();
-    d.v_he = g->v_he.as<uint32_t>();
-    d.thr = g->thr.as<uint32_t>();
+    d.vrec = g->vrec.as<uint4>();
+    d.irec = g->irec.as<uint4>();
     d.P = g->P.as<uint32_t>();
-    d.v_hbs = g->v_hbs.as<unsigned long long>();
     d.n = g->n;
     d.bm_words = (uint32_t)(((uint64_t)g->n + 31u) / 32u);
     if (g->lt()) d.chan = g->chan.as<unsigned long long>();

@@ -59,23 +59,23 @@ struct PrepInfo {
 };
 
 // Incidence spans of one wave, flattened: body(u) for every member of the
-// incidences [e0, e1) of v_hbs (at most 64), v itself left out; `u` is valid
+// incidences [e0, e1) of irec (at most 64), v itself left out; `u` is valid
 // where the lane has one (else kNoKey), and every lane calls body together.
 struct SpanLds {
     uint32_t scan[kWave], hb[kWave];
 };
 template <class Body>
-__device__ __forceinline__ void wave_members(SpanLds &L, const uint2 *__restrict__ v_hbs,
+__device__ __forceinline__ void wave_members(SpanLds &L, const uint4 *__restrict__ irec,
                                              const uint32_t *__restrict__ he_mem, uint64_t e0, uint64_t e1, uint32_t v,
                                              Body &&body) {
     const uint32_t lane = lane_id();
-    uint2 bs = make_uint2(0u, 0u);
-    if (e0 + lane < e1) bs = v_hbs[e0 + lane];
-    const uint32_t incl = wave_incl_scan(bs.y);
+    uint4 rec = make_uint4(0u, 0u, 0u, 0u);
+    if (e0 + lane < e1) rec = irec[e0 + lane];
+    const uint32_t incl = wave_incl_scan(rec.z);
     const uint32_t total = wave_bcast(incl, kWave - 1);
     wave_sync();
     L.scan[lane] = incl;
-    L.hb[lane] = bs.x;
+    L.hb[lane] = rec.y;
     wave_sync();
     for (uint32_t b = 0; b < total; b += kWave) {
         const uint32_t q = b + lane;
@@ -161,7 +161,7 @@ __global__ __launch_bounds__(kBlock) void k_classify(uint32_t n, uint32_t dense,
 // another.
 __global__ __launch_bounds__(kBlock) void k_layers_reg(uint32_t n, const unsigned long long *__restrict__ c,
                                                         const uint32_t *__restrict__ v_off,
-                                                        const uint2 *__restrict__ v_hbs,
+                                                        const uint4 *__restrict__ irec,
                                                         const uint32_t *__restrict__ he_mem, uint32_t *__restrict__ deg,
                                                         uint32_t *__restrict__ l, uint32_t *__restrict__ top) {
     __shared__ SpanLds spans[kWavesPerBlock];
@@ -182,7 +182,7 @@ __global__ __launch_bounds__(kBlock) void k_layers_reg(uint32_t n, const unsigne
         const uint32_t v = (uint32_t)v0 + (uint32_t)k, e0 = wave_bcast(off0, k), e1 = wave_bcast(off1, k);
         uint32_t count = 0;   // occurrences found (wave-uniform)
         for (uint64_t e = e0; e < e1; e += kWave)
-            wave_members(spans[wv], v_hbs, he_mem, e, min(e + kWave, (uint64_t)e1), v, [&](uint32_t u) {
+            wave_members(spans[wv], irec, he_mem, e, min(e + kWave, (uint64_t)e1), v, [&](uint32_t u) {
                 const uint64_t has = __ballot(u != kNoKey);
                 const uint32_t at = count + lane_rank(has);
                 if (u != kNoKey && at < kWave) occ[at] = u;
@@ -222,7 +222,7 @@ __global__ __launch_bounds__(kBlock) void k_layers_reg(uint32_t n, const unsigne
 __global__ __launch_bounds__(kBlock) void k_layers_wave(const PrepInfo *__restrict__ info,
                                                          const uint32_t *__restrict__ list,
                                                          const uint32_t *__restrict__ v_off,
-                                                         const uint2 *__restrict__ v_hbs,
+                                                         const uint4 *__restrict__ irec,
                                                          const uint32_t *__restrict__ he_mem,
                                                          uint32_t *__restrict__ deg, uint32_t *__restrict__ l,
                                                          uint32_t *__restrict__ top) {
@@ -243,7 +243,7 @@ __global__ __launch_bounds__(kBlock) void k_layers_wave(const PrepInfo *__restri
         bits[lane] = 0u;
         wave_sync();
         for (uint64_t e = e0; e < e1; e += kWave)
-            wave_members(spans[wv], v_hbs, he_mem, e, min(e + kWave, (uint64_t)e1), v, [&](uint32_t u) {
+            wave_members(spans[wv], irec, he_mem, e, min(e + kWave, (uint64_t)e1), v, [&](uint32_t u) {
                 if (u != kNoKey) (void)lds_count<kSlots>(key, cnt, u);   // at most kSlots / 2 keys
             });
         wave_sync();
@@ -279,7 +279,7 @@ __global__ __launch_bounds__(kThreads) void k_layers_block(const uint32_t *__res
                                                             const uint32_t *__restrict__ list, uint32_t n,
                                                             const unsigned long long *__restrict__ c,
                                                             const uint32_t *__restrict__ v_off,
-                                                            const uint2 *__restrict__ v_hbs,
+                                                            const uint4 *__restrict__ irec,
                                                             const uint32_t *__restrict__ he_mem,
                                                             uint32_t *__restrict__ deg, uint32_t *__restrict__ l,
                                                             uint32_t *__restrict__ top, uint32_t *__restrict__ hubs,
@@ -308,7 +308,7 @@ __global__ __launch_bounds__(kThreads) void k_layers_block(const uint32_t *__res
             }
             __syncthreads();
             for (uint64_t e = (uint64_t)e0 + (uint64_t)wv * step; e < e1; e += (uint64_t)kWaves * step)
-                wave_members(spans[wv], v_hbs, he_mem, e, min(e + step, (uint64_t)e1), v, [&](uint32_t u) {
+                wave_members(spans[wv], irec, he_mem, e, min(e + step, (uint64_t)e1), v, [&](uint32_t u) {
                     if (u != kNoKey && (passes == 1u || __umulhi(mix32(u ^ 0x9E3779B9u), passes) == p) &&
                         !lds_count<kSlots>(key, cnt, u))
                         full = 1u;
@@ -404,7 +404,7 @@ __global__ __launch_bounds__(kBlock) void k_hub_chunks(const uint32_t *__restric
 __global__ __launch_bounds__(kBlock) void k_hub_count(const uint32_t *__restrict__ hubs, uint32_t count,
                                                        const unsigned long long *__restrict__ chunk_off,
                                                        const uint32_t *__restrict__ v_off,
-                                                       const uint2 *__restrict__ v_hbs,
+                                                       const uint4 *__restrict__ irec,
                                                        const uint32_t *__restrict__ he_mem, uint64_t n,
                                                        uint32_t *__restrict__ rows) {
     __shared__ SpanLds spans[kWavesPerBlock];
@@ -427,7 +427,7 @@ __global__ __launch_bounds__(kBlock) void k_hub_count(const uint32_t *__restrict
         const uint64_t b0 = v_off[v] + (ch - chunk_off[lo]) * kHubChunk;
         const uint64_t b1 = min(b0 + kHubChunk, e_end);
         for (uint64_t e = b0 + (uint64_t)wv * kWave; e < b1; e += kBlock)
-            wave_members(spans[wv], v_hbs, he_mem, e, min(e + kWave, b1), v, [&](uint32_t u) {
+            wave_members(spans[wv], irec, he_mem, e, min(e + kWave, b1), v, [&](uint32_t u) {
                 if (u == kNoKey) return;
                 const uint32_t sl = tab.slot(u);
                 if (sl != kTableEmpty) atomicAdd(&tcnt[sl], 1u);
@@ -640,7 +640,7 @@ int stratify_device(hyperim_graph g, PrepWorkspace &w, hipStream_t s) {
     uint32_t *lists = w.lists.as<uint32_t>();   // one list of n per class: wave, two workgroup sizes, hubs
     uint32_t *hubs = lists + 3 * (size_t)n;
     const uint32_t *v_off = g->v_off.as<uint32_t>(), *he_mem = g->he_mem.as<uint32_t>();
-    const uint2 *v_hbs = g->v_hbs.as<uint2>();
+    const uint4 *irec = g->irec.as<uint4>();
     const unsigned long long *cc = g->c.as<unsigned long long>();
     uint32_t *deg = g->deg.as<uint32_t>(), *ll = g->l.as<uint32_t>(), *top = g->top.as<uint32_t>();
     const uint32_t tiles = (uint32_t)std::max<uint64_t>(div_up(n, kBlock), 1);
@@ -653,16 +653,16 @@ int stratify_device(hyperim_graph g, PrepWorkspace &w, hipStream_t s) {
     hipLaunchKernelGGL(k_classify, dim3((uint32_t)div_up(n, kBlock * kClassPer)), dim3(kBlock), 0, s, n, dense, cc,
                        v_off, lists, di);
     hipLaunchKernelGGL((k_layers_block<1024, kBlockTable, kDensePairs>), dim3(std::min<uint32_t>(tiles, 512)), dim3(1024), 0,
-                       s, &di->n_big, lists + 2 * (size_t)n, n, cc, v_off, v_hbs, he_mem, deg, ll, top, hubs, di);
+                       s, &di->n_big, lists + 2 * (size_t)n, n, cc, v_off, irec, he_mem, deg, ll, top, hubs, di);
     hipLaunchKernelGGL((k_layers_block<kBlock, 4096, kBlockPairs>), dim3(std::min<uint32_t>(tiles, 4096)), dim3(kBlock),
-                       0, s, &di->n_block, lists + (size_t)n, n, cc, v_off, v_hbs, he_mem, deg, ll, top, hubs, di);
+                       0, s, &di->n_block, lists + (size_t)n, n, cc, v_off, irec, he_mem, deg, ll, top, hubs, di);
     hipLaunchKernelGGL(k_layers_wave, dim3(std::min<uint32_t>(tiles, 2048)), dim3(kBlock), 0, s, di, lists, v_off,
-                       v_hbs, he_mem, deg, ll, top);
+                       irec, he_mem, deg, ll, top);
     HIM_HIP(hipGetLastError());
     // the class counts, before the registers' class runs: the wait is short
     HIM_HIP(hipMemcpyAsync(&hi, di, sizeof(PrepInfo), hipMemcpyDeviceToHost, s));
     hipLaunchKernelGGL(k_layers_reg, dim3(std::max<uint32_t>((uint32_t)div_up(n, kBlock), 1)), dim3(kBlock), 0, s, n,
-                       cc, v_off, v_hbs, he_mem, deg, ll, top);
+                       cc, v_off, irec, he_mem, deg, ll, top);
     HIM_HIP(hipStreamSynchronize(s));
     if (hi.n_hub) {
         const uint32_t words = hi.dmax / 32u + 1u, row_tiles = (uint32_t)div_up(n, kHubScan);
@@ -679,7 +679,7 @@ int stratify_device(hyperim_graph g, PrepWorkspace &w, hipStream_t s) {
             hipLaunchKernelGGL(k_hub_chunks, dim3(1), dim3(kBlock), 0, s, hubs + h0, cnt, v_off,
                                w.pc.as<unsigned long long>());
             hipLaunchKernelGGL(k_hub_count, dim3(2048), dim3(kBlock), 0, s, hubs + h0, cnt,
-                               w.pc.as<unsigned long long>(), v_off, v_hbs, he_mem, (uint64_t)n, w.k1.as<uint32_t>());
+                               w.pc.as<unsigned long long>(), v_off, irec, he_mem, (uint64_t)n, w.k1.as<uint32_t>());
             hipLaunchKernelGGL(k_hub_scan, dim3(cnt * row_tiles), dim3(kBlock), 0, s, n, row_tiles,
                                w.k1.as<uint32_t>(), words, w.k2.as<uint32_t>(), w.vals.as<uint32_t>());
             hipLaunchKernelGGL(k_hub_final, dim3(cnt), dim3(kBlock), 0, s, hubs + h0, row_tiles,

@@ -20,10 +20,10 @@ def hy():
     return hy
 
 
-def _graph(n, seed):
-    """Two hyperedges per vertex of 2 to 90 members and a few hubs."""
+def _graph(n, seed, largest=90):
+    """Two hyperedges per vertex of 2 to `largest` members and a few hubs."""
     rng = np.random.Generator(np.random.PCG64(seed))
-    sizes = np.minimum(2 + (rng.pareto(1.2, size=2 * n)).astype(np.int64), min(90, n))
+    sizes = np.minimum(2 + (rng.pareto(1.2, size=2 * n)).astype(np.int64), min(largest, n))
     edges = [rng.choice(n, size=int(s), replace=False).tolist() for s in sizes]
     for h in range(3):
         for e in rng.choice(len(edges), size=n // 3, replace=False):
@@ -72,3 +72,20 @@ def test_small_and_larger_graphs_share_a_workspace(hy):
         pool = hy.Pool(g)
         hy.generate_rr(g, 5, 1, 0, 0, 300, pool)
         _check(hy, g, o, [(0, pool)], 300)
+
+
+@pytest.mark.parametrize("chunk,seg", [(16, 16), (256, 512)])
+def test_long_hyperedges_weigh_by_their_members(hy, chunk, seg):
+    """Vertices in few, long hyperedges: items are cut by member positions."""
+    print(f"[gpu] defer: long hyperedges chunk={chunk}", flush=True)
+    hg = _graph(2500, 9, largest=2000)
+    extra = [list(range(0, 2500, 2)), list(range(1, 2400)), list(range(5, 2500, 3))]
+    hg = hypergen.from_lists(hg.n, [hg.he_mem[a:b].tolist() for a, b in zip(hg.he_off[:-1], hg.he_off[1:])] + extra)
+    for model, p in ((0, 0.002), (1, 0.0)):
+        g, o = hy.build_graph(hg.n, hg.he_off, hg.he_mem, model, p), oracle.Graph(hg, model, p)
+        g.stratify()
+        o.stratify()
+        g.set_tuning(heavy=4, budget=500, chunk=chunk, seg=seg)
+        pool = hy.Pool(g)
+        hy.generate_rr(g, 5, 1, 0, 0, 200, pool)
+        _check(hy, g, o, [(0, pool)], 200)
