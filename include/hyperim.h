@@ -458,10 +458,11 @@ int hyperim_workspace_release(void);
  *   blocks_b:      grid-wide expansion workgroups per compute unit (6; 0 =
  *                  the occupancy limit);
  *   ms_filter:     bundled mode reads the members' seen masks before drawing
- *                  coins only for frontier entries that carry at least this
- *                  many sets (1 = always; 65 = never: every set of an entry
- *                  draws its coins and the level's advance drops members a
- *                  set already holds);
+ *                  coins only for light frontier entries (segments) that carry
+ *                  at least this many sets (1 = always; 65 = never: every set
+ *                  of an entry draws its coins, as for heavy entries, and
+ *                  members a set already holds are dropped when their live
+ *                  channels are marked);
  *   ms_min:        graphs whose RR sets hold at least this many members on
  *                  average (learned from earlier launches) grow their sets
  *                  in bundles of 64, bit-parallel over the sets: each vertex

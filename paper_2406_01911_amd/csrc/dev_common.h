@@ -30,22 +30,31 @@ __host__ __device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32
 // the key.  VALU-bound: 20 v_mad_u64_u32 and 20 three-input xors per block
 // with the key schedule in scalar registers, 845 Gblocks/s on MI355X at full
 // occupancy (two-input xors: 40 of them, 661-695 Gblocks/s).
-__host__ __device__ __forceinline__ uint4 philox4x32_10(uint4 ctr, uint2 key) {
+constexpr uint32_t kPhiloxM0 = 0xD2511F53u, kPhiloxM1 = 0xCD9E8D57u;   // multipliers of words 0 and 2
+constexpr uint32_t kPhiloxW0 = 0x9E3779B9u, kPhiloxW1 = 0xBB67AE85u;   // key increments
+
+// Rounds kFirst .. 9 on the state before round kFirst; key: that of round 0.
+template <int kFirst>
+__host__ __device__ __forceinline__ uint4 philox_rounds(uint4 ctr, uint2 key) {
+    key.x += (uint32_t)kFirst * kPhiloxW0;
+    key.y += (uint32_t)kFirst * kPhiloxW1;
 #pragma unroll
-    for (int round = 0; round < 10; ++round) {
-        const uint64_t m0 = (uint64_t)0xD2511F53u * (uint64_t)ctr.x;
-        const uint64_t m2 = (uint64_t)0xCD9E8D57u * (uint64_t)ctr.z;
+    for (int round = kFirst; round < 10; ++round) {
+        const uint64_t m0 = (uint64_t)kPhiloxM0 * (uint64_t)ctr.x;
+        const uint64_t m2 = (uint64_t)kPhiloxM1 * (uint64_t)ctr.z;
         uint4 next;
         next.x = xor3((uint32_t)(m2 >> 32), ctr.y, key.x);
         next.y = (uint32_t)m2;
         next.z = xor3((uint32_t)(m0 >> 32), ctr.w, key.y);
         next.w = (uint32_t)m0;
         ctr = next;
-        key.x += 0x9E3779B9u;
-        key.y += 0xBB67AE85u;
+        key.x += kPhiloxW0;
+        key.y += kPhiloxW1;
     }
     return ctr;
 }
+
+__host__ __device__ __forceinline__ uint4 philox4x32_10(uint4 ctr, uint2 key) { return philox_rounds<0>(ctr, key); }
 
 // Counter of the four coins of channels (he, u -> v) in RR set j whose
 // source positions pos in he satisfy pos >> 2 == quad.  Word (pos & 3) of the

@@ -415,7 +415,8 @@ __device__ __forceinline__ void flush_live(uint32_t *bm, WaveLds &L, uint32_t &n
 
 // Test the channels (he, u -> ve) at member positions [p0, p0 + cm) of one
 // hyperedge (cm <= kRun, p0 a multiple of 4) in this lane: the coins are the
-// words of the Philox blocks of quads p0/4, p0/4 + 1, ...  Newly reached
+// words of the Philox block of quad p0/4.  The coins come first, the members
+// are read where one is live (with the prefilter, before the coins).  Newly reached
 // members go to `app`: at once when the visited bitmap is in LDS, else
 // through the wave's buffer of live channels (L.live, nlive entries), marked
 // in batches.  Every lane of the wave must call it (inactive lanes with
@@ -425,58 +426,50 @@ __device__ __forceinline__ void test_run(const GraphView &G, uint64_t j, uint32_
                                          bool prefilter, bool active, uint32_t he, uint32_t hb, uint32_t p0,
                                          uint32_t cm, uint32_t ve, uint32_t the, App &app, uint64_t &px,
                                          Lds &L, uint32_t &nlive) {
+    static_assert(kRun == 4, "one Philox block and one member load per run");
     uint32_t u[8];
 #pragma unroll
     for (uint32_t t = 0; t < 8; ++t) u[t] = ve;
-    if (active) {
-        static_assert(kRun == 4, "one load per run");
-        const Quad m = load_quad(G.he_mem + (hb + p0));
-#pragma unroll
-        for (uint32_t t = 0; t < kRun; ++t) u[t] = t < cm ? m[t] : ve;
-    }
-    uint32_t seen[kRun];
-#pragma unroll
-    for (uint32_t t = 0; t < kRun; ++t) seen[t] = 0u;
+    uint32_t cand = active ? (1u << cm) - 1u : 0u;   // positions whose coins count
     if (prefilter) {
+        if (active) {
+            const Quad m = load_quad(G.he_mem + (hb + p0));
+#pragma unroll
+            for (uint32_t t = 0; t < kRun; ++t) u[t] = t < cm ? m[t] : ve;
+        }
         // all mark words in flight together (u[t] is always a vertex id)
+        uint32_t seen[kRun];
 #pragma unroll
         for (uint32_t t = 0; t < kRun; ++t) seen[t] = bm_load<kLds>(bm, u[t] >> 5);
+#pragma unroll
+        for (uint32_t t = 0; t < kRun; ++t)
+            if (u[t] == ve || (seen[t] & (1u << (u[t] & 31)))) cand &= ~(1u << t);
     }
-    bool cand[kRun];
-    bool need[kQ];
-#pragma unroll
-    for (uint32_t q = 0; q < kQ; ++q) need[q] = false;
-#pragma unroll
-    for (uint32_t t = 0; t < kRun; ++t) {
-        cand[t] = u[t] != ve && !(seen[t] & (1u << (u[t] & 31)));
-        need[t / 4] |= cand[t];
+    if (__ballot(cand != 0u) == 0) return;
+    uint4 c = make_uint4(0u, 0u, 0u, 0u);
+    if (cand) {
+        c = philox4x32_10(coin_counter(j, he, ve, pool, p0 >> 2), key);
+        ++px;
     }
-    bool any = false;
+    const uint32_t w[kRun] = {c.x, c.y, c.z, c.w};
+    uint32_t lv = 0;
 #pragma unroll
-    for (uint32_t q = 0; q < kQ; ++q) any |= need[q];
-    if (__ballot(any) == 0) return;
-    uint32_t w[kRun];
+    for (uint32_t t = 0; t < kRun; ++t) lv |= ((cand >> t) & 1u) && channel_live(w[t], the) ? 1u << t : 0u;
+    // with small probabilities most runs have no live channel at all, and
+    // their members are never read
+    if (__ballot(lv != 0u) == 0) return;
+    if (!prefilter && lv) {
+        const Quad m = load_quad(G.he_mem + (hb + p0));
 #pragma unroll
-    for (uint32_t q = 0; q < kQ; ++q) {
-        uint4 c = make_uint4(0u, 0u, 0u, 0u);
-        if (__ballot(need[q]) != 0 && need[q]) {
-            c = philox4x32_10(coin_counter(j, he, ve, pool, (p0 >> 2) + q), key);
-            ++px;
+        for (uint32_t t = 0; t < kRun; ++t) {
+            if (!((lv >> t) & 1u)) continue;
+            u[t] = m[t];
+            if (u[t] == ve) lv &= ~(1u << t);   // the target itself is no channel
         }
-        w[4 * q] = c.x;
-        w[4 * q + 1] = c.y;
-        w[4 * q + 2] = c.z;
-        w[4 * q + 3] = c.w;
     }
     bool live[kRun];
-    bool any_live = false;
 #pragma unroll
-    for (uint32_t t = 0; t < kRun; ++t) {
-        live[t] = cand[t] && channel_live(w[t], the);
-        any_live |= live[t];
-    }
-    // with small probabilities most runs have no live channel at all
-    if (__ballot(any_live) == 0) return;
+    for (uint32_t t = 0; t < kRun; ++t) live[t] = ((lv >> t) & 1u) != 0u;
     if constexpr (kLds) {
         uint32_t fresh = 0;
 #pragma unroll
@@ -1720,35 +1713,26 @@ struct MsArgs {
     uint32_t nvb;                       // vertex blocks per bundle
 };
 
-constexpr uint32_t kMsLiveCap = 512;   // live channels a wave holds before marking them
+constexpr uint32_t kMsLiveCap = 256;   // live channels a wave holds before marking them
+constexpr uint32_t kMsPend = 128;      // pairs with a live coin a wave holds before looking closer
 
 struct MsLds {
-    // level 2: frontier entries of the wave
-    uint32_t fr_scan[kWave], fr_v[kWave], fr_e0[kWave], fr_b[kWave], fr_thr[kWave];
+    // level 2: frontier entries of the wave: vertex, first incidence -
+    // incidences before, threshold, bundle; and their set masks
+    uint4 fr[kWave];
     unsigned long long fr_m[kWave];
-    // level 3: one incidence per lane (in_k: its frontier entry's lane)
-    uint32_t in_scan[kWave], in_he[kWave], in_hb[kWave], in_hs[kWave], in_k[kWave];
+    // level 3: one incidence per lane: hyperedge, first position, size, quads
+    // before; and its frontier entry's lane
+    uint4 in[kWave];
+    uint32_t in_k[kWave];
+    uint32_t mark[kWave];                // owners of a window of slots (window_owner)
+    // pairs with a coin below the threshold: (bundle << 8 | positions - 1 << 6 |
+    // set, vertex, first member's place, largest live coin), (hyperedge, quad)
+    uint4 pend[kMsPend];
+    uint2 pend_q[kMsPend];
     // live channels waiting to be marked: (member, bundle << 6 | set)
     uint2 live[kMsLiveCap];
 };
-
-// Position of the r-th set bit (r < popcount(m)) of m.
-__device__ __forceinline__ uint32_t nth_bit(unsigned long long m, uint32_t r) {
-    uint32_t pos = 0;
-#pragma unroll
-    for (uint32_t w = 32; w > 0; w >>= 1) {
-        const unsigned long long low = m & ((1ull << w) - 1ull);
-        const uint32_t c = (uint32_t)__popcll(low);
-        if (r >= c) {
-            r -= c;
-            m >>= w;
-            pos += w;
-        } else {
-            m = low;
-        }
-    }
-    return pos;
-}
 
 __device__ __forceinline__ void ms_append_next(const MsArgs &m, uint32_t b, uint32_t u) {
     const unsigned long long pos = atomicAdd(&m.ctr[kMsNext], 1ull);
@@ -1906,228 +1890,277 @@ __global__ __launch_bounds__(kWG) void k_ms_plan(MsArgs m) {
     if (lane_id() == 0 && bytes) atomicAdd(m.bytes, bytes);
 }
 
-// Appends (bundle, vertex) pairs that just got their first bit in nxt to the
-// next-level list: one counter reservation per wavefront.  Every lane of the
-// wave calls it; lanes with `fresh` set contribute (b, u).
-__device__ __forceinline__ void ms_append_wave(const MsArgs &m, bool fresh, uint32_t b, uint32_t u) {
-    const uint64_t who = __ballot(fresh);
-    if (who == 0) return;
-    unsigned long long base = 0;
-    if (lane_id() == (uint32_t)__ffsll((unsigned long long)who) - 1u)
-        base = atomicAdd(&m.ctr[kMsNext], (unsigned long long)__popcll(who));
-    base = wave_bcast64(base, (int)__ffsll((unsigned long long)who) - 1);
-    if (fresh) {
-        const unsigned long long pos = base + lane_rank(who);
-        if (pos < m.list_cap) {
-            m.nx_b[pos] = b;
-            m.nx_v[pos] = u;
-        } else {
-            atomicOr(&m.ctr[kMsOverflow], 1ull);
-        }
-    }
-}
-
-// Marks the wave's buffered live channels in nxt and appends the (bundle,
-// member) pairs that got their first bit to the next-level list.  A marking
-// needs the old mask back, so each lane first issues up to four atomics and
-// only then waits: one memory round trip per 256 channels instead of one per
-// coin batch.  Every lane of the wave calls it.
+// Marks the wave's buffered live channels in nxt, those that lead to a member
+// the set does not hold yet, and appends the (bundle, member) pairs that got
+// their first bit to the next-level list.  A marking needs the old mask back,
+// so each lane first issues up to four reads of seen, then up to four atomics,
+// and only then waits: two memory round trips per 256 channels.  One
+// reservation of places for all of them.  Every lane of the wave calls it.
 __device__ __forceinline__ void ms_flush(const MsArgs &m, MsLds &L, uint32_t &nlive) {
     wave_sync();
     const uint32_t lane = lane_id();
-    for (uint32_t i0 = 0; i0 < nlive; i0 += 4 * kWave) {
-        unsigned long long old[4];
-        uint32_t bb[4], uu[4];
-        bool act[4];
+    static_assert(kMsLiveCap == 4 * kWave, "four channels per lane");
+    unsigned long long old[4], held[4];
+    uint32_t bb[4], uu[4], ss[4];
+#pragma unroll
+    for (uint32_t r = 0; r < 4; ++r) {
+        const uint32_t i = r * kWave + lane;
+        bb[r] = uu[r] = ss[r] = 0;
+        held[r] = ~0ull;
+        if (i < nlive) {
+            const uint2 e = L.live[i];
+            uu[r] = e.x;
+            bb[r] = e.y >> 6;
+            ss[r] = e.y & 63u;
+            held[r] = m.seen[(uint64_t)bb[r] * m.stride + uu[r]];
+        }
+    }
+#pragma unroll
+    for (uint32_t r = 0; r < 4; ++r) {
+        old[r] = ~0ull;
+        if (((held[r] >> ss[r]) & 1ull) == 0ull)
+            old[r] = atomicOr(&m.nxt[(uint64_t)bb[r] * m.stride + uu[r]], 1ull << ss[r]);
+    }
+    uint64_t who[4];
+    uint32_t total = 0;
+#pragma unroll
+    for (uint32_t r = 0; r < 4; ++r) {
+        who[r] = __ballot(old[r] == 0ull);
+        total += (uint32_t)__popcll(who[r]);
+    }
+    if (total) {
+        unsigned long long base = 0;
+        if (lane == 0) base = atomicAdd(&m.ctr[kMsNext], (unsigned long long)total);
+        base = wave_bcast64(base, 0);
 #pragma unroll
         for (uint32_t r = 0; r < 4; ++r) {
-            const uint32_t i = i0 + r * kWave + lane;
-            act[r] = i < nlive;
-            bb[r] = uu[r] = 0;
-            old[r] = ~0ull;
-            if (act[r]) {
-                const uint2 e = L.live[i];
-                uu[r] = e.x;
-                bb[r] = e.y >> 6;
-                old[r] = atomicOr(&m.nxt[(uint64_t)bb[r] * m.stride + uu[r]], 1ull << (e.y & 63u));
+            if (old[r] == 0ull) {
+                const unsigned long long pos = base + lane_rank(who[r]);
+                if (pos < m.list_cap) {
+                    m.nx_b[pos] = bb[r];
+                    m.nx_v[pos] = uu[r];
+                } else {
+                    atomicOr(&m.ctr[kMsOverflow], 1ull);
+                }
             }
+            base += (uint64_t)__popcll(who[r]);
         }
-#pragma unroll
-        for (uint32_t r = 0; r < 4; ++r) ms_append_wave(m, act[r] && old[r] == 0ull, bb[r], uu[r]);
     }
     nlive = 0;
     wave_sync();
 }
 
-// Coins of one (quad, set) pair: channels (he, u[t] -> v) for the candidate
-// positions t of set s; live ones wait in the wave's buffer to be marked in
-// nxt (sets already holding u are removed when the level advances).  Lanes
-// with act = false only join the wave-wide steps.
-__device__ __forceinline__ void ms_pair(const MsArgs &m, MsLds &L, uint32_t &nlive, bool act, uint32_t bnd,
-                                        uint32_t s, uint32_t he, uint32_t q, uint32_t v, uint32_t thr,
-                                        uint32_t cand4, const uint32_t (&u)[4], uint64_t &px) {
-    uint4 c = make_uint4(0u, 0u, 0u, 0u);
-    if (act) {
-        c = philox4x32_10(coin_counter(m.first_id + (uint64_t)bnd * kMsSets + s, he, v, m.pool, q),
-                          make_uint2(m.key0, m.key1));
-        ++px;
-    }
-    const uint32_t w[4] = {c.x, c.y, c.z, c.w};
-    uint32_t lv = 0;
+// The held pairs' live channels go to the buffer: their block is drawn again
+// (64 pairs to a wave here, two or three of its lanes where they were found)
+// and their members are read for the first time; the vertex itself is left out.
+// Every lane of the wave calls it.
+__device__ __forceinline__ void ms_resolve(const MsArgs &m, const GraphView &G, MsLds &L, uint32_t &npend,
+                                           uint32_t &nlive) {
+    wave_sync();
+    const uint32_t lane = lane_id();
+    const uint64_t below = (1ull << lane) - 1ull;
+    for (uint32_t i0 = 0; i0 < npend; i0 += kWave) {
+        uint32_t lv = 0, tag = 0;
+        Quad u = {0u, 0u, 0u, 0u};
+        if (i0 + lane < npend) {
+            const uint4 e = L.pend[i0 + lane];
+            const uint2 q = L.pend_q[i0 + lane];
+            u = load_quad(G.he_mem + e.z);
+            const uint32_t bnd = e.x >> 8, s = e.x & 63u, cnt = ((e.x >> 6) & 3u) + 1u;
+            const uint4 w = philox4x32_10(
+                coin_counter(m.first_id + (uint64_t)bnd * kMsSets + s, q.x, e.y, m.pool, q.y),
+                make_uint2(m.key0, m.key1));
+            const uint32_t c[4] = {w.x, w.y, w.z, w.w};
 #pragma unroll
-    for (uint32_t t = 0; t < 4; ++t)
-        lv |= (act && ((cand4 >> t) & 1u) && channel_live(w[t], thr)) ? 1u << t : 0u;
-    // placement from one ballot per position: the live channels of position
-    // t follow those of positions < t, in lane order
-    const uint64_t b0 = __ballot(lv & 1u), b1 = __ballot(lv & 2u), b2 = __ballot(lv & 4u), b3 = __ballot(lv & 8u);
-    if ((b0 | b1 | b2 | b3) == 0ull) return;   // with small probabilities most pairs have no live channel
-    const uint32_t c0 = (uint32_t)__popcll(b0), c1 = (uint32_t)__popcll(b1), c2 = (uint32_t)__popcll(b2);
-    const uint32_t tot = c0 + c1 + c2 + (uint32_t)__popcll(b3);
-    if (nlive + tot > kMsLiveCap) ms_flush(m, L, nlive);
-    const uint64_t below = (1ull << lane_id()) - 1ull;
-    const uint32_t tag = (bnd << 6) | s;
-    if (lv & 1u) L.live[nlive + (uint32_t)__popcll(b0 & below)] = make_uint2(u[0], tag);
-    if (lv & 2u) L.live[nlive + c0 + (uint32_t)__popcll(b1 & below)] = make_uint2(u[1], tag);
-    if (lv & 4u) L.live[nlive + c0 + c1 + (uint32_t)__popcll(b2 & below)] = make_uint2(u[2], tag);
-    if (lv & 8u) L.live[nlive + c0 + c1 + c2 + (uint32_t)__popcll(b3 & below)] = make_uint2(u[3], tag);
-    nlive += tot;
+            for (uint32_t t = 0; t < 4; ++t) lv |= t < cnt && u[t] != e.y && c[t] <= e.w ? 1u << t : 0u;
+            tag = (bnd << 6) | s;
+        }
+        // placement from one ballot per position: the live channels of
+        // position t follow those of positions < t, in lane order
+        uint64_t b[4];
+        uint32_t tot = 0;
+#pragma unroll
+        for (uint32_t t = 0; t < 4; ++t) {
+            b[t] = __ballot((lv >> t) & 1u);
+            tot += (uint32_t)__popcll(b[t]);
+        }
+        if (nlive + tot > kMsLiveCap) ms_flush(m, L, nlive);
+#pragma unroll
+        for (uint32_t t = 0; t < 4; ++t) {
+            if ((lv >> t) & 1u) L.live[nlive + (uint32_t)__popcll(b[t] & below)] = make_uint2(u[t], tag);
+            nlive += (uint32_t)__popcll(b[t]);
+        }
+    }
+    npend = 0;
+    wave_sync();
 }
 
-// Levels 2-4 of a bundled expansion.  Each lane brings a frontier entry
-// (bundle b, vertex v, set mask) and the incidence range [e0, e0 + d) of v to
-// expand (d = 0 for none).  Level 2 spreads the incidences over the wave,
-// level 3 the quads of member positions of those hyperedges, level 4 the
-// (quad, set) pairs whose coins are drawn.  A quad whose entry carries at
-// least m.filter sets first reads its members' seen masks and keeps
-// only the sets that do not hold them; for smaller masks those scattered
-// loads cost more than the coins they would save, so every set of the mask
-// draws its coins and the level's advance drops what a set already holds.
-// When the wave's pair counts are even (no lane has more than twice the
-// mean), every lane walks its own quad's sets in registers; otherwise the
-// pairs are spread over the wave through LDS.
-__device__ __forceinline__ void ms_expand(const MsArgs &m, const GraphView &G, MsLds &L, uint32_t &nlive, uint32_t b,
-                                          uint32_t v, unsigned long long mask, uint32_t e0, uint32_t d, uint32_t thr,
-                                          uint64_t &px) {
+// A quad of member positions on its way through the sets of an entry: what of
+// its Philox blocks does not depend on the set.  Of the counter's words only
+// the set's id j does, so the first round's product of v and one of the second
+// round's are the quad's (37 of a block's 40 instructions are left), and M0 j
+// is M0 times the bundle's first id plus M0 s.
+struct MsQuad {
+    uint32_t e, f, cw, mx;           // words of rounds 1 and 2 without the set's part
+    uint32_t tag, v, at, most, he, q;
+};
+__device__ __forceinline__ MsQuad ms_quad(const MsArgs &m, uint32_t bnd, uint32_t v, uint32_t thr, uint32_t he,
+                                          uint32_t q, uint32_t cnt, uint32_t at) {
+    const uint64_t mv = (uint64_t)kPhiloxM1 * v;
+    const uint64_t mx = (uint64_t)kPhiloxM0 * xor3((uint32_t)(mv >> 32), he, m.key0);
+    MsQuad o;
+    o.e = (uint32_t)mv ^ (m.key0 + kPhiloxW0);
+    o.f = (uint32_t)(mx >> 32) ^ (m.key1 + kPhiloxW1);
+    o.cw = coin_counter(m.first_id + (uint64_t)bnd * kMsSets, he, v, m.pool, q).w ^ m.key1;
+    o.mx = (uint32_t)mx;
+    o.tag = (bnd << 8) | (((cnt - 1u) & 3u) << 6);
+    o.v = v;
+    o.at = at;
+    o.most = thr == kAlways ? kAlways : thr - 1u;
+    o.he = he;
+    o.q = q;
+    return o;
+}
+
+// One (quad, set) pair per lane: its block, and the pair is held when a coin is
+// low enough.  m0 = M0 j; lanes with act = false only join the wave-wide steps.
+__device__ __forceinline__ void ms_pair(const MsArgs &m, const GraphView &G, MsLds &L, uint32_t &npend,
+                                        uint32_t &nlive, const MsQuad &Q, bool act, uint32_t s, uint64_t m0) {
+    const uint64_t m2 = (uint64_t)kPhiloxM1 * ((uint32_t)(m0 >> 32) ^ Q.cw);
+    const uint4 w = philox_rounds<2>(make_uint4((uint32_t)(m2 >> 32) ^ Q.e, (uint32_t)m2, (uint32_t)m0 ^ Q.f, Q.mx),
+                                     make_uint2(m.key0, m.key1));
+    const bool hit = act && min(min(w.x, w.y), min(w.z, w.w)) <= Q.most;
+    const uint64_t b = __ballot(hit);
+    if (b == 0ull) return;
+    const uint32_t tot = (uint32_t)__popcll(b);
+    if (npend + tot > kMsPend) ms_resolve(m, G, L, npend, nlive);
+    if (hit) {
+        const uint32_t i = npend + lane_rank(b);
+        L.pend[i] = make_uint4(Q.tag | s, Q.v, Q.at, Q.most);
+        L.pend_q[i] = make_uint2(Q.he, Q.q);
+    }
+    npend += tot;
+}
+
+// M0 j of set s of a bundle whose first id is j0, j taken modulo 2^32 as the
+// counter does (no bundle passes a multiple of 2^32, where the counter's last
+// word would change too: launch groups end there).
+__device__ __forceinline__ uint64_t ms_m0(uint64_t j0, uint32_t s) {
+    return (uint64_t)kPhiloxM0 * (uint32_t)(j0 + s);
+}
+
+// Levels 2-4 for light entries.  Each lane brings a frontier entry (bundle b,
+// vertex v, set mask) and the incidence range [e0, e0 + d) of v to expand
+// (d = 0 for none).  Level 2 spreads the incidences over the wave, level 3 the
+// quads of member positions of those hyperedges, and at level 4 every lane
+// walks the sets of its quad.  A quad whose entry carries at least m.filter
+// sets first reads its members and their seen masks and keeps only the sets
+// that miss one of them; otherwise every set of the mask draws its coins.
+__device__ __forceinline__ void ms_expand(const MsArgs &m, const GraphView &G, MsLds &L, uint32_t &npend,
+                                          uint32_t &nlive, uint32_t b, uint32_t v, unsigned long long mask,
+                                          uint32_t e0, uint32_t d, uint32_t thr, uint64_t &px) {
     const uint32_t lane = lane_id();
     const uint32_t dscan = wave_incl_scan(d);
-    const uint32_t D = uni(wave_bcast(dscan, kWave - 1));
+    const uint32_t D = wave_bcast(dscan, kWave - 1);
     wave_sync();
-    L.fr_scan[lane] = dscan;
-    L.fr_v[lane] = v;
-    L.fr_e0[lane] = e0;
-    L.fr_b[lane] = b;
-    L.fr_thr[lane] = thr;
+    L.fr[lane] = make_uint4(v, e0 - (dscan - d), thr, b);
     L.fr_m[lane] = mask;
     wave_sync();
     for (uint32_t base = 0; base < D; base += kWave) {
         // level 2: one incidence (v, he) per lane
         const uint32_t g = base + lane;
-        uint32_t he = 0, hb = 0, hs = 0, nq = 0, fk = 0;
+        uint32_t he = 0, hb = 0, hs = 0, nq = 0;
+        const uint32_t fk = window_owner(L.mark, dscan - d, d, base);
         if (g < D) {
-            fk = search64(L.fr_scan, g);
-            const uint32_t start = fk ? L.fr_scan[fk - 1] : 0u;
-            const uint32_t e = L.fr_e0[fk] + (g - start);
-            const Rec ir = G.irec[e];
+            const uint4 f = L.fr[fk];
+            const Rec ir = G.irec[f.y + g];
             he = ir[0];
             hb = ir[1];
             hs = ir[2];
-            nq = L.fr_thr[fk] ? (hs + 3u) >> 2 : 0u;   // threshold 0: no channel into the vertex is live
+            nq = f.z && hs > 1u ? (hs + 3u) >> 2 : 0u;   // threshold 0: no channel into the vertex is live
         }
         const uint32_t qscan = wave_incl_scan(nq);
-        const uint32_t Q = uni(wave_bcast(qscan, kWave - 1));
+        const uint32_t Q = wave_bcast(qscan, kWave - 1);
         if (Q == 0) continue;
         wave_sync();
-        L.in_scan[lane] = qscan;
-        L.in_he[lane] = he;
-        L.in_hb[lane] = hb;
-        L.in_hs[lane] = hs;
+        L.in[lane] = make_uint4(he, hb, hs, qscan - nq);
         L.in_k[lane] = fk;
         wave_sync();
         for (uint32_t qb = 0; qb < Q; qb += kWave) {
             // level 3: one quad of member positions per lane
             const uint32_t qg = qb + lane;
-            uint32_t pc = 0;
-            uint32_t u[4] = {0u, 0u, 0u, 0u};
-            unsigned long long cand[4] = {0ull, 0ull, 0ull, 0ull}, un = 0ull;
-            uint32_t qhe = 0, qq = 0, qv = 0, qth = 0, qbnd = 0;
+            const uint32_t k = window_owner(L.mark, qscan - nq, nq, qb);
+            const uint4 in = L.in[k];
+            const uint32_t fl = L.in_k[k];
+            const uint4 f = L.fr[fl];   // vertex, -, threshold, bundle
+            const uint32_t qq = qg - in.w, p0 = 4u * qq, at = in.y + p0, cnt = min(4u, in.z - p0);
+            unsigned long long un = 0ull;
             if (qg < Q) {
-                const uint32_t k = search64(L.in_scan, qg);
-                const uint32_t start = k ? L.in_scan[k - 1] : 0u;
-                const uint32_t f = L.in_k[k];
-                qq = qg - start;
-                qhe = L.in_he[k];
-                qv = L.fr_v[f];
-                qth = L.fr_thr[f];
-                qbnd = L.fr_b[f];
-                const unsigned long long qm = L.fr_m[f];
-                const uint32_t p0 = 4u * qq, cnt = min(4u, L.in_hs[k] - p0);
-                const uint32_t hbk = L.in_hb[k];
-#pragma unroll
-                for (uint32_t t = 0; t < 4; ++t) u[t] = t < cnt ? G.he_mem[hbk + p0 + t] : qv;
-                uint32_t valid = 0;
-#pragma unroll
-                for (uint32_t t = 0; t < 4; ++t) valid |= (t < cnt && u[t] != qv) ? 1u << t : 0u;
-                if ((uint32_t)__popcll(qm) >= m.filter) {
-                    const uint64_t row = (uint64_t)qbnd * m.stride;
+                un = L.fr_m[fl];
+                if ((uint32_t)__popcll(un) >= m.filter) {
+                    const Quad u = load_quad(G.he_mem + at);
+                    const uint64_t row = (uint64_t)f.w * m.stride;
                     unsigned long long sm[4];
 #pragma unroll
-                    for (uint32_t t = 0; t < 4; ++t) sm[t] = ((valid >> t) & 1u) ? m.seen[row + u[t]] : ~0ull;
-#pragma unroll
-                    for (uint32_t t = 0; t < 4; ++t) cand[t] = qm & ~sm[t];
-                } else {
-#pragma unroll
-                    for (uint32_t t = 0; t < 4; ++t) cand[t] = ((valid >> t) & 1u) ? qm : 0ull;
+                    for (uint32_t t = 0; t < 4; ++t) sm[t] = t < cnt && u[t] != f.x ? m.seen[row + u[t]] : ~0ull;
+                    un &= ~(sm[0] & sm[1] & sm[2] & sm[3]);
                 }
-#pragma unroll
-                for (uint32_t t = 0; t < 4; ++t) un |= cand[t];
-                pc = (uint32_t)__popcll(un);
             }
-            const uint32_t pscan = wave_incl_scan(pc);
-            const uint32_t PT = uni(wave_bcast(pscan, kWave - 1));
-            if (PT == 0) continue;
-            const uint32_t pmax = uni(wave_max(pc));
-            if ((uint64_t)pmax * kWave <= 2ull * PT) {
-                // level 4 in registers: lane walks the sets of its own quad
-                unsigned long long rem = un;
-                for (uint32_t r = 0; r < pmax; ++r) {
-                    const bool act = rem != 0ull;
-                    uint32_t s = 0, c4 = 0;
-                    if (act) {
-                        s = (uint32_t)__ffsll(rem) - 1u;
-                        rem &= rem - 1ull;
-#pragma unroll
-                        for (uint32_t t = 0; t < 4; ++t) c4 |= (uint32_t)((cand[t] >> s) & 1ull) << t;
-                    }
-                    ms_pair(m, L, nlive, act, qbnd, s, qhe, qq, qv, qth, c4, u, px);
-                }
-                continue;
+            const uint32_t pc = (uint32_t)__popcll(un), pmax = wave_max(pc);
+            if (pmax == 0u) continue;
+            px += pc;
+            const uint64_t j0 = m.first_id + (uint64_t)f.w * kMsSets;
+            const MsQuad mq = ms_quad(m, f.w, f.x, f.z, in.x, qq, cnt, at);
+            const uint64_t base0 = ms_m0(j0, 0u);
+            unsigned long long rem = un;
+            for (uint32_t r = 0; r < pmax; ++r) {
+                const bool act = rem != 0ull;
+                const uint32_t s = (uint32_t)__ffsll(rem) - 1u;
+                rem &= rem - 1ull;
+                ms_pair(m, G, L, npend, nlive, mq, act, s & 63u, base0 + (uint64_t)kPhiloxM0 * (s & 63u));
             }
-            // level 4 over the wave: one (quad, set) pair per lane, the
-            // quad's data read from its lane by shuffles
-            for (uint32_t pb = 0; pb < PT; pb += kWave) {
-                const uint32_t pg = pb + lane;
-                const bool act = pg < PT;
-                const uint32_t k = owner_of(pscan, act ? pg : PT - 1u);
-                const uint32_t before = (uint32_t)__shfl((int)(pscan - pc), (int)k, kWave);
-                const unsigned long long unk =
-                    ((unsigned long long)(uint32_t)__shfl((int)(uint32_t)(un >> 32), (int)k, kWave) << 32) |
-                    (uint32_t)__shfl((int)(uint32_t)un, (int)k, kWave);
-                const uint32_t s = nth_bit(unk, act ? pg - before : 0u);
-                const uint32_t bk = (uint32_t)__shfl((int)qbnd, (int)k, kWave);
-                const uint32_t vk = (uint32_t)__shfl((int)qv, (int)k, kWave);
-                const uint32_t thk = (uint32_t)__shfl((int)qth, (int)k, kWave);
-                const uint32_t hek = (uint32_t)__shfl((int)qhe, (int)k, kWave);
-                const uint32_t qk = (uint32_t)__shfl((int)qq, (int)k, kWave);
-                uint32_t uk[4], c4 = 0;
-#pragma unroll
-                for (uint32_t t = 0; t < 4; ++t) {
-                    uk[t] = (uint32_t)__shfl((int)u[t], (int)k, kWave);
-                    // the set's bit of cand[t]: from the half that holds bit s
-                    const uint32_t lo = (uint32_t)__shfl((int)(uint32_t)cand[t], (int)k, kWave);
-                    const uint32_t hi = (uint32_t)__shfl((int)(uint32_t)(cand[t] >> 32), (int)k, kWave);
-                    c4 |= (((s < 32 ? lo >> s : hi >> (s - 32)) & 1u)) << t;
-                }
-                ms_pair(m, L, nlive, act, bk, s, hek, qk, vk, thk, c4, uk, px);
+        }
+    }
+    wave_sync();
+}
+
+// Levels 2-4 for a chunk [e0, e1) of a heavy entry's incidences: bundle, vertex
+// and sets are the wave's, so every lane draws for the same set at a time, the
+// set's part of the block is scalar work, and no lane waits for another.  The
+// members' seen masks are not read before the coins: that spares a third of the
+// blocks and costs more than those (with them 522 ms of expansion for a
+// million vertices at theta = 4096, this form 400).
+__device__ __forceinline__ void ms_expand_heavy(const MsArgs &m, const GraphView &G, MsLds &L, uint32_t &npend,
+                                                uint32_t &nlive, uint32_t b, uint32_t v, unsigned long long mask,
+                                                uint32_t e0, uint32_t e1, uint32_t thr, uint64_t &px) {
+    if (thr == 0u) return;   // no channel into the vertex is live
+    const uint32_t lane = lane_id(), sets = (uint32_t)__popcll(mask);
+    const uint64_t j0 = m.first_id + (uint64_t)b * kMsSets;
+    for (uint32_t base = e0; base < e1; base += kWave) {
+        uint32_t he = 0, hb = 0, hs = 0, nq = 0;
+        if (e1 - base > lane) {
+            const Rec ir = G.irec[base + lane];
+            he = ir[0];
+            hb = ir[1];
+            hs = ir[2];
+            nq = hs > 1u ? (hs + 3u) >> 2 : 0u;
+        }
+        const uint32_t qscan = wave_incl_scan(nq);
+        const uint32_t Q = wave_bcast(qscan, kWave - 1);
+        if (Q == 0) continue;
+        wave_sync();
+        L.in[lane] = make_uint4(he, hb, hs, qscan - nq);
+        wave_sync();
+        for (uint32_t qb = 0; qb < Q; qb += kWave) {
+            const uint32_t qg = qb + lane;
+            const uint4 in = L.in[window_owner(L.mark, qscan - nq, nq, qb)];
+            const uint32_t qq = qg - in.w, p0 = 4u * qq;
+            const bool act = qg < Q;
+            if (act) px += sets;
+            const MsQuad mq = ms_quad(m, b, v, thr, in.x, qq, min(4u, in.z - p0), in.y + p0);
+            for (unsigned long long rem = mask; rem; rem &= rem - 1ull) {
+                const uint32_t s = (uint32_t)__ffsll(rem) - 1u;
+                ms_pair(m, G, L, npend, nlive, mq, act, s, ms_m0(j0, s));
             }
         }
     }
@@ -2142,13 +2175,19 @@ __global__ __launch_bounds__(kWG) void k_ms_expand(MsArgs m) {
     const uint64_t nitems = min(m.ctr[kMsItems], (unsigned long long)kItemCap);
     const uint32_t lane = lane_id();
     uint64_t px = 0;
-    uint32_t nlive = 0;   // live channels buffered in L.live (wave-uniform)
-    for (;;) {
-        // items cost up to a few times each other (hyperedge sizes vary
-        // inside a chunk), so waves take them one at a time
-        unsigned long long it = 0;
-        if (lane == 0) it = atomicAdd(&m.ctr[kMsFetch], 1ull);
-        it = uni64(wave_bcast64(it, 0));
+    uint32_t npend = 0, nlive = 0;   // blocks and live channels held in LDS (wave-uniform)
+    // items cost up to a few times each other (hyperedge sizes vary inside a
+    // chunk), so waves fetch them as they go, a share of 1/16 of a wave's even
+    // part at a time (all fetches meet at one counter, 7.5 ns each)
+    const uint64_t waves = (uint64_t)gridDim.x * kWavesPerWG;
+    const uint64_t share = max((uint64_t)1, min((uint64_t)64, nitems / (16u * waves)));
+    for (uint64_t it = 0, end = 0;; ++it) {
+        if (it == end) {
+            unsigned long long got = 0;
+            if (lane == 0) got = atomicAdd(&m.ctr[kMsFetch], (unsigned long long)share);
+            it = uni64(wave_bcast64(got, 0));
+            end = it + share;
+        }
         if (it >= nitems) break;
         const uint4 ld = m.items[it];
         const uint4 item = make_uint4(uni(ld.x), uni(ld.y), uni(ld.z), uni(ld.w));
@@ -2168,20 +2207,17 @@ __global__ __launch_bounds__(kWG) void k_ms_expand(MsArgs m) {
                 thr = r[2];
                 if (ms_heavy_split(d, (uint32_t)__popcll(mask), m.chunk).count) d = 0;   // expanded by its heavy items
             }
-            ms_expand(m, G, L, nlive, b, v, mask, e0, d, thr, px);
+            ms_expand(m, G, L, npend, nlive, b, v, mask, e0, d, thr, px);
         } else {
             // one heavy vertex: incidences [item.y, item.z) of entry item.x
             const uint32_t f = item.x & 0x7FFFFFFFu;
             const uint32_t b = uni(m.cur_b[f]), v = uni(m.cur_v[f]);
             const unsigned long long mask = uni64(m.cur_m[f]);
             const uint32_t thr = uni(G.vrec[v][2]);
-            // the chunk's incidences go to lanes in runs of up to 64 entries
-            for (uint32_t e = item.y; e < item.z; e += kWave) {
-                const uint32_t mine = e + lane < item.z ? 1u : 0u;
-                ms_expand(m, G, L, nlive, b, v, mask, e + lane, mine, thr, px);
-            }
+            ms_expand_heavy(m, G, L, npend, nlive, b, v, mask, item.y, item.z, thr, px);
         }
     }
+    ms_resolve(m, G, L, npend, nlive);
     ms_flush(m, L, nlive);
     px = wave_sum(px);
     if (lane == 0 && px) atomicAdd(m.philox, (unsigned long long)px);
@@ -3269,6 +3305,9 @@ int rr_generate_into(RRWorkspace &ws, RRStats &st, const std::vector<RRTask> &ta
             const double m = per_set(t.g);
             uint64_t take = std::min<uint64_t>(rest, max_sets);
             take = std::min<uint64_t>(take, std::max<uint64_t>(1, (uint64_t)(stage_words / m)));
+            // the ids of a group share their upper words (ms_m0)
+            const uint64_t id0 = t.id_begin + (pos - tstart[ti]);
+            take = std::min<uint64_t>(take, (1ull << 32) - (id0 & 0xFFFFFFFFull));
             acc = (double)take * m;
             pos += take;
         }

@@ -89,3 +89,25 @@ def test_long_hyperedges_weigh_by_their_members(hy, chunk, seg):
         pool = hy.Pool(g)
         hy.generate_rr(g, 5, 1, 0, 0, 200, pool)
         _check(hy, g, o, [(0, pool)], 200)
+
+
+@pytest.mark.parametrize("first", [(1 << 32) - 100, (1 << 33) - 64, (1 << 32) + 5])
+@pytest.mark.parametrize("chunk", [16, 4096])
+def test_bundles_at_multiples_of_2_32(hy, first, chunk):
+    """Bundled generation across a multiple of 2^32, where the ids' upper word
+    changes: every entry heavy (chunk 16) or light (4096)."""
+    print(f"[gpu] bundles at {first} chunk={chunk}", flush=True)
+    hg = _graph(600, 6)
+    for model, p in ((0, 0.05), (1, 0.0), (0, 1.0)):
+        g, o = hy.build_graph(hg.n, hg.he_off, hg.he_mem, model, p), oracle.Graph(hg, model, p)
+        g.stratify()
+        o.stratify()
+        for filt in (1, 65):
+            g.set_tuning(ms_min=1, chunk=chunk, seg=4096, ms_filter=filt)
+            pool = hy.Pool(g)
+            hy.generate_rr(g, 5, 1, 1, first, first + 300, pool)
+            off, mem, roots = pool.read()
+            roff, rmem, rroots = o.generate(5, 1, 1, first, first + 300)
+            assert np.array_equal(roots, rroots)
+            assert np.array_equal(off, roff)
+            assert np.array_equal(mem, rmem)
