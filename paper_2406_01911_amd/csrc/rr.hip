@@ -170,6 +170,7 @@ struct RRArgs {
 };
 
 constexpr uint32_t kLiveCap = 256;   // live channels a wave holds before marking them (global marks)
+constexpr uint32_t kRunCap = 128;    // runs with a live coin a wave holds before reading their members
 
 struct WaveLdsCore {
     uint32_t fr_scan[kWave];                   // gap models: inclusive scan of the frontier's incidence counts
@@ -177,6 +178,7 @@ struct WaveLdsCore {
     uint4 in[kWave];                           // incidence: hyperedge, first position, size, runs before
     uint2 in_vt[kWave];                        // ... its vertex and threshold
     uint32_t mark[kWave];                      // owners of a window of slots (window_owner)
+    uint4 runs[kRunCap];                       // held runs: first member's place, live positions, target
     uint32_t cont_u[kWave], cont_pos[kWave];   // phase B: members this wave appended, and where
 };
 // With visited bitmaps in global memory a wave also buffers live channels.
@@ -413,19 +415,71 @@ __device__ __forceinline__ void flush_live(uint32_t *bm, WaveLds &L, uint32_t &n
     wave_sync();
 }
 
+// Reads the members of the wave's held runs, 64 runs at a time, and hands the
+// live ones on: to `app` at once when the visited bitmap is in LDS, else to the
+// buffer of live channels, marked in batches.  Every lane of the wave calls it.
+template <bool kLds, class App, class Lds>
+__device__ __forceinline__ void read_runs(const GraphView &G, uint32_t *bm, Lds &L, uint32_t &nrun, uint32_t &nlive,
+                                          App &app) {
+    wave_sync();
+    const uint32_t lane = lane_id();
+    for (uint32_t i0 = 0; i0 < nrun; i0 += kWave) {
+        uint32_t u[8], lv = 0;
+#pragma unroll
+        for (uint32_t t = 0; t < 8; ++t) u[t] = 0u;
+        if (i0 + lane < nrun) {
+            const uint4 r = L.runs[i0 + lane];
+            const Quad m = load_quad(G.he_mem + r.x);
+            // the target itself is no channel
+#pragma unroll
+            for (uint32_t t = 0; t < kRun; ++t) {
+                u[t] = m[t];
+                lv |= ((r.y >> t) & 1u) && m[t] != r.z ? 1u << t : 0u;
+            }
+        }
+        if constexpr (kLds) {
+            uint32_t fresh = 0;
+#pragma unroll
+            for (uint32_t t = 0; t < kRun; ++t) {
+                if ((lv >> t) & 1u) {
+                    const uint32_t bit = 1u << (u[t] & 31);
+                    if ((atomicOr(&bm[u[t] >> 5], bit) & bit) == 0u) fresh |= 1u << t;
+                }
+            }
+            app.push8(fresh, u);
+        } else {
+            // placement from one ballot per position
+            static_assert(kRun == 4 && kLiveCap >= kRun * kWave, "64 runs fit the buffer");
+            uint64_t b[kRun];
+            uint32_t tot = 0;
+#pragma unroll
+            for (uint32_t t = 0; t < kRun; ++t) {
+                b[t] = __ballot((lv >> t) & 1u);
+                tot += (uint32_t)__popcll(b[t]);
+            }
+            if (nlive + tot > kLiveCap) flush_live(bm, L, nlive, app);
+#pragma unroll
+            for (uint32_t t = 0; t < kRun; ++t) {
+                if ((lv >> t) & 1u) L.live[nlive + lane_rank(b[t])] = u[t];
+                nlive += (uint32_t)__popcll(b[t]);
+            }
+        }
+    }
+    nrun = 0;
+    wave_sync();
+}
+
 // Test the channels (he, u -> ve) at member positions [p0, p0 + cm) of one
 // hyperedge (cm <= kRun, p0 a multiple of 4) in this lane: the coins are the
 // words of the Philox block of quad p0/4.  The coins come first, the members
-// are read where one is live (with the prefilter, before the coins).  Newly reached
-// members go to `app`: at once when the visited bitmap is in LDS, else
-// through the wave's buffer of live channels (L.live, nlive entries), marked
-// in batches.  Every lane of the wave must call it (inactive lanes with
-// active = false).
+// are read where one is live (with the prefilter, before the coins too): such runs
+// are held in L.runs (nrun entries) for read_runs.  Every lane of the wave must
+// call it (inactive lanes with active = false).
 template <bool kLds, class App, class Lds>
 __device__ __forceinline__ void test_run(const GraphView &G, uint64_t j, uint32_t pool, uint2 key, uint32_t *bm,
                                          bool prefilter, bool active, uint32_t he, uint32_t hb, uint32_t p0,
                                          uint32_t cm, uint32_t ve, uint32_t the, App &app, uint64_t &px,
-                                         Lds &L, uint32_t &nlive) {
+                                         Lds &L, uint32_t &nrun, uint32_t &nlive) {
     static_assert(kRun == 4, "one Philox block and one member load per run");
     uint32_t u[8];
 #pragma unroll
@@ -456,44 +510,14 @@ __device__ __forceinline__ void test_run(const GraphView &G, uint64_t j, uint32_
 #pragma unroll
     for (uint32_t t = 0; t < kRun; ++t) lv |= ((cand >> t) & 1u) && channel_live(w[t], the) ? 1u << t : 0u;
     // with small probabilities most runs have no live channel at all, and
-    // their members are never read
-    if (__ballot(lv != 0u) == 0) return;
-    if (!prefilter && lv) {
-        const Quad m = load_quad(G.he_mem + (hb + p0));
-#pragma unroll
-        for (uint32_t t = 0; t < kRun; ++t) {
-            if (!((lv >> t) & 1u)) continue;
-            u[t] = m[t];
-            if (u[t] == ve) lv &= ~(1u << t);   // the target itself is no channel
-        }
-    }
-    bool live[kRun];
-#pragma unroll
-    for (uint32_t t = 0; t < kRun; ++t) live[t] = ((lv >> t) & 1u) != 0u;
-    if constexpr (kLds) {
-        uint32_t fresh = 0;
-#pragma unroll
-        for (uint32_t t = 0; t < kRun; ++t) {
-            if (live[t]) {
-                const uint32_t bit = 1u << (u[t] & 31);
-                if ((atomicOr(&bm[u[t] >> 5], bit) & bit) == 0u) fresh |= 1u << t;
-            }
-        }
-        app.push8(fresh, u);
-    } else {
-        // placement from one ballot per position (as in ms_pair)
-        static_assert(kRun == 4, "one ballot per run position");
-        const uint64_t b0 = __ballot(live[0]), b1 = __ballot(live[1]), b2 = __ballot(live[2]), b3 = __ballot(live[3]);
-        const uint32_t c0 = (uint32_t)__popcll(b0), c1 = (uint32_t)__popcll(b1), c2 = (uint32_t)__popcll(b2);
-        const uint32_t tot = c0 + c1 + c2 + (uint32_t)__popcll(b3);
-        if (nlive + tot > kLiveCap) flush_live(bm, L, nlive, app);
-        const uint64_t below = (1ull << lane_id()) - 1ull;
-        if (live[0]) L.live[nlive + (uint32_t)__popcll(b0 & below)] = u[0];
-        if (live[1]) L.live[nlive + c0 + (uint32_t)__popcll(b1 & below)] = u[1];
-        if (live[2]) L.live[nlive + c0 + c1 + (uint32_t)__popcll(b2 & below)] = u[2];
-        if (live[3]) L.live[nlive + c0 + c1 + c2 + (uint32_t)__popcll(b3 & below)] = u[3];
-        nlive += tot;
-    }
+    // their members are never read; the others wait until there are 64 to read
+    // at once (a few lanes of a wave find one here)
+    const uint64_t hit = __ballot(lv != 0u);
+    if (hit == 0ull) return;
+    const uint32_t tot = (uint32_t)__popcll(hit);
+    if (nrun + tot > kRunCap) read_runs<kLds>(G, bm, L, nrun, nlive, app);
+    if (lv) L.runs[nrun + lane_rank(hit)] = make_uint4(hb + p0, lv, ve, 0u);
+    nrun += tot;
 }
 
 // Independent cascade drawn by geometric gaps (models HYPERIM_MODEL_GAPS_*;
@@ -671,7 +695,7 @@ __device__ __forceinline__ uint64_t expand(const GraphView &G, Lds &L, uint64_t 
                                            uint32_t *bm, bool prefilter, uint32_t v, uint32_t e0, uint32_t d,
                                            uint32_t thr, App &app, uint64_t &px, uint32_t w = 0, uint32_t W = 1) {
     const uint32_t lane = lane_id();
-    uint32_t nlive = 0;   // live channels buffered in L.live (wave-uniform)
+    uint32_t nrun = 0, nlive = 0;   // runs and live channels held in LDS (wave-uniform)
     uint32_t D = d, fstart = 0;
     if constexpr (!kUniform) {
         const uint32_t dscan = wave_incl_scan(d);
@@ -721,7 +745,7 @@ __device__ __forceinline__ uint64_t expand(const GraphView &G, Lds &L, uint64_t 
         // level 3, first pass: run 0 of the lane's own incidence
         if (sub_w == 0)
             test_run<kLds>(G, j, pool, key, bm, prefilter, no > 0, he, hb, 0u, min(kRun, hs), vv, th, app, px, L,
-                           nlive);
+                           nrun, nlive);
         // second pass: runs 1.. of the longer hyperedges, flattened over the wave
         const uint32_t rem = no > 1 ? no - 1u : 0u;
         if (__ballot(rem > 0) == 0) continue;
@@ -744,9 +768,10 @@ __device__ __forceinline__ uint64_t expand(const GraphView &G, Lds &L, uint64_t 
             }
             const uint32_t p0 = (qg - in.w + 1u) * kRun;
             test_run<kLds>(G, j, pool, key, bm, prefilter, active, in.x, in.y, p0, min(kRun, in.z - p0), ve, the, app,
-                           px, L, nlive);
+                           px, L, nrun, nlive);
         }
     }
+    read_runs<kLds>(G, bm, L, nrun, nlive, app);
     if constexpr (!kLds) flush_live(bm, L, nlive, app);
     wave_sync();
     return wave_sum(bytes);
@@ -787,12 +812,13 @@ template <bool kLdsBitmap, bool kGaps>
 __global__ __launch_bounds__(kWG) void k_rr_light(RRArgs a) {
     using Lds = typename std::conditional<kLdsBitmap, WaveLdsCore, WaveLds>::type;
     __shared__ Lds lds[kWavesPerWG];
-    __shared__ uint32_t sort_s[kWavesPerWG][kSortMax];
     __shared__ uint32_t lbm[kLdsBitmap ? kWavesPerWG : 1][kLdsBitmap ? kLdsBitmapWords : 1];
     const uint32_t lane = lane_id(), wv = uni(threadIdx.x / kWave);
     uint32_t slot = blockIdx.x * kWavesPerWG + wv;
     Lds &L = lds[wv];
-    uint32_t *sortb = sort_s[wv];
+    // a finished set is sorted where its expansions kept their state
+    static_assert(sizeof(Lds) >= sizeof(uint32_t) * kSortMax, "sort buffer");
+    uint32_t *sortb = reinterpret_cast<uint32_t *>(&L);
     uint32_t *list = a.lists + (uint64_t)slot * a.slot_n;
     uint32_t *bm;
     if constexpr (kLdsBitmap) {
@@ -1769,25 +1795,68 @@ __global__ __launch_bounds__(kWG) void k_ms_roots(MsArgs m, RRArgs a) {
 // hold them yet, become the frontier.  Runs only once the level's frontier
 // is fully planned and expanded.
 __global__ __launch_bounds__(kWG) void k_ms_advance(MsArgs m) {
+    constexpr uint32_t kPer = 4;   // entries per thread and turn: one reservation for all of the workgroup's
+    __shared__ uint32_t part[kWavesPerWG];
+    __shared__ unsigned long long base_s;
     if (m.ctr[kMsLevelDone] == 0ull) return;
     const uint64_t cnt = min(m.ctr[kMsNext], (unsigned long long)m.list_cap);
-    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < cnt; i += (uint64_t)gridDim.x * blockDim.x) {
-        const uint32_t b = m.nx_b[i], u = m.nx_v[i];
-        const uint64_t w = (uint64_t)b * m.stride + u;
-        const unsigned long long found = m.nxt[w];
-        m.nxt[w] = 0ull;
-        const unsigned long long fresh = found & ~m.seen[w];
-        if (fresh) {
-            m.seen[w] |= fresh;   // each (bundle, vertex) appears once in the list
-            const unsigned long long pos = atomicAdd(&m.ctr[kMsCur], 1ull);
-            if (pos < m.list_cap) {
-                m.cur_b[pos] = b;
-                m.cur_v[pos] = u;
-                m.cur_m[pos] = fresh;
-            } else {
-                atomicOr(&m.ctr[kMsOverflow], 1ull);
+    const uint32_t lane = lane_id(), wv = threadIdx.x / kWave;
+    for (uint64_t i0 = (uint64_t)blockIdx.x * kWG * kPer; i0 < cnt; i0 += (uint64_t)gridDim.x * kWG * kPer) {
+        uint32_t b[kPer], u[kPer];
+        unsigned long long found[kPer], fresh[kPer];
+#pragma unroll
+        for (uint32_t r = 0; r < kPer; ++r) {
+            const uint64_t i = i0 + r * kWG + threadIdx.x;
+            b[r] = u[r] = 0u;
+            if (i < cnt) {
+                b[r] = m.nx_b[i];
+                u[r] = m.nx_v[i];
             }
         }
+#pragma unroll
+        for (uint32_t r = 0; r < kPer; ++r) {
+            const uint64_t w = (uint64_t)b[r] * m.stride + u[r];
+            found[r] = fresh[r] = 0ull;
+            if (i0 + r * kWG + threadIdx.x < cnt) {
+                found[r] = m.nxt[w];
+                fresh[r] = found[r] & ~m.seen[w];
+            }
+        }
+        uint64_t who[kPer];
+        uint32_t mine = 0;
+#pragma unroll
+        for (uint32_t r = 0; r < kPer; ++r) {
+            const uint64_t w = (uint64_t)b[r] * m.stride + u[r];
+            if (found[r]) m.nxt[w] = 0ull;
+            if (fresh[r]) m.seen[w] |= fresh[r];   // each (bundle, vertex) appears once in the list
+            who[r] = __ballot(fresh[r] != 0ull);
+            mine += (uint32_t)__popcll(who[r]);
+        }
+        if (lane == 0) part[wv] = mine;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            uint32_t all = 0;
+            for (uint32_t q = 0; q < kWavesPerWG; ++q) all += part[q];
+            base_s = all ? atomicAdd(&m.ctr[kMsCur], (unsigned long long)all) : 0ull;
+        }
+        __syncthreads();
+        unsigned long long pos = base_s;
+        for (uint32_t q = 0; q < wv; ++q) pos += part[q];
+#pragma unroll
+        for (uint32_t r = 0; r < kPer; ++r) {
+            if (fresh[r]) {
+                const unsigned long long p = pos + lane_rank(who[r]);
+                if (p < m.list_cap) {
+                    m.cur_b[p] = b[r];
+                    m.cur_v[p] = u[r];
+                    m.cur_m[p] = fresh[r];
+                } else {
+                    atomicOr(&m.ctr[kMsOverflow], 1ull);
+                }
+            }
+            pos += (uint64_t)__popcll(who[r]);
+        }
+        __syncthreads();   // part and base_s are reused
     }
 }
 
@@ -1826,68 +1895,103 @@ __global__ __launch_bounds__(kWG) void k_ms_plan(MsArgs m) {
     const uint32_t epoch = (uint32_t)m.ctr[kMsEpoch] + 1u;   // never 0: fresh entries read 0
     const uint64_t nbatch = (ncur + kWave - 1) / kWave;
     const GraphView G = graph_view(m.graph);
-    unsigned long long bytes = 0;
-    for (uint64_t bt = (uint64_t)blockIdx.x * kWavesPerWG + wv; bt < nbatch; bt += (uint64_t)gridDim.x * kWavesPerWG) {
-        if (uni(m.batch_epoch[bt]) == epoch) continue;
-        const uint64_t f = bt * kWave + lane;
-        const uint32_t nb = (uint32_t)min((uint64_t)kWave, ncur - bt * kWave);
-        uint32_t v = 0, e0 = 0, deg = 0, hv = 0, light = 0, cv = m.chunk, sets = 0;
-        if (lane < nb) {
-            v = m.cur_v[f];
-            sets = (uint32_t)__popcll(m.cur_m[f]);
-            const Rec r = G.vrec[v];
-            e0 = r[0];
-            deg = r[1];
-            // work grows with incidences times sets: heavy entries are cut
-            // into chunks of about `chunk` (incidence, set) pairs
-            const HeavySplit hs = ms_heavy_split(deg, sets, m.chunk);
-            cv = hs.len;
-            hv = hs.count;
-            light = hv ? 0u : deg * sets;   // segment weight: (incidence, set) pairs
+    unsigned long long bytes = 0, planned = 0;
+    // kPlanBatches batches per reservation (as in k_plan; one at a time when
+    // their items might not fit an empty buffer)
+    for (uint64_t b0 = ((uint64_t)blockIdx.x * kWavesPerWG + wv) * kPlanBatches; b0 < nbatch;
+         b0 += (uint64_t)gridDim.x * kWavesPerWG * kPlanBatches) {
+        uint32_t e0[kPlanBatches], deg[kPlanBatches], cv[kPlanBatches], hv[kPlanBatches], hscan[kPlanBatches],
+            batch_need[kPlanBatches];
+        uint64_t firsts[kPlanBatches];
+        unsigned long long weight[kPlanBatches];   // algorithmic bytes of the lane's entry
+        uint32_t todo = 0;
+        uint64_t need = 0;
+#pragma unroll
+        for (uint32_t k = 0; k < kPlanBatches; ++k) {
+            e0[k] = deg[k] = hv[k] = hscan[k] = batch_need[k] = 0u;
+            cv[k] = m.chunk;
+            firsts[k] = weight[k] = 0ull;
+            const uint64_t bt = b0 + k;
+            if (bt >= nbatch || uni(m.batch_epoch[bt]) == epoch) continue;
+            todo |= 1u << k;
+            const uint64_t f = bt * kWave + lane;
+            const bool in = f < ncur;
+            uint32_t light = 0;
+            if (in) {
+                const uint32_t v = m.cur_v[f], sets = (uint32_t)__popcll(m.cur_m[f]);
+                const Rec r = G.vrec[v];
+                e0[k] = r[0];
+                deg[k] = r[1];
+                weight[k] = (unsigned long long)sets * m.bytesw[v];
+                // work grows with incidences times sets: heavy entries are cut
+                // into chunks of about `chunk` (incidence, set) pairs
+                const HeavySplit hs = ms_heavy_split(deg[k], sets, m.chunk);
+                cv[k] = hs.len;
+                hv[k] = hs.count;
+                light = hs.count ? 0u : deg[k] * sets;   // segment weight: (incidence, set) pairs
+            }
+            const uint32_t lscan = wave_incl_scan(light);
+            const uint32_t seg = segment_of(lscan, light, m.seg);
+            const uint32_t prev_seg = __shfl_up(seg, 1, kWave);
+            firsts[k] = __ballot(in && (lane == 0 || seg != prev_seg));
+            hscan[k] = wave_incl_scan(hv[k]);
+            batch_need[k] = (uint32_t)__popcll(firsts[k]) + wave_bcast(hscan[k], kWave - 1);
+            need += batch_need[k];
         }
-        const uint32_t lscan = wave_incl_scan(light);
-        const uint32_t seg = segment_of(lscan, light, m.seg);
-        const uint32_t prev_seg = __shfl_up(seg, 1, kWave);
-        const bool first = lane < nb && (lane == 0 || seg != prev_seg);
-        const uint64_t firsts = __ballot(first);
-        const uint32_t nseg = (uint32_t)__popcll(firsts);
-        const uint32_t hscan = wave_incl_scan(hv);
-        const uint32_t need = nseg + uni(wave_bcast(hscan, kWave - 1));
+        if (todo == 0u) continue;
+        const bool together = need <= kItemCap / 2u;
         unsigned long long base = 0;
-        if (lane == 0) base = atomicAdd(&m.ctr[kMsItems], (unsigned long long)need);
-        base = uni64(wave_bcast64(base, 0));
-        if (base + need > kItemCap) {
-            for (uint64_t x = base + lane; x < kItemCap; x += kWave) m.items[x].x = kSkipItem;
-            continue;
-        }
-        if (lane < nb && ((firsts >> lane) & 1ull)) {
-            const uint64_t above = lane + 1 < 64 ? (firsts >> (lane + 1)) << (lane + 1) : 0ull;
-            const uint32_t next = above ? (uint32_t)__ffsll((unsigned long long)above) - 1u : nb;
-            m.items[base + lane_rank(firsts)] = make_uint4((uint32_t)f, min(next, nb) - lane, 0u, 0u);
-        }
-        // heavy chunks, spread over the wave
-        const uint32_t H = uni(wave_bcast(hscan, kWave - 1));
-        for (uint32_t q0 = 0; q0 < H; q0 += kWave) {
-            const uint32_t q = q0 + lane;
-            const uint32_t k = owner_of(hscan, min(q, H - 1u));
-            const uint32_t excl = (uint32_t)__shfl((int)(hscan - hv), (int)k, kWave);
-            const uint32_t fk = (uint32_t)__shfl((int)(uint32_t)f, (int)k, kWave);
-            const uint32_t ek = (uint32_t)__shfl((int)e0, (int)k, kWave);
-            const uint32_t ck = (uint32_t)__shfl((int)cv, (int)k, kWave);
-            const uint32_t dk = (uint32_t)__shfl((int)deg, (int)k, kWave);
-            if (q < H) {
-                const ChunkRange cr = chunk_range(ek, dk, ck, q - excl);
-                m.items[base + nseg + q] = make_uint4(fk | 0x80000000u, cr.lo, cr.hi, 0u);
+        if (together) {
+            if (lane == 0) base = atomicAdd(&m.ctr[kMsItems], (unsigned long long)need);
+            base = uni64(wave_bcast64(base, 0));
+            if (base + need > kItemCap) {
+                for (uint64_t x = base + lane; x < kItemCap; x += kWave) m.items[x].x = kSkipItem;
+                continue;
             }
         }
-        if (lane < nb) bytes += (unsigned long long)sets * m.bytesw[v];
-        if (lane == 0) {
-            m.batch_epoch[bt] = epoch;
-            atomicSub(&m.ctr[kMsPending], 1ull);
+#pragma unroll
+        for (uint32_t k = 0; k < kPlanBatches; ++k) {
+            if (((todo >> k) & 1u) == 0u) continue;
+            if (!together) {
+                if (lane == 0) base = atomicAdd(&m.ctr[kMsItems], (unsigned long long)batch_need[k]);
+                base = uni64(wave_bcast64(base, 0));
+                if (base + batch_need[k] > kItemCap) {
+                    for (uint64_t x = base + lane; x < kItemCap; x += kWave) m.items[x].x = kSkipItem;
+                    continue;
+                }
+            }
+            const uint64_t f = (b0 + k) * kWave + lane;
+            const uint32_t nb = (uint32_t)min((uint64_t)kWave, ncur - (b0 + k) * kWave);
+            if ((firsts[k] >> lane) & 1ull) {
+                const uint64_t above = lane + 1 < 64 ? (firsts[k] >> (lane + 1)) << (lane + 1) : 0ull;
+                const uint32_t next = above ? (uint32_t)__ffsll((unsigned long long)above) - 1u : nb;
+                m.items[base + lane_rank(firsts[k])] = make_uint4((uint32_t)f, min(next, nb) - lane, 0u, 0u);
+            }
+            const uint32_t nseg = (uint32_t)__popcll(firsts[k]);
+            // heavy chunks, spread over the wave
+            const uint32_t H = wave_bcast(hscan[k], kWave - 1);
+            for (uint32_t q0 = 0; q0 < H; q0 += kWave) {
+                const uint32_t q = q0 + lane;
+                const uint32_t o = owner_of(hscan[k], min(q, H - 1u));
+                const uint32_t excl = (uint32_t)__shfl((int)(hscan[k] - hv[k]), (int)o, kWave);
+                const uint32_t fk = (uint32_t)__shfl((int)(uint32_t)f, (int)o, kWave);
+                const uint32_t ek = (uint32_t)__shfl((int)e0[k], (int)o, kWave);
+                const uint32_t ck = (uint32_t)__shfl((int)cv[k], (int)o, kWave);
+                const uint32_t dk = (uint32_t)__shfl((int)deg[k], (int)o, kWave);
+                if (q < H) {
+                    const ChunkRange cr = chunk_range(ek, dk, ck, q - excl);
+                    m.items[base + nseg + q] = make_uint4(fk | 0x80000000u, cr.lo, cr.hi, 0u);
+                }
+            }
+            base += batch_need[k];
+            bytes += weight[k];
+            if (lane == 0) m.batch_epoch[b0 + k] = epoch;
+            ++planned;
         }
     }
+    if (lane == 0 && planned) atomicSub(&m.ctr[kMsPending], planned);
     bytes = wave_sum(bytes);
-    if (lane_id() == 0 && bytes) atomicAdd(m.bytes, bytes);
+    if (lane == 0 && bytes) atomicAdd(m.bytes, bytes);
 }
 
 // Marks the wave's buffered live channels in nxt, those that lead to a member
