@@ -155,14 +155,14 @@ void RRWorkspace::release() {
 size_t PrepWorkspace::bytes() const {
     size_t b = 0;
     for (const DevBuf *x : {&k1, &vals, &k2, &info, &pc, &tmp, &counts, &base, &hist, &occ, &occ2, &sort_tmp,
-                            &run_start, &pair_val, &flag, &cnt, &off64, &lists, &bm})
+                            &run_start, &pair_val, &flag, &cnt, &off64, &lists, &bm, &hub_cnt, &hub_off})
         b += x->bytes;
     return b;
 }
 
 void PrepWorkspace::release() {
     for (DevBuf *x : {&k1, &vals, &k2, &info, &pc, &tmp, &counts, &base, &hist, &occ, &occ2, &sort_tmp, &run_start,
-                      &pair_val, &flag, &cnt, &off64, &lists, &bm})
+                      &pair_val, &flag, &cnt, &off64, &lists, &bm, &hub_cnt, &hub_off})
         x->release();
 }
 

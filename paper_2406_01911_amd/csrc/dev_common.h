@@ -177,6 +177,26 @@ __device__ __forceinline__ uint32_t search64(const uint32_t *scan, uint32_t g) {
     return k;
 }
 
+// Lanes own consecutive runs of slots (lane k: [start, start + count), starts
+// ascending).  For the window of slots base .. base + 63 this gives each lane
+// the owner of slot base + lane (a slot that somebody owns; else any lane): the
+// owners that begin inside the window leave their lane number at their first
+// slot, a running maximum over the lanes carries it on.  Three LDS accesses in a
+// row and six DPP moves, where a binary search over the starts was a chain of
+// six LDS reads.  Every lane of the wave calls it.
+__device__ __forceinline__ uint32_t window_owner(uint32_t *mark, uint32_t start, uint32_t count, uint32_t base) {
+    const uint32_t lane = lane_id();
+    const uint64_t first = __ballot(start <= base && base - start < count);   // owner of slot base
+    const uint32_t rel = start - base;                                        // wraps for earlier starts
+    mark[lane] = 0u;
+    wave_sync();
+    if (count != 0u && start >= base && rel < kWave) mark[rel] = lane + 1u;
+    wave_sync();
+    uint32_t x = mark[lane];
+    x = wave_scan_op(x, [](uint32_t a, uint32_t b) { return a > b ? a : b; });
+    return x ? x - 1u : (uint32_t)__ffsll((unsigned long long)first) - 1u;
+}
+
 __host__ __device__ __forceinline__ uint64_t div_up(uint64_t a, uint64_t b) { return (a + b - 1) / b; }
 
 }  // namespace hyperim

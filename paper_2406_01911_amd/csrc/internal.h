@@ -127,8 +127,8 @@ struct GreedyWorkspace {
 // between calls (allocating and freeing it per call cost more than a small
 // graph's kernels).
 struct PrepWorkspace {
-    DevBuf k1, k2;                         // hubs: counter rows, weight marks; build: per-incidence counts, prefixes
-    DevBuf vals, pc;                       // hubs: partial results, chunk prefix
+    DevBuf k1, k2;                         // hubs: occurrences by range, weight marks; build: per-incidence counts, prefixes
+    DevBuf vals, pc, hub_cnt, hub_off;     // hubs: partial results, chunk prefix, counts by range and their prefix
     DevBuf info, tmp;                      // class counts and sums, scan blocks
     DevBuf counts, base, hist;             // strata counts and statistics
     DevBuf occ, occ2, sort_tmp, run_start, pair_val;   // layer tables: occurrences, pairs

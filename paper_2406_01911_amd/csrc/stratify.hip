@@ -13,18 +13,18 @@
 //   c <= kDensePairs    in one workgroup's LDS hash table (two sizes), in
 //                       several passes over parts of the ids when the distinct
 //                       co-members may outnumber it;
-//   above, or above n / 16 (hubs)  in a row of n counters in device memory, the hub's
-//                       incidences and then its counters spread over the grid.
-// Reading and counting bound every class (LDS atomics; device atomics for the
-// hubs).  A million vertices with 3.4e8 occurrences (Zipf 1.1 members): 46 ms
-// when all pairs went through two hash tables in device memory, 10 ms now.
+//   above, or above n / 48 (hubs)  brought together by ranges of ids, a range's
+//                       counters in one workgroup's LDS.
+// Reading and counting (LDS atomics) bound every class.  A million vertices
+// with 1.9e8 occurrences (Zipf 1.1 members): 46 ms when all pairs went through
+// two hash tables in device memory, 9 ms with rows of counters in device memory
+// for the hubs, 4.5 ms now.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
 #include <cmath>
 #include <vector>
 
-#include "block_table.h"
 #include "dev_common.h"
 #include "internal.h"
 
@@ -37,7 +37,8 @@ constexpr uint32_t kWavePairs = 512;            // one wave's table: load at mos
 constexpr uint32_t kBlockPairs = 3072;          // the small workgroup table
 constexpr uint32_t kBlockTable = 16384;         // slots of the large one (ids up to three quarters of it)
 constexpr uint32_t kDensePairs = 131072;        // ... in up to 11 passes
-constexpr uint64_t kDenseBudget = 2ull << 30;   // bytes of hub counters and weight marks per batch
+constexpr uint64_t kHubBudget = 2ull << 30;     // bytes of occurrences, counts and marks per batch of hubs
+constexpr uint32_t kHubChunk = 512;             // a hub's incidences per workgroup and turn
 constexpr int kWavesPerBlock = kBlock / kWave;
 
 __device__ __forceinline__ uint32_t mix32(uint32_t x) {
@@ -54,6 +55,7 @@ struct PrepInfo {
     uint32_t n_wave, n_block, n_big, n_hub;   // vertices per class (the rest is in registers)
     uint32_t dmax, lmax;                      // hyperedges of the largest hub; largest l_v
     unsigned long long cmax;                  // largest c(v)
+    unsigned long long hub_occ, hub_chunks;   // the hubs' occurrences and chunks of incidences
     unsigned long long sum_top, sum_deg, sum_l;
     unsigned long long B[kNStrata];
 };
@@ -62,7 +64,7 @@ struct PrepInfo {
 // incidences [e0, e1) of irec (at most 64), v itself left out; `u` is valid
 // where the lane has one (else kNoKey), and every lane calls body together.
 struct SpanLds {
-    uint32_t scan[kWave], hb[kWave];
+    uint32_t mark[kWave], hb[kWave];
 };
 template <class Body>
 __device__ __forceinline__ void wave_members(SpanLds &L, const uint4 *__restrict__ irec,
@@ -74,15 +76,13 @@ __device__ __forceinline__ void wave_members(SpanLds &L, const uint4 *__restrict
     const uint32_t incl = wave_incl_scan(rec.z);
     const uint32_t total = wave_bcast(incl, kWave - 1);
     wave_sync();
-    L.scan[lane] = incl;
-    L.hb[lane] = rec.y;
-    wave_sync();
+    L.hb[lane] = rec.y - (incl - rec.z);   // member q of the span is he_mem[hb + q]; may wrap
     for (uint32_t b = 0; b < total; b += kWave) {
         const uint32_t q = b + lane;
+        const uint32_t k = window_owner(L.mark, incl - rec.z, rec.z, b);
         uint32_t u = kNoKey;
         if (q < total) {
-            const uint32_t k = search64(L.scan, q);
-            u = he_mem[L.hb[k] + (q - (k ? L.scan[k - 1] : 0u))];
+            u = he_mem[L.hb[k] + q];   // the sum is taken in 32 bits
             if (u == v) u = kNoKey;
         }
         body(u);
@@ -109,6 +109,45 @@ __device__ __forceinline__ bool lds_count(uint32_t *key, uint32_t *cnt, uint32_t
     return false;
 }
 
+// One thread's share of a table of weights: how many are not zero, the largest,
+// how many have it (meaningless while the largest is 0), and which of 1 .. 31
+// occur (bit 0: set by zeros).  Free of branches for these, which almost all
+// are: with one per weight, scanning 16384 counters of a hub cost 11000 cycles.
+struct Tally {
+    uint32_t d = 0, wm = 0, tops = 0, low = 0;
+    __device__ __forceinline__ void count(uint32_t w) {
+        d += w != 0u ? 1u : 0u;
+        tops = w > wm ? 1u : tops + (w == wm ? 1u : 0u);
+        wm = max(w, wm);
+    }
+    template <class Mark>   // mark(w): a weight of 32 or more
+    __device__ __forceinline__ void add(const uint4 &c, Mark &&mark) {
+        const uint32_t w[4] = {c.x, c.y, c.z, c.w};
+#pragma unroll
+        for (uint32_t q = 0; q < 4; ++q) count(w[q]);
+        if ((c.x | c.y | c.z | c.w) < 32u) {
+#pragma unroll
+            for (uint32_t q = 0; q < 4; ++q) low |= 1u << w[q];
+        } else {
+#pragma unroll
+            for (uint32_t q = 0; q < 4; ++q) {
+                if (w[q] < 32u) low |= 1u << w[q];
+                else mark(w[q]);
+            }
+        }
+    }
+    template <class Mark>
+    __device__ __forceinline__ void one(uint32_t w, Mark &&mark) {
+        count(w);
+        if (w < 32u) low |= 1u << w;
+        else mark(w);
+    }
+    // The marks of the wave's weights 1 .. 31.
+    __device__ __forceinline__ uint32_t wave_low() const {
+        return wave_last(wave_scan_op(low, [](uint32_t a, uint32_t b) { return a | b; })) & ~1u;
+    }
+};
+
 // Vertices of each class above 64 occurrences, and the largest c(v) and hub.
 // kClassPer vertices per thread: one device atomic per workgroup and class
 // (one per wave took 0.59 ms on a million vertices).
@@ -118,11 +157,11 @@ __global__ __launch_bounds__(kBlock) void k_classify(uint32_t n, uint32_t dense,
                                                       const uint32_t *__restrict__ v_off, uint32_t *__restrict__ lists,
                                                       PrepInfo *__restrict__ info) {
     __shared__ uint32_t cnt[4], base[4], dm_s;
-    __shared__ unsigned long long cm_s;
+    __shared__ unsigned long long cm_s, occ_s, ch_s;
     if (threadIdx.x < 4) cnt[threadIdx.x] = 0u;
     if (threadIdx.x == 4) {
         dm_s = 0u;
-        cm_s = 0ull;
+        cm_s = occ_s = ch_s = 0ull;
     }
     __syncthreads();
     const uint64_t v0 = (uint64_t)blockIdx.x * kBlock * kClassPer + threadIdx.x;
@@ -135,7 +174,12 @@ __global__ __launch_bounds__(kBlock) void k_classify(uint32_t n, uint32_t dense,
         const unsigned long long cv = v < n ? c[v] : 0ull;
         cls[r] = cv <= kWave ? -1 : cv <= kWavePairs ? 0 : cv <= kBlockPairs ? 1 : cv <= dense ? 2 : 3;
         cm = cv > cm ? cv : cm;
-        if (cls[r] == 3) dm = max(dm, v_off[v + 1] - v_off[v]);
+        if (cls[r] == 3) {
+            const uint32_t d = v_off[v + 1] - v_off[v];
+            dm = max(dm, d);
+            atomicAdd(&occ_s, cv);
+            atomicAdd(&ch_s, (unsigned long long)div_up(d, kHubChunk));
+        }
         if (cls[r] >= 0) at[r] = atomicAdd(&cnt[cls[r]], 1u);
     }
     cm = wave_max(cm);
@@ -148,7 +192,11 @@ __global__ __launch_bounds__(kBlock) void k_classify(uint32_t n, uint32_t dense,
     if (threadIdx.x < 4 && cnt[threadIdx.x]) base[threadIdx.x] = atomicAdd(&info->n_wave + threadIdx.x, cnt[threadIdx.x]);
     if (threadIdx.x == 4) {
         if (cm_s) atomicMax(&info->cmax, cm_s);
-        if (dm_s) atomicMax(&info->dmax, dm_s);
+        if (dm_s) {
+            atomicMax(&info->dmax, dm_s);
+            atomicAdd(&info->hub_occ, occ_s);
+            atomicAdd(&info->hub_chunks, ch_s);
+        }
     }
     __syncthreads();
 #pragma unroll
@@ -286,8 +334,8 @@ __global__ __launch_bounds__(kThreads) void k_layers_block(const uint32_t *__res
                                                             PrepInfo *__restrict__ info) {
     constexpr uint32_t kWaves = kThreads / kWave, kLoad = kSlots / 4 * 3, kBits = kMaxPairs / 32 + 1;
     __shared__ SpanLds spans[kWaves];
-    __shared__ uint32_t key[kSlots], cnt[kSlots], bits[kBits];
-    __shared__ uint32_t part[3][kWaves];
+    __shared__ alignas(16) uint32_t key[kSlots], cnt[kSlots];
+    __shared__ uint32_t bits[kBits], part[4][kWaves];
     __shared__ uint32_t full;
     const uint32_t lane = lane_id(), wv = uni(threadIdx.x / kWave), t = threadIdx.x;
     const uint32_t count = *n_list;
@@ -300,11 +348,11 @@ __global__ __launch_bounds__(kThreads) void k_layers_block(const uint32_t *__res
         if (t == 0) full = 0u;
         // incidences per wave and turn
         const uint32_t step = min((uint32_t)kWave, (e1 - e0 + kWaves - 1u) / kWaves);
-        uint32_t d = 0, wm = 0, tops = 0;   // this thread's slots over all passes
+        Tally y;   // this thread's slots over all passes
         for (uint32_t p = 0; p < passes; ++p) {
-            for (uint32_t s = t; s < kSlots; s += kThreads) {
-                key[s] = kNoKey;
-                cnt[s] = 0u;
+            for (uint32_t s = t; s < kSlots / 4; s += kThreads) {
+                ((uint4 *)key)[s] = make_uint4(kNoKey, kNoKey, kNoKey, kNoKey);
+                ((uint4 *)cnt)[s] = make_uint4(0u, 0u, 0u, 0u);
             }
             __syncthreads();
             for (uint64_t e = (uint64_t)e0 + (uint64_t)wv * step; e < e1; e += (uint64_t)kWaves * step)
@@ -314,44 +362,42 @@ __global__ __launch_bounds__(kThreads) void k_layers_block(const uint32_t *__res
                         full = 1u;
                 });
             __syncthreads();
-            for (uint32_t s = t; s < kSlots; s += kThreads) {
-                const uint32_t w = cnt[s];
-                if (w == 0u) continue;
-                ++d;
-                tops = w > wm ? 1u : tops + (w == wm ? 1u : 0u);
-                wm = max(w, wm);
-                const uint32_t bit = 1u << (w & 31u);
-                if ((bits[w >> 5] & bit) == 0u) atomicOr(&bits[w >> 5], bit);
-            }
+            for (uint32_t s = t; s < kSlots / 4; s += kThreads)
+                y.add(((const uint4 *)cnt)[s], [&](uint32_t w) {
+                    const uint32_t bit = 1u << (w & 31u);
+                    if ((bits[w >> 5] & bit) == 0u) atomicOr(&bits[w >> 5], bit);
+                });
             __syncthreads();
         }
-        uint32_t layers = 0;
-        for (uint32_t s = t; s < kBits; s += kThreads) layers += (uint32_t)__popc(bits[s]);
-        const uint32_t wmw = wave_max(wm);
-        d = wave_sum(d);
-        layers = wave_sum(layers);
+        const uint32_t lows = y.wave_low();
+        if (lane == 0 && lows) atomicOr(&bits[0], lows);
+        const uint32_t wmw = wave_max(y.wm), d = wave_sum(y.d);
+        const uint32_t tops = wave_sum(y.wm == wmw ? y.tops : 0u);
         if (lane == 0) {
             part[0][wv] = d;
-            part[1][wv] = layers;
-            part[2][wv] = wmw;
+            part[1][wv] = wmw;
+            part[2][wv] = tops;
         }
         __syncthreads();
-        uint32_t wmax = 0;
-        for (uint32_t q = 0; q < kWaves; ++q) wmax = max(wmax, part[2][q]);
-        __syncthreads();
-        tops = wave_sum(wm == wmax ? tops : 0u);
-        if (lane == 0) part[2][wv] = tops;
+        uint32_t layers = 0;
+        for (uint32_t s = t; s < kBits; s += kThreads) layers += (uint32_t)__popc(bits[s]);
+        layers = wave_sum(layers);
+        if (lane == 0) part[3][wv] = layers;
         __syncthreads();
         if (t == 0) {
-            uint32_t sd = 0, sl = 0, st = 0;
+            uint32_t sd = 0, sl = 0, st = 0, wmax = 0;
             for (uint32_t q = 0; q < kWaves; ++q) {
                 sd += part[0][q];
-                sl += part[1][q];
-                st += part[2][q];
+                wmax = max(wmax, part[1][q]);
+                sl += part[3][q];
             }
+            for (uint32_t q = 0; q < kWaves; ++q)
+                if (part[1][q] == wmax) st += part[2][q];
             if (full) {
                 hubs[atomicAdd(&info->n_hub, 1u)] = v;
                 atomicMax(&info->dmax, e1 - e0);
+                atomicAdd(&info->hub_occ, c[v]);
+                atomicAdd(&info->hub_chunks, (unsigned long long)div_up(e1 - e0, kHubChunk));
             } else {
                 deg[v] = sd;
                 l[v] = sl;
@@ -363,32 +409,40 @@ __global__ __launch_bounds__(kThreads) void k_layers_block(const uint32_t *__res
 }
 
 // ---- hubs --------------------------------------------------------------------
-// A batch of hubs, each with a row of `n` counters and `words` words of weight
-// marks.  chunk_off: exclusive prefix of the hubs' chunks of kHubChunk
-// incidences (one workgroup).
-constexpr uint32_t kHubChunk = 256;
-constexpr uint32_t kHubTable = 4096;      // per workgroup: occurrences met before their counters
-constexpr uint32_t kHubScan = 4096;       // counters per workgroup and turn
+// Occurrences are brought together by (hub, range of kHubBin ids) before they
+// are counted: a pass over the hubs' incidences counts them per range, a second
+// one writes their places within the range (16 bits each) there, and a
+// workgroup per (hub, range) counts them in LDS.  Chunks of kHubChunk
+// incidences spread the passes over the grid; the table of counts is laid out
+// (hub, range, chunk), so that its prefix sums are the places and no counter is
+// shared.  The passes are bound by finding and reading the members, the count
+// by LDS accesses.  The 283 largest hubs of a million vertices (Zipf 1.1), with
+// 9.3e7 occurrences: 4.8 ms when each had a row of n counters in device memory
+// (4.7e7 device atomics even after a table in LDS), 1.7 ms now.
+constexpr uint32_t kHubBinLog = 14, kHubBin = 1u << kHubBinLog;   // ids per range: 64 KB of counters
+constexpr uint32_t kHubBins = 1024;                               // ranges per pass
+constexpr int kHubBlock = 1024;                                   // threads that count a range
 
+// chunk_off: exclusive prefix of the hubs' chunks (one workgroup).
 __global__ __launch_bounds__(kBlock) void k_hub_chunks(const uint32_t *__restrict__ hubs, uint32_t count,
                                                         const uint32_t *__restrict__ v_off,
-                                                        unsigned long long *__restrict__ chunk_off) {
-    __shared__ unsigned long long part[kWavesPerBlock];
-    __shared__ unsigned long long carry;
-    if (threadIdx.x == 0) carry = 0ull;
+                                                        uint32_t *__restrict__ chunk_off) {
+    __shared__ uint32_t part[kWavesPerBlock];
+    __shared__ uint32_t carry;
+    if (threadIdx.x == 0) carry = 0u;
     __syncthreads();
     const uint32_t lane = lane_id(), wv = threadIdx.x / kWave;
     for (uint32_t base = 0; base < count; base += kBlock) {
         const uint32_t i = base + threadIdx.x;
-        unsigned long long x = 0;
+        uint32_t x = 0;
         if (i < count) {
             const uint32_t v = hubs[i];
-            x = (v_off[v + 1] - v_off[v] + (uint64_t)kHubChunk - 1u) / kHubChunk;
+            x = (uint32_t)div_up(v_off[v + 1] - v_off[v], kHubChunk);
         }
-        const unsigned long long incl = wave_incl_scan(x);
+        const uint32_t incl = wave_incl_scan(x);
         if (lane == kWave - 1) part[wv] = incl;
         __syncthreads();
-        unsigned long long before = carry;
+        uint32_t before = carry;
         for (uint32_t q = 0; q < wv; ++q) before += part[q];
         if (i < count) chunk_off[i] = before + incl - x;
         __syncthreads();
@@ -398,109 +452,165 @@ __global__ __launch_bounds__(kBlock) void k_hub_chunks(const uint32_t *__restric
     if (threadIdx.x == 0) chunk_off[count] = carry;
 }
 
-// Occurrences of the hubs into their counters, a chunk per workgroup and turn.
-// The chunk's occurrences meet in an LDS table first: co-members of a hub are
-// mostly hubs again, and device atomics on one counter queue up.
-__global__ __launch_bounds__(kBlock) void k_hub_count(const uint32_t *__restrict__ hubs, uint32_t count,
-                                                       const unsigned long long *__restrict__ chunk_off,
-                                                       const uint32_t *__restrict__ v_off,
-                                                       const uint4 *__restrict__ irec,
-                                                       const uint32_t *__restrict__ he_mem, uint64_t n,
-                                                       uint32_t *__restrict__ rows) {
+// Largest i in [0, count) with off[i] <= x (off[0] = 0, off[count] > x), 64
+// entries at a time; every lane of the wave calls it with the same x.
+__device__ __forceinline__ uint32_t wave_find(const uint32_t *__restrict__ off, uint32_t count, uint32_t x) {
+    uint32_t lo = 0, len = count;   // in [lo, lo + len)
+    while (len > 1) {
+        const uint32_t step = (len + kWave - 1u) / kWave, i = lane_id() * step;
+        const uint32_t k = (uint32_t)__popcll(__ballot(i < len && off[lo + i] <= x)) - 1u;
+        lo += k * step;
+        len = min(step, len - k * step);
+    }
+    return lo;
+}
+
+// The members of the hubs' chunks with ids in the ranges [bin0, bin0 + nb):
+// counted per (hub, range, chunk), or (kPlace) written to the places whose
+// firsts `off` holds.
+template <bool kPlace>
+__global__ __launch_bounds__(kBlock) void k_hub_pass(const uint32_t *__restrict__ hubs, uint32_t count,
+                                                      const uint32_t *__restrict__ chunk_off,
+                                                      const uint32_t *__restrict__ v_off,
+                                                      const uint4 *__restrict__ irec,
+                                                      const uint32_t *__restrict__ he_mem, uint32_t bin0, uint32_t nb,
+                                                      const uint64_t *__restrict__ off, uint32_t *__restrict__ cnt,
+                                                      uint16_t *__restrict__ entries) {
     __shared__ SpanLds spans[kWavesPerBlock];
-    __shared__ BlockTable<kHubTable> tab;
-    __shared__ uint32_t tcnt[kHubTable];
+    __shared__ uint32_t bin[kHubBins];   // counts, or next places (below 2^32: he_mem's positions are)
     const uint32_t wv = uni(threadIdx.x / kWave);
-    tab.clear_keys();
-    for (uint32_t s = threadIdx.x; s < kHubTable; s += kBlock) tcnt[s] = 0u;
-    __syncthreads();
-    const unsigned long long chunks = chunk_off[count];
-    for (unsigned long long ch = blockIdx.x; ch < chunks; ch += gridDim.x) {
-        uint32_t lo = 0, hi = count;   // chunk_off[lo] <= ch < chunk_off[hi]
-        while (hi - lo > 1) {
-            const uint32_t mid = (lo + hi) / 2;
-            if (chunk_off[mid] <= ch) lo = mid; else hi = mid;
-        }
-        const uint32_t v = uni(hubs[lo]);
-        uint32_t *row = rows + (uint64_t)lo * n;
-        const uint64_t e_end = v_off[v + 1];
-        const uint64_t b0 = v_off[v] + (ch - chunk_off[lo]) * kHubChunk;
-        const uint64_t b1 = min(b0 + kHubChunk, e_end);
+    const uint32_t chunks = uni(chunk_off[count]);
+    for (uint32_t ch = blockIdx.x; ch < chunks; ch += gridDim.x) {
+        const uint32_t h = uni(wave_find(chunk_off, count, ch)), v = uni(hubs[h]);
+        const uint32_t c0 = uni(chunk_off[h]), nch = uni(chunk_off[h + 1]) - c0;
+        const uint64_t first = (uint64_t)c0 * nb + (ch - c0);   // of this chunk's counts, nch apart
+        for (uint32_t b = threadIdx.x; b < nb; b += kBlock)
+            bin[b] = kPlace ? (uint32_t)off[first + (uint64_t)b * nch] : 0u;
+        __syncthreads();
+        const uint64_t b0 = (uint64_t)v_off[v] + (uint64_t)(ch - c0) * kHubChunk;
+        const uint64_t b1 = min(b0 + kHubChunk, (uint64_t)v_off[v + 1]);
         for (uint64_t e = b0 + (uint64_t)wv * kWave; e < b1; e += kBlock)
             wave_members(spans[wv], irec, he_mem, e, min(e + kWave, b1), v, [&](uint32_t u) {
-                if (u == kNoKey) return;
-                const uint32_t sl = tab.slot(u);
-                if (sl != kTableEmpty) atomicAdd(&tcnt[sl], 1u);
-                else atomicAdd(&row[u], 1u);
+                const uint32_t b = (u >> kHubBinLog) - bin0;
+                if (u == kNoKey || b >= nb) return;
+                const uint32_t at = atomicAdd(&bin[b], 1u);
+                if constexpr (kPlace) entries[at] = (uint16_t)(u & (kHubBin - 1u));
             });
         __syncthreads();
-        for (uint32_t s = threadIdx.x; s < kHubTable; s += kBlock) {
-            const uint32_t u = tab.key[s];
-            if (u != kTableEmpty) {
-                atomicAdd(&row[u], tcnt[s]);
-                tab.key[s] = kTableEmpty;
-                tcnt[s] = 0u;
-            }
+        if constexpr (!kPlace) {
+            for (uint32_t b = threadIdx.x; b < nb; b += kBlock) cnt[first + (uint64_t)b * nch] = bin[b];
+            __syncthreads();
         }
-        __syncthreads();
     }
 }
 
-// Per (hub, kHubScan counters): co-members, largest weight and how many have
-// it (part: 3 words each), and the weights' marks.
-__global__ __launch_bounds__(kBlock) void k_hub_scan(uint32_t n, uint32_t tiles, const uint32_t *__restrict__ rows,
-                                                      uint32_t words, uint32_t *__restrict__ marks,
-                                                      uint32_t *__restrict__ part) {
-    constexpr uint32_t kLow = 2048;   // smaller weights are marked once per workgroup
-    __shared__ uint32_t low[kLow / 32];
-    __shared__ uint32_t wpart[2][kWavesPerBlock];
-    const uint32_t lane = lane_id(), wv = threadIdx.x / kWave;
-    const uint32_t hub = blockIdx.x / tiles, tile = blockIdx.x % tiles;
-    const uint32_t *row = rows + (uint64_t)hub * n;
-    uint32_t *mk = marks + (uint64_t)hub * words;
-    for (uint32_t s = threadIdx.x; s < kLow / 32; s += kBlock) low[s] = 0u;
+// Per (hub, range): co-members, largest weight and how many have it (part: 3
+// words each), and the weights' marks.
+__global__ __launch_bounds__(kHubBlock) void k_hub_count(uint32_t count, const uint32_t *__restrict__ chunk_off,
+                                                          const uint64_t *__restrict__ off,
+                                                          const uint16_t *__restrict__ entries, uint32_t bin0,
+                                                          uint32_t nb, uint32_t tiles, uint32_t words,
+                                                          uint32_t *__restrict__ marks, uint32_t *__restrict__ part) {
+    constexpr uint32_t kLow = 2048, kWaves = kHubBlock / kWave;   // smaller weights are marked once per workgroup
+    __shared__ alignas(16) uint32_t cnt[kHubBin];   // zero between items
+    __shared__ uint32_t low[kLow / 32];             // likewise
+    __shared__ uint32_t wpart[3][kWaves];
+    const uint32_t lane = lane_id(), wv = uni(threadIdx.x / kWave), t = threadIdx.x;
+    for (uint32_t s = t; s < kHubBin / 4; s += kHubBlock) ((uint4 *)cnt)[s] = make_uint4(0u, 0u, 0u, 0u);
+    if (t < kLow / 32) low[t] = 0u;
     __syncthreads();
-    uint32_t d = 0, wm = 0, tops = 0;
-    for (uint32_t i = threadIdx.x; i < kHubScan; i += kBlock) {
-        const uint64_t u = (uint64_t)tile * kHubScan + i;
-        const uint32_t w = u < n ? row[u] : 0u;
-        if (w == 0u) continue;
-        ++d;
-        tops = w > wm ? 1u : tops + (w == wm ? 1u : 0u);
-        wm = max(w, wm);
-        const uint32_t bit = 1u << (w & 31u);
-        if (w < kLow) {
-            if ((low[w >> 5] & bit) == 0u) atomicOr(&low[w >> 5], bit);
+    // (hub, range) of an item, the workgroups' items being gridDim.x apart
+    const uint32_t dh = gridDim.x / nb, db = gridDim.x % nb;
+    uint32_t hub1 = blockIdx.x / nb, b1 = blockIdx.x % nb;
+    uint64_t beg, end, beg1 = 0, end1 = 0;   // of this item and the next, read one item ahead
+    auto span = [&]() {
+        beg1 = end1 = 0;
+        if (hub1 >= count) return;
+        const uint32_t c0 = chunk_off[hub1], nch = chunk_off[hub1 + 1] - c0;
+        const uint64_t first = (uint64_t)c0 * nb + (uint64_t)b1 * nch;
+        beg1 = uni64(off[first]);
+        end1 = uni64(off[first + nch]);
+    };
+    uint32_t u[4], u1[4];   // entries of this item; the first ones of the next
+    auto load = [&](uint32_t (&u)[4], uint64_t e, uint64_t to) {
+#pragma unroll
+        for (uint32_t q = 0; q < 4; ++q) u[q] = e + q * kHubBlock < to ? entries[e + q * kHubBlock] : kNoKey;
+    };
+    span();
+    load(u1, beg1 + t, end1);
+    while (hub1 < count) {
+        const uint32_t hub = hub1, b = b1;
+        beg = beg1;
+        end = end1;
+        hub1 += dh;
+        b1 += db;
+        if (b1 >= nb) {
+            b1 -= nb;
+            ++hub1;
+        }
+        span();
+#pragma unroll
+        for (uint32_t q = 0; q < 4; ++q) u[q] = u1[q];
+        uint32_t *o = part + 3 * ((uint64_t)hub * tiles + bin0 + b);
+        uint32_t *mk = marks + (uint64_t)hub * words;
+        for (uint64_t e = beg + t; e < end;) {
+#pragma unroll
+            for (uint32_t q = 0; q < 4; ++q)
+                if (u[q] != kNoKey) atomicAdd(&cnt[u[q]], 1u);
+            e += 4u * kHubBlock;
+            if (e < end) load(u, e, end);
+        }
+        load(u1, beg1 + t, end1);
+        if (beg == end) {
+            if (t < 3) o[t] = 0u;
+            continue;
+        }
+        __syncthreads();
+        Tally y;
+        auto mark = [&](uint32_t w) {
+            const uint32_t bit = 1u << (w & 31u);
+            if (w >= kLow) atomicOr(&mk[w >> 5], bit);
+            else if ((low[w >> 5] & bit) == 0u) atomicOr(&low[w >> 5], bit);
+        };
+        if (end - beg <= 4u * kHubBlock) {
+            // every entry is still in a register: whoever takes a counter first has its weight
+#pragma unroll
+            for (uint32_t q = 0; q < 4; ++q)
+                if (u[q] != kNoKey) y.one(atomicExch(&cnt[u[q]], 0u), mark);
         } else {
-            atomicOr(&mk[w >> 5], bit);
+            for (uint32_t s = t; s < kHubBin / 4; s += kHubBlock) {
+                const uint4 c4 = ((const uint4 *)cnt)[s];
+                if ((c4.x | c4.y | c4.z | c4.w) == 0u) continue;
+                ((uint4 *)cnt)[s] = make_uint4(0u, 0u, 0u, 0u);
+                y.add(c4, mark);
+            }
+        }
+        uint32_t wmw = 0, lows = 0, d = 0, tops = 0;
+        if (__ballot(y.d != 0u)) {
+            wmw = wave_max(y.wm);
+            lows = y.wave_low();
+            d = wave_sum(y.d);
+            tops = wave_sum(y.wm == wmw ? y.tops : 0u);
+        }
+        if (lane == 0) {
+            wpart[0][wv] = d;
+            wpart[1][wv] = wmw;
+            wpart[2][wv] = tops;
+            if (lows) atomicOr(&low[0], lows);
+        }
+        __syncthreads();
+        if (wv == 0) {
+            const uint32_t w = lane < kWaves ? wpart[1][lane] : 0u, wmax = wave_max(w);
+            const uint32_t sd = wave_sum(lane < kWaves ? wpart[0][lane] : 0u);
+            const uint32_t st = wave_sum(lane < kWaves && w == wmax ? wpart[2][lane] : 0u);
+            if (lane < 3) o[lane] = lane == 0 ? sd : lane == 1 ? wmax : st;
+        } else if (wv == 1) {
+            static_assert(kLow / 32 == kWave, "one word of marks per lane");
+            const uint32_t m = low[lane];
+            low[lane] = 0u;
+            if (lane < words && m) atomicOr(&mk[lane], m);
         }
     }
-    const uint32_t wmw = wave_max(wm);
-    d = wave_sum(d);
-    if (lane == 0) {
-        wpart[0][wv] = d;
-        wpart[1][wv] = wmw;
-    }
-    __syncthreads();
-    uint32_t wmax = 0, sd = 0;
-    for (uint32_t q = 0; q < kWavesPerBlock; ++q) {
-        sd += wpart[0][q];
-        wmax = max(wmax, wpart[1][q]);
-    }
-    __syncthreads();
-    tops = wave_sum(wm == wmax ? tops : 0u);
-    if (lane == 0) wpart[0][wv] = tops;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        uint32_t st = 0;
-        for (uint32_t q = 0; q < kWavesPerBlock; ++q) st += wpart[0][q];
-        uint32_t *o = part + 3 * ((uint64_t)hub * tiles + tile);
-        o[0] = sd;
-        o[1] = wmax;
-        o[2] = wmax ? st : 0u;
-    }
-    for (uint32_t s = threadIdx.x; s < kLow / 32 && s < words; s += kBlock)
-        if (low[s]) atomicOr(&mk[s], low[s]);
 }
 
 // One workgroup per hub: its tiles' results and marks together.
@@ -644,12 +754,13 @@ int stratify_device(hyperim_graph g, PrepWorkspace &w, hipStream_t s) {
     const unsigned long long *cc = g->c.as<unsigned long long>();
     uint32_t *deg = g->deg.as<uint32_t>(), *ll = g->l.as<uint32_t>(), *top = g->top.as<uint32_t>();
     const uint32_t tiles = (uint32_t)std::max<uint64_t>(div_up(n, kBlock), 1);
-    // From here on a vertex is a hub.  A hub's row costs 8 n bytes and spreads
-    // over the grid; below n / 16 occurrences that is more than the occurrences
-    // are worth, and a workgroup's passes over them (at most 11) are short.
-    // With 131072 for every n the last workgroup of a 1e5-vertex graph took
-    // 0.96 ms.
-    const uint32_t dense = std::min(std::max<uint32_t>(n / 16u, kBlockTable / 4u * 3u), kDensePairs);
+    // Above this a vertex is a hub.  A hub costs its occurrences twice through
+    // memory and n / 16384 ranges, a workgroup's passes grow with the square of
+    // the occurrences (at most 11 passes).  On a million vertices the large
+    // workgroups and the hubs take 3.6 ms together with n / 16, 2.9 with n / 42,
+    // 3.1 with 12000 and 3.5 with 8000; with 131072 for every n the last
+    // workgroup of a 1e5-vertex graph took 0.96 ms.
+    const uint32_t dense = std::min(std::max<uint32_t>(n / 48u, kBlockTable / 4u * 3u), kDensePairs);
     hipLaunchKernelGGL(k_classify, dim3((uint32_t)div_up(n, kBlock * kClassPer)), dim3(kBlock), 0, s, n, dense, cc,
                        v_off, lists, di);
     hipLaunchKernelGGL((k_layers_block<1024, kBlockTable, kDensePairs>), dim3(std::min<uint32_t>(tiles, 512)), dim3(1024), 0,
@@ -665,25 +776,70 @@ int stratify_device(hyperim_graph g, PrepWorkspace &w, hipStream_t s) {
                        cc, v_off, irec, he_mem, deg, ll, top);
     HIM_HIP(hipStreamSynchronize(s));
     if (hi.n_hub) {
-        const uint32_t words = hi.dmax / 32u + 1u, row_tiles = (uint32_t)div_up(n, kHubScan);
-        const uint64_t per_hub = 4ull * n + 4ull * words + 12ull * row_tiles;
-        const uint32_t batch = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(hi.n_hub, kDenseBudget / per_hub));
-        HIM_CHECK(w.k1.reserve(4ull * n * batch, s));
-        HIM_CHECK(w.k2.reserve(4ull * words * batch, s));
-        HIM_CHECK(w.vals.reserve(12ull * row_tiles * batch, s));
-        HIM_CHECK(w.pc.reserve(8ull * ((size_t)batch + 1), s));
-        for (uint32_t h0 = 0; h0 < hi.n_hub; h0 += batch) {
-            const uint32_t cnt = std::min(batch, hi.n_hub - h0);
-            HIM_HIP(hipMemsetAsync(w.k1.ptr, 0, 4ull * n * cnt, s));
-            HIM_HIP(hipMemsetAsync(w.k2.ptr, 0, 4ull * words * cnt, s));
-            hipLaunchKernelGGL(k_hub_chunks, dim3(1), dim3(kBlock), 0, s, hubs + h0, cnt, v_off,
-                               w.pc.as<unsigned long long>());
-            hipLaunchKernelGGL(k_hub_count, dim3(2048), dim3(kBlock), 0, s, hubs + h0, cnt,
-                               w.pc.as<unsigned long long>(), v_off, irec, he_mem, (uint64_t)n, w.k1.as<uint32_t>());
-            hipLaunchKernelGGL(k_hub_scan, dim3(cnt * row_tiles), dim3(kBlock), 0, s, n, row_tiles,
-                               w.k1.as<uint32_t>(), words, w.k2.as<uint32_t>(), w.vals.as<uint32_t>());
-            hipLaunchKernelGGL(k_hub_final, dim3(cnt), dim3(kBlock), 0, s, hubs + h0, row_tiles,
-                               w.vals.as<uint32_t>(), words, w.k2.as<uint32_t>(), deg, ll, top);
+        const uint32_t words = hi.dmax / 32u + 1u, bins = (uint32_t)div_up(n, kHubBin), nb = std::min(bins, kHubBins);
+        // Batches of hubs: 2 bytes an occurrence, 12 a chunk and range of a
+        // pass, and the marks and parts of a hub.  Most graphs' hubs are one
+        // batch, and their sizes stay on the device.
+        const uint64_t per_chunk = 12ull * nb, per_hub = 4ull * words + 12ull * bins;
+        std::vector<std::pair<uint32_t, uint64_t>> batches{{hi.n_hub, hi.hub_chunks}};   // hubs, chunks
+        uint64_t occ = hi.hub_occ;   // of the largest batch
+        if (2 * hi.hub_occ + per_chunk * hi.hub_chunks + per_hub * hi.n_hub > kHubBudget) {
+            std::vector<uint32_t> ids(hi.n_hub), ends(n + 1ull);
+            std::vector<uint64_t> cv(n);
+            HIM_HIP(hipMemcpyAsync(ids.data(), hubs, 4ull * hi.n_hub, hipMemcpyDeviceToHost, s));
+            HIM_HIP(hipMemcpyAsync(ends.data(), v_off, 4ull * (n + 1ull), hipMemcpyDeviceToHost, s));
+            HIM_HIP(hipMemcpyAsync(cv.data(), cc, 8ull * n, hipMemcpyDeviceToHost, s));
+            HIM_HIP(hipStreamSynchronize(s));
+            batches.clear();
+            occ = 0;
+            uint64_t used = 0, occ_b = 0;
+            for (uint32_t v : ids) {
+                const uint64_t chunks = div_up(ends[v + 1ull] - ends[v], kHubChunk);
+                const uint64_t need = 2 * cv[v] + per_chunk * chunks + per_hub;
+                if (batches.empty() || used + need > kHubBudget) {
+                    batches.push_back({0, 0});
+                    used = occ_b = 0;
+                }
+                batches.back().first += 1;
+                batches.back().second += chunks;
+                used += need;
+                occ_b += cv[v];
+                occ = std::max(occ, occ_b);
+            }
+        }
+        uint64_t hubs_max = 0, chunks_max = 0;
+        for (const auto &b : batches) {
+            hubs_max = std::max<uint64_t>(hubs_max, b.first);
+            chunks_max = std::max(chunks_max, b.second);
+        }
+        HIM_CHECK(w.k1.reserve(2ull * occ, s));
+        HIM_CHECK(w.k2.reserve(4ull * words * hubs_max, s));
+        HIM_CHECK(w.vals.reserve(12ull * bins * hubs_max, s));
+        HIM_CHECK(w.pc.reserve(4ull * (hubs_max + 1), s));
+        HIM_CHECK(w.hub_cnt.reserve(4ull * nb * chunks_max, s));
+        HIM_CHECK(w.hub_off.reserve(8ull * (nb * chunks_max + 1), s));
+        uint32_t *chunk_off = w.pc.as<uint32_t>(), *cnt = w.hub_cnt.as<uint32_t>();
+        uint64_t *off = w.hub_off.as<uint64_t>();
+        uint16_t *entries = w.k1.as<uint16_t>();
+        const uint32_t *hub = hubs;
+        for (const auto &[count, chunks] : batches) {
+            HIM_HIP(hipMemsetAsync(w.k2.ptr, 0, 4ull * words * count, s));
+            hipLaunchKernelGGL(k_hub_chunks, dim3(1), dim3(kBlock), 0, s, hub, count, v_off, chunk_off);
+            const dim3 grid((uint32_t)std::min<uint64_t>(chunks, 2048));
+            for (uint32_t bin0 = 0; bin0 < bins; bin0 += kHubBins) {
+                const uint32_t now = std::min(bins - bin0, kHubBins);
+                hipLaunchKernelGGL(k_hub_pass<false>, grid, dim3(kBlock), 0, s, hub, count, chunk_off, v_off, irec,
+                                   he_mem, bin0, now, off, cnt, entries);
+                HIM_CHECK(scan_u32_to_u64(cnt, off, chunks * now, 0, tmp_b, s));
+                hipLaunchKernelGGL(k_hub_pass<true>, grid, dim3(kBlock), 0, s, hub, count, chunk_off, v_off, irec,
+                                   he_mem, bin0, now, off, cnt, entries);
+                hipLaunchKernelGGL(k_hub_count, dim3((uint32_t)std::min<uint64_t>((uint64_t)count * now, 2048)),
+                                   dim3(kHubBlock), 0, s, count, chunk_off, off, entries, bin0, now, bins, words,
+                                   w.k2.as<uint32_t>(), w.vals.as<uint32_t>());
+            }
+            hipLaunchKernelGGL(k_hub_final, dim3(count), dim3(kBlock), 0, s, hub, bins, w.vals.as<uint32_t>(), words,
+                               w.k2.as<uint32_t>(), deg, ll, top);
+            hub += count;
         }
         HIM_HIP(hipGetLastError());
     }

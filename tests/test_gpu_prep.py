@@ -1,6 +1,6 @@
 """Graph preparation at the edges of its classes: vertices are counted by one
 of five routes depending on their co-member occurrences c(v) (64, 512 and
-3072 are the last of three; the hubs begin above 12288, n / 16 or 131072), and segments of more than 4096 hyperedges are
+3072 are the last of three; the hubs begin above 12288, n / 48 or 131072), and segments of more than 4096 hyperedges are
 sorted through bitmaps.  Everything is whole numbers and has to equal the
 oracle's."""
 import numpy as np
@@ -49,8 +49,8 @@ VERTICES = {
 @pytest.mark.parametrize("case", sorted(VERTICES))
 def test_layer_counts_at_class_edges(hy, case):
     print(f"[gpu] prep case={case}", flush=True)
-    # hubs begin above 131072 occurrences on two million vertices or more
-    n = {"block_passes": 2100000, "last_before_hubs": 150000}.get(case, 140000)
+    # hubs begin above 131072 occurrences on 6.3 million vertices or more
+    n = {"block_passes": 6300000, "last_before_hubs": 150000}.get(case, 140000)
     rng = np.random.Generator(np.random.PCG64(sorted(VERTICES).index(case)))
     edges = []
     for i, (c, size, pool) in enumerate(VERTICES[case]):
@@ -94,3 +94,48 @@ def test_long_segments(hy, d, duplicate):
     a, b = g.read(strata=False), o.arrays()
     for k in ("v_off", "v_he", "thr", "c"):
         assert np.array_equal(a[k], b[k]), k
+
+
+def _layers_of(co):
+    """l, deg and top of a vertex with these co-member occurrences."""
+    w = np.unique(co, return_counts=True)[1]
+    return len(np.unique(w)), len(w), int((w == w.max()).sum())
+
+
+def test_hubs_in_several_batches(hy):
+    """Every vertex a hub and 1.4e9 occurrences together: more than one batch
+    of hubs holds (2 GiB, two bytes each)."""
+    print("[gpu] prep hub batches", flush=True)
+    n = 24000
+    half = n // 2
+    rng = np.random.Generator(np.random.PCG64(3))
+    edges = [rng.permutation(n), rng.permutation(n), rng.permutation(half), rng.permutation(half)]
+    hg = hypergen.from_lists(n, [e.tolist() for e in edges])
+    g = hy.build_graph(n, hg.he_off, hg.he_mem, 1, 0.0)
+    g.stratify()
+    a = g.read()
+    first = np.arange(n) < half   # in four hyperedges: weight 4 inside the half, 2 outside
+    assert np.array_equal(a["l"], np.where(first, 2, 1))
+    assert np.array_equal(a["deg"], np.full(n, n - 1))
+    assert np.array_equal(a["top"], np.where(first, half - 1, n - 1))
+
+
+@pytest.mark.parametrize("n", [(1 << 24) - 1, (1 << 24) + 1, (1 << 24) + 40000])
+def test_hubs_over_wide_ids(hy, n):
+    """Ids on both sides of 2^24, the ids one pass over a hub's members takes."""
+    print(f"[gpu] prep wide hub n={n}", flush=True)
+    rng = np.random.Generator(np.random.PCG64(n))
+    hub = n - 1
+    edges = []
+    for i in range(400):
+        near = rng.integers(n - 3000, n - 1, size=200)   # weights up to dozens, at the far end of the ids
+        m = np.unique(np.concatenate([near, rng.integers(0, n - 1, size=300)]))
+        edges.append([hub] + m.tolist())
+    hg = hypergen.from_lists(n, edges)
+    co = np.concatenate([np.asarray(e[1:]) for e in edges])
+    assert len(co) > 131072
+    g = hy.build_graph(n, hg.he_off, hg.he_mem, 1, 0.0)
+    g.stratify()
+    a = g.read()
+    assert a["c"][hub] == len(co)
+    assert (a["l"][hub], a["deg"][hub], a["top"][hub]) == _layers_of(co)
