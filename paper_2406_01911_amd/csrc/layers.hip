@@ -4,20 +4,24 @@
 // tables of ln(l + 1) and e^-P(L_i) that the RR kernel's count draws use.
 //
 // Built once per graph at stratify time, on the device:
-//   1. every co-member occurrence (v, u) of incidence e is written, as the
-//      key v << b | u (b = bits of a vertex id), at the incidence's channel
-//      prefix chan[e] (the graph's exclusive prefix of |he| - 1 over v_he);
-//   2. a device-wide radix sort orders the keys (rocPRIM), so each vertex's
-//      occurrences are contiguous and ascending in u;
-//   3. run heads give the distinct pairs (v, u) and their run lengths w(v,u)
-//      (heads are counted per tile, then written at the tiles' offsets: two
-//      reads of the keys and no per-key flag or offset);
-//   4. a second, stable radix sort by the key v << 32 | ~w puts each vertex's
-//      co-members in layers (descending w; equal w keep ascending u);
-//   5. positions where the key changes are the layer ends.
+//   1. every co-member occurrence (v, u) is written as the key u << b | v (b =
+//      bits of a vertex id) at the incidences' channel prefixes, v's
+//      incidences after those of smaller ids: ascending in the low half;
+//   2. a stable device-wide radix sort by the high half alone (rocPRIM) leaves
+//      the occurrences in order of both (they are symmetric: which half is
+//      whose is not told apart any more, and the high one is called v);
+//   3. a run of equal keys is a distinct pair (v, u), its length w(v, u).  Runs
+//      of one key, most of them, are v's last layer and are in order already:
+//      they go to their places, told by prefix sums;
+//   4. the longer runs are sorted, stable, by v and descending w;
+//   5. positions where that key changes are the other layers' ends.
+// The passes over all occurrences bound it: sorting by both halves was five
+// passes instead of three, and sorting all distinct pairs by 32 + b bits seven
+// passes of 12 bytes: the sorts of a million vertices with 1.9e8 occurrences
+// took 18.4 ms, 7.8 now, all of the tables 30 ms, 13 now.
 // The buffers of 1-5 serve twice where one step's input is spent, and stay in
 // the workspace up to kKeepBytes: allocating and freeing 15 GB per call took up
-// to half a second (a million vertices, 3.4e8 occurrences).
+// to half a second (a million vertices, 1.9e8 occurrences).
 // ln and e^-P are evaluated on the host with the C library's log and exp, so
 // the device uses the same doubles as any host code that calls them.
 #include <hip/hip_runtime.h>
@@ -43,9 +47,9 @@ uint32_t grid_for(uint64_t items, uint32_t cap = 8192) {
     return (uint32_t)std::min<uint64_t>(g, cap);
 }
 
-// Owner vertex of incidence e: the last v with v_off[v] <= e.
-__device__ __forceinline__ uint32_t owner(const uint32_t *__restrict__ v_off, uint32_t n, uint64_t e) {
-    uint32_t lo = 0, hi = n;   // v_off[lo] <= e < v_off[hi]
+// Owner vertex of incidence e: the last v in [lo, hi) with v_off[v] <= e, given
+// v_off[lo] <= e < v_off[hi].
+__device__ __forceinline__ uint32_t owner(const uint32_t *__restrict__ v_off, uint32_t lo, uint32_t hi, uint64_t e) {
     while (hi - lo > 1) {
         const uint32_t mid = lo + (hi - lo) / 2;
         if (v_off[mid] <= e) lo = mid; else hi = mid;
@@ -53,18 +57,43 @@ __device__ __forceinline__ uint32_t owner(const uint32_t *__restrict__ v_off, ui
     return lo;
 }
 
-// 1. Occurrences: incidence e = (v, he) writes v << b | u for the members u
-// of he other than v at chan[e] ...
-__global__ void k_occ_emit(uint32_t n, uint64_t nnz, uint32_t b, const uint32_t *__restrict__ v_off,
-                           const uint32_t *__restrict__ v_he, const uint32_t *__restrict__ he_off,
-                           const uint32_t *__restrict__ he_mem, const unsigned long long *__restrict__ chan,
-                           unsigned long long *__restrict__ occ) {
-    for (uint64_t e = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; e < nnz; e += (uint64_t)gridDim.x * blockDim.x) {
-        const uint32_t v = owner(v_off, n, e), he = v_he[e];
-        uint64_t at = chan[e];
-        for (uint32_t i = he_off[he]; i < he_off[he + 1]; ++i) {
-            const uint32_t u = he_mem[i];
-            if (u != v) occ[at++] = ((unsigned long long)v << b) | u;
+// 1. Occurrences: incidence e = (v, he) writes u << b | v for the members u of
+// he other than v, at chan[e] ...  A wave takes 64 incidences, flattened over
+// their members; bound by the writes.  (One thread per incidence, its members
+// one after another and its owner searched among all vertices: 4.4 ms for 1.9e8
+// occurrences, 1.2 now.)
+__global__ __launch_bounds__(kBlock) void k_occ_emit(uint32_t n, uint64_t nnz, uint32_t b,
+                                                      const uint32_t *__restrict__ v_off,
+                                                      const uint4 *__restrict__ irec,
+                                                      const uint32_t *__restrict__ he_mem,
+                                                      const unsigned long long *__restrict__ chan,
+                                                      unsigned long long *__restrict__ occ) {
+    __shared__ uint32_t mark_s[kBlock / kWave][kWave], hb_s[kBlock / kWave][kWave], own_s[kBlock / kWave][kWave];
+    const uint32_t lane = lane_id(), wv = uni(threadIdx.x / kWave);
+    uint32_t *hb = hb_s[wv], *own = own_s[wv];
+    const uint64_t waves = (uint64_t)gridDim.x * (kBlock / kWave);
+    for (uint64_t e0 = ((uint64_t)blockIdx.x * (kBlock / kWave) + wv) * kWave; e0 < nnz; e0 += waves * kWave) {
+        const uint64_t e = min(e0 + lane, nnz - 1u);
+        // the owners of the ends first, the others between them
+        const uint32_t end = lane < 2 ? owner(v_off, 0u, n, lane ? min(e0 + kWave, nnz) - 1u : e0) : 0u;
+        const uint32_t v = owner(v_off, wave_bcast(end, 0), wave_bcast(end, 1) + 1u, e);
+        uint4 rec = irec[e];
+        if (e0 + lane >= nnz) rec.z = 0u;
+        const uint32_t incl = wave_incl_scan(rec.z), total = wave_bcast(incl, kWave - 1);
+        uint64_t at = chan[e0];
+        wave_sync();
+        hb[lane] = rec.y - (incl - rec.z);   // member q of the span is he_mem[hb + q]; may wrap
+        own[lane] = v;
+        for (uint32_t q0 = 0; q0 < total; q0 += kWave) {
+            const uint32_t q = q0 + lane, k = window_owner(mark_s[wv], incl - rec.z, rec.z, q0);
+            uint32_t u = 0, o = 0;
+            if (q < total) {
+                u = he_mem[hb[k] + q];   // the sum is taken in 32 bits
+                o = own[k];
+            }
+            const uint64_t who = __ballot(u != o);   // never for lanes without a member
+            if (u != o) occ[at + lane_rank(who)] = ((unsigned long long)u << b) | o;
+            at += (uint64_t)__popcll(who);
         }
     }
 }
@@ -89,91 +118,183 @@ __device__ __forceinline__ uint32_t block_prefix(uint32_t c, uint32_t *total) {
     return before;
 }
 
-// 3. Run heads of the sorted keys: their count per tile.
-__global__ __launch_bounds__(kBlock) void k_head_count(uint64_t total, const unsigned long long *__restrict__ key,
-                                                        uint32_t *__restrict__ tile_cnt) {
-    const uint64_t i0 = (uint64_t)blockIdx.x * kTile;
-    uint32_t c = 0, all;
+// The runs that begin at the sorted keys k[1 .. kPer] (k[0] and k[kPer + 1]:
+// their neighbours), positions i0 ..: of one key (single) and longer.
+__device__ __forceinline__ void run_heads(const unsigned long long (&k)[kPer + 2], uint64_t i0, uint64_t total,
+                                          uint32_t *single, uint32_t *longer) {
+    *single = *longer = 0u;
+#pragma unroll
     for (uint32_t r = 0; r < kPer; ++r) {
-        const uint64_t i = i0 + r * kBlock + threadIdx.x;
-        c += i < total && (i == 0 || key[i] != key[i - 1]) ? 1u : 0u;
+        const uint64_t i = i0 + r;
+        if (i >= total || (i != 0 && k[r + 1] == k[r])) continue;
+        if (i + 1 < total && k[r + 2] == k[r + 1]) *longer |= 1u << r;
+        else *single |= 1u << r;
     }
-    (void)block_prefix(c, &all);
-    if (threadIdx.x == 0) tile_cnt[blockIdx.x] = all;
+}
+__device__ __forceinline__ void load_keys(const unsigned long long *__restrict__ key, uint64_t i0, uint64_t total,
+                                          unsigned long long (&k)[kPer + 2]) {
+    k[0] = i0 > 0 && i0 <= total ? key[i0 - 1] : 0ull;
+#pragma unroll
+    for (uint32_t r = 0; r <= kPer; ++r) k[r + 1] = i0 + r < total ? key[i0 + r] : 0ull;
 }
 
-// Distinct pair k (at run head i): its key and its run's start.
-__global__ __launch_bounds__(kBlock) void k_head_write(uint64_t total, const unsigned long long *__restrict__ key,
-                                                        const uint64_t *__restrict__ tile_off,
-                                                        unsigned long long *__restrict__ ukey,
+// 3. Runs per tile: of one key, and longer ones (two halves of tile_cnt).
+__global__ __launch_bounds__(kBlock) void k_head_count(uint64_t total, uint32_t tiles,
+                                                        const unsigned long long *__restrict__ key,
+                                                        uint32_t *__restrict__ tile_cnt) {
+    const uint64_t i0 = (uint64_t)blockIdx.x * kTile + threadIdx.x * kPer;
+    unsigned long long k[kPer + 2];
+    uint32_t single, longer, all;
+    load_keys(key, i0, total, k);
+    run_heads(k, i0, total, &single, &longer);
+    (void)block_prefix((uint32_t)__popc(single) | ((uint32_t)__popc(longer) << 16), &all);   // at most kTile each
+    if (threadIdx.x == 0) {
+        tile_cnt[blockIdx.x] = all & 0xFFFFu;
+        tile_cnt[tiles + blockIdx.x] = all >> 16;
+    }
+}
+
+// Per vertex: runs of one key up to its end, longer runs before it and up to its end.
+struct VertexRuns {
+    uint32_t *s_end, *l_beg, *l_end;
+};
+
+// The longer runs' starts, in order, and each vertex's counts (written where
+// the vertex of the keys changes).
+__global__ __launch_bounds__(kBlock) void k_head_write(uint64_t total, uint32_t tiles, uint32_t b,
+                                                        const unsigned long long *__restrict__ key,
+                                                        const uint64_t *__restrict__ tile_off, VertexRuns vr,
                                                         uint32_t *__restrict__ run_start) {
     const uint64_t i0 = (uint64_t)blockIdx.x * kTile + threadIdx.x * kPer;
-    unsigned long long k[kPer + 1];
-    k[0] = i0 > 0 && i0 <= total ? key[i0 - 1] : 0ull;
-    uint32_t heads = 0, all;
+    unsigned long long k[kPer + 2];
+    uint32_t single, longer, all;
+    load_keys(key, i0, total, k);
+    run_heads(k, i0, total, &single, &longer);
+    const uint32_t pre = block_prefix((uint32_t)__popc(single) | ((uint32_t)__popc(longer) << 16), &all);
+    // offsets are prefixes over both halves: the second half's begin at all singles
+    uint32_t s = (uint32_t)tile_off[blockIdx.x] + (pre & 0xFFFFu);
+    uint32_t l = (uint32_t)(tile_off[tiles + blockIdx.x] - tile_off[tiles]) + (pre >> 16);
 #pragma unroll
     for (uint32_t r = 0; r < kPer; ++r) {
-        k[r + 1] = i0 + r < total ? key[i0 + r] : k[r];
-        if (i0 + r < total && (i0 + r == 0 || k[r + 1] != k[r])) heads |= 1u << r;
+        const uint64_t i = i0 + r;
+        if (i >= total) break;
+        const uint32_t v = (uint32_t)(k[r + 1] >> b);
+        if (i == 0 || (uint32_t)(k[r] >> b) != v) vr.l_beg[v] = l;
+        s += (single >> r) & 1u;
+        if ((longer >> r) & 1u) run_start[l++] = (uint32_t)i;
+        if (i + 1 == total || (uint32_t)(k[r + 2] >> b) != v) {
+            vr.s_end[v] = s;
+            vr.l_end[v] = l;
+        }
     }
-    uint64_t at = block_prefix((uint32_t)__popc(heads), &all);
-    at += tile_off[blockIdx.x];
+}
+
+// The runs of one key: the last of their vertex's co-members, in order.
+__global__ __launch_bounds__(kBlock) void k_last_write(uint64_t total, uint32_t b,
+                                                        const unsigned long long *__restrict__ key,
+                                                        const uint64_t *__restrict__ tile_off, VertexRuns vr,
+                                                        const unsigned long long *__restrict__ nb_off,
+                                                        uint32_t *__restrict__ nb) {
+    const uint64_t i0 = (uint64_t)blockIdx.x * kTile + threadIdx.x * kPer;
+    unsigned long long k[kPer + 2];
+    uint32_t single, longer, all;
+    load_keys(key, i0, total, k);
+    run_heads(k, i0, total, &single, &longer);
+    uint32_t s = (uint32_t)tile_off[blockIdx.x] + block_prefix((uint32_t)__popc(single), &all);
+    const unsigned long long umask = (1ull << b) - 1ull;
 #pragma unroll
     for (uint32_t r = 0; r < kPer; ++r)
-        if ((heads >> r) & 1u) {
-            ukey[at] = k[r + 1];
-            run_start[at] = (uint32_t)(i0 + r);
-            ++at;
+        if ((single >> r) & 1u) {
+            const uint32_t v = (uint32_t)(k[r + 1] >> b);
+            nb[nb_off[v + 1] - (vr.s_end[v] - s)] = (uint32_t)(k[r + 1] & umask);
+            ++s;
         }
 }
 
-// Layer sort key of distinct pair k: v << 32 | ~w (ascending keys: v, then
-// descending w); the value is u.
-__global__ void k_wkeys(uint64_t uniq, uint64_t total, uint32_t b, const unsigned long long *__restrict__ ukey,
-                        const uint32_t *__restrict__ run_start, unsigned long long *__restrict__ key2,
-                        uint32_t *__restrict__ val) {
-    const unsigned long long umask = (1ull << b) - 1ull;
-    for (uint64_t k = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; k < uniq; k += (uint64_t)gridDim.x * blockDim.x) {
-        const uint32_t end = k + 1 < uniq ? run_start[k + 1] : (uint32_t)total;
-        const uint32_t w = end - run_start[k];
-        const unsigned long long v = ukey[k] >> b;
-        key2[k] = (v << 32) | (unsigned long long)(~w);
-        val[k] = (uint32_t)(ukey[k] & umask);
+// 4. Sort keys of the longer runs: v << wb | (2^wb - 1 - w), ascending v and
+// descending w (w < 2^wb); the value is u.  A run's end is found by doubling
+// steps from its start, then halving them: most are two or three keys long.
+__global__ __launch_bounds__(kBlock) void k_wkeys(uint64_t runs, uint64_t total, uint32_t b, uint32_t wb,
+                                                   const unsigned long long *__restrict__ key,
+                                                   const uint32_t *__restrict__ run_start,
+                                                   unsigned long long *__restrict__ key2, uint32_t *__restrict__ val) {
+    const unsigned long long umask = (1ull << b) - 1ull, wmask = (1ull << wb) - 1ull;
+    for (uint64_t k = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; k < runs; k += (uint64_t)gridDim.x * blockDim.x) {
+        const uint64_t i = run_start[k];
+        const unsigned long long me = key[i];
+        uint64_t w = 2, step = 1;   // key[i .. i + w) is in the run
+        while (i + w + step - 1 < total && key[i + w + step - 1] == me) {
+            w += step;
+            step *= 2;
+        }
+        for (; step; step /= 2)
+            if (i + w + step - 1 < total && key[i + w + step - 1] == me) w += step;
+        key2[k] = ((me >> b) << wb) | (wmask - w);
+        val[k] = (uint32_t)(me & umask);
     }
 }
 
-// 5. Layer ends: entry k ends a layer when the next key differs (another
-// weight or another vertex) or k is the last entry.  Counted per tile, then
-// written.
-__global__ __launch_bounds__(kBlock) void k_end_count(uint64_t uniq, const unsigned long long *__restrict__ key2,
+// The sorted longer runs' co-members: the first of their vertex.
+__global__ __launch_bounds__(kBlock) void k_first_write(uint64_t runs, uint32_t wb,
+                                                         const unsigned long long *__restrict__ key2,
+                                                         const uint32_t *__restrict__ val, VertexRuns vr,
+                                                         const unsigned long long *__restrict__ nb_off,
+                                                         uint32_t *__restrict__ nb) {
+    for (uint64_t k = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; k < runs; k += (uint64_t)gridDim.x * blockDim.x) {
+        const uint32_t v = (uint32_t)(key2[k] >> wb);
+        nb[nb_off[v] + (k - vr.l_beg[v])] = val[k];
+    }
+}
+
+// Vertices with a layer of runs of one key (w = 1): 1 each, and its end.
+__global__ __launch_bounds__(kBlock) void k_last_layer(uint32_t n, const uint32_t *__restrict__ deg,
+                                                        const uint32_t *__restrict__ l, VertexRuns vr,
+                                                        const unsigned long long *__restrict__ ly_off,
+                                                        uint32_t *__restrict__ has, uint32_t *__restrict__ ly_end) {
+    const uint32_t v = blockIdx.x * kBlock + threadIdx.x;
+    if (v >= n) return;
+    const uint32_t d = deg[v];
+    const bool last = d != 0u && vr.l_end[v] - vr.l_beg[v] != d;
+    has[v] = last ? 1u : 0u;
+    if (last) ly_end[ly_off[v] + l[v] - 1u] = d;
+}
+
+// 5. The other layers' ends: sorted run k ends a layer when the next key
+// differs (another weight or another vertex) or k is the last one.  Counted per
+// tile, then written, after the layers of w = 1 of the vertices before (last_off).
+__global__ __launch_bounds__(kBlock) void k_end_count(uint64_t runs, const unsigned long long *__restrict__ key2,
                                                        uint32_t *__restrict__ tile_cnt) {
     const uint64_t k0 = (uint64_t)blockIdx.x * kTile;
     uint32_t c = 0, all;
     for (uint32_t r = 0; r < kPer; ++r) {
         const uint64_t k = k0 + r * kBlock + threadIdx.x;
-        c += k < uniq && (k + 1 == uniq || key2[k + 1] != key2[k]) ? 1u : 0u;
+        c += k < runs && (k + 1 == runs || key2[k + 1] != key2[k]) ? 1u : 0u;
     }
     (void)block_prefix(c, &all);
     if (threadIdx.x == 0) tile_cnt[blockIdx.x] = all;
 }
 
-__global__ __launch_bounds__(kBlock) void k_end_write(uint64_t uniq, const unsigned long long *__restrict__ key2,
-                                                       const uint64_t *__restrict__ tile_off,
-                                                       const unsigned long long *__restrict__ nb_off,
+__global__ __launch_bounds__(kBlock) void k_end_write(uint64_t runs, uint32_t wb,
+                                                       const unsigned long long *__restrict__ key2,
+                                                       const uint64_t *__restrict__ tile_off, VertexRuns vr,
+                                                       const uint64_t *__restrict__ last_off,
                                                        uint32_t *__restrict__ ly_end) {
     const uint64_t k0 = (uint64_t)blockIdx.x * kTile + threadIdx.x * kPer;
     unsigned long long k[kPer + 1];
     uint32_t ends = 0, all;
 #pragma unroll
-    for (uint32_t r = 0; r <= kPer; ++r) k[r] = k0 + r < uniq ? key2[k0 + r] : ~0ull;
+    for (uint32_t r = 0; r <= kPer; ++r) k[r] = k0 + r < runs ? key2[k0 + r] : ~0ull;
 #pragma unroll
     for (uint32_t r = 0; r < kPer; ++r)
-        if (k0 + r < uniq && (k0 + r + 1 == uniq || k[r + 1] != k[r])) ends |= 1u << r;
+        if (k0 + r < runs && (k0 + r + 1 == runs || k[r + 1] != k[r])) ends |= 1u << r;
     uint64_t at = block_prefix((uint32_t)__popc(ends), &all);
     at += tile_off[blockIdx.x];
 #pragma unroll
     for (uint32_t r = 0; r < kPer; ++r)
-        if ((ends >> r) & 1u) ly_end[at++] = (uint32_t)(k0 + r + 1 - nb_off[(uint32_t)(k[r] >> 32)]);
+        if ((ends >> r) & 1u) {
+            const uint32_t v = (uint32_t)(k[r] >> wb);
+            ly_end[last_off[v] + at++] = (uint32_t)(k0 + r + 1) - vr.l_beg[v];
+        }
 }
 
 constexpr size_t kKeepBytes = 8ull << 30;   // scratch kept between calls
@@ -206,49 +327,47 @@ int layers_build_device(hyperim_graph g, PrepWorkspace &w, uint32_t lmax, hipStr
         }
     } scratch{w, s};
     const uint32_t b = n > 1 ? 32u - (uint32_t)__builtin_clz(n - 1u) : 1u;   // bits of a vertex id
+    const uint32_t wb = 32u - (uint32_t)__builtin_clz(std::max(g->m, 1u));         // bits of a weight (at most m)
     const uint64_t total1 = std::max<uint64_t>(total, 1), uniq1 = std::max<uint64_t>(uniq, 1);
+    const uint64_t runs1 = std::max<uint64_t>(std::min(uniq, total / 2), 1);       // longer runs, at most
     HIM_CHECK(w.occ.reserve(sizeof(uint64_t) * total1, s));
     HIM_CHECK(w.occ2.reserve(sizeof(uint64_t) * total1, s));
-    HIM_CHECK(w.run_start.reserve(sizeof(uint32_t) * uniq1, s));
-    HIM_CHECK(w.pair_val.reserve(2 * sizeof(uint32_t) * uniq1, s));
+    HIM_CHECK(w.run_start.reserve(sizeof(uint32_t) * runs1, s));
+    HIM_CHECK(w.pair_val.reserve(2 * sizeof(uint32_t) * runs1, s));
+    HIM_CHECK(w.vals.reserve(4 * sizeof(uint32_t) * (size_t)n, s));
+    HIM_CHECK(w.base.reserve(sizeof(uint64_t) * ((size_t)n + 1), s));
     const uint32_t tiles = (uint32_t)std::max<uint64_t>(div_up(total, kTile), 1);
-    HIM_CHECK(w.k1.reserve(sizeof(uint32_t) * tiles, s));
-    HIM_CHECK(w.k2.reserve(sizeof(uint64_t) * ((size_t)tiles + 1), s));
+    HIM_CHECK(w.k1.reserve(2 * sizeof(uint32_t) * (size_t)tiles, s));
+    HIM_CHECK(w.k2.reserve(sizeof(uint64_t) * (2 * (size_t)tiles + 1), s));
     uint32_t *tile_cnt = w.k1.as<uint32_t>();
     uint64_t *tile_off = w.k2.as<uint64_t>();
+    uint32_t *per_v = w.vals.as<uint32_t>(), *has_last = per_v + 3 * (size_t)n;
+    const VertexRuns vr{per_v, per_v + n, per_v + 2 * (size_t)n};
     using Key = unsigned long long;
     // 1., 2. all occurrences by (v, u)
     rocprim::double_buffer<Key> keys(w.occ.as<Key>(), w.occ2.as<Key>());
+    uint64_t found[2] = {0, 0};   // runs of one key; all runs
     if (total) {
-        hipLaunchKernelGGL(k_occ_emit, dim3(grid_for(nnz)), dim3(kBlock), 0, s, n, nnz, b, g->v_off.as<uint32_t>(),
-                           g->v_he.as<uint32_t>(), g->he_off.as<uint32_t>(), g->he_mem.as<uint32_t>(),
-                           g->chan.as<Key>(), keys.current());
+        hipLaunchKernelGGL(k_occ_emit, dim3(grid_for(nnz, 2048)), dim3(kBlock), 0, s, n, nnz, b,
+                           g->v_off.as<uint32_t>(), g->irec.as<uint4>(), g->he_mem.as<uint32_t>(), g->chan.as<Key>(),
+                           keys.current());
         HIM_HIP(hipGetLastError());
         size_t tbytes = 0;
-        HIM_HIP(rocprim::radix_sort_keys(nullptr, tbytes, keys, (size_t)total, 0u, 2u * b, s));
+        HIM_HIP(rocprim::radix_sort_keys(nullptr, tbytes, keys, (size_t)total, b, 2u * b, s));
         HIM_CHECK(w.sort_tmp.reserve(std::max<size_t>(tbytes, 1), s));
-        HIM_HIP(rocprim::radix_sort_keys(w.sort_tmp.ptr, tbytes, keys, (size_t)total, 0u, 2u * b, s));
-    }
-    // 3. distinct pairs and their weights, into the other key buffer
-    uint64_t uniq_dev = 0;
-    if (total) {
-        hipLaunchKernelGGL(k_head_count, dim3(tiles), dim3(kBlock), 0, s, total, keys.current(), tile_cnt);
-        HIM_CHECK(scan_u32_to_u64(tile_cnt, tile_off, tiles, 0, w.tmp, s));
-        HIM_HIP(hipMemcpyAsync(&uniq_dev, tile_off + tiles, sizeof(uint64_t), hipMemcpyDeviceToHost, s));
+        HIM_HIP(rocprim::radix_sort_keys(w.sort_tmp.ptr, tbytes, keys, (size_t)total, b, 2u * b, s));
+        // 3. runs
+        hipLaunchKernelGGL(k_head_count, dim3(tiles), dim3(kBlock), 0, s, total, tiles, keys.current(), tile_cnt);
+        HIM_CHECK(scan_u32_to_u64(tile_cnt, tile_off, 2 * (uint64_t)tiles, 0, w.tmp, s));
+        HIM_HIP(hipMemcpyAsync(found, tile_off + tiles, sizeof(uint64_t), hipMemcpyDeviceToHost, s));
+        HIM_HIP(hipMemcpyAsync(found + 1, tile_off + 2 * (size_t)tiles, sizeof(uint64_t), hipMemcpyDeviceToHost, s));
         HIM_HIP(hipStreamSynchronize(s));
     }
-    if (uniq_dev != uniq) {
+    if (found[1] != uniq) {
         set_error_detail("stratified-setting tables: distinct co-members disagree with deg");
         return HYPERIM_EHIP;
     }
-    Key *ukey = keys.alternate(), *key2 = keys.current();   // the sorted occurrences are spent after k_head_write
-    uint32_t *val = w.pair_val.as<uint32_t>(), *val2 = val + uniq1;
-    if (total) {
-        hipLaunchKernelGGL(k_head_write, dim3(tiles), dim3(kBlock), 0, s, total, keys.current(), tile_off, ukey,
-                           w.run_start.as<uint32_t>());
-        hipLaunchKernelGGL(k_wkeys, dim3(grid_for(uniq)), dim3(kBlock), 0, s, uniq, total, b, ukey,
-                           w.run_start.as<uint32_t>(), key2, val);
-    }
+    const uint64_t runs = found[1] - found[0];
     // per-vertex ranges of the distinct co-members (deg prefix) and of the
     // layers (l prefix)
     HIM_CHECK(g->lay_nb.reserve(sizeof(uint32_t) * uniq1, s));
@@ -257,21 +376,38 @@ int layers_build_device(hyperim_graph g, PrepWorkspace &w, uint32_t lmax, hipStr
     HIM_CHECK(scan_u32_to_u64(g->deg.as<uint32_t>(), g->lay_nb_off.as<uint64_t>(), n, 0, w.tmp, s));
     HIM_CHECK(scan_u32_to_u64(g->l.as<uint32_t>(), g->lay_ly_off.as<uint64_t>(), n, 0, w.tmp, s));
     HIM_CHECK(g->lay_ly_end.reserve(sizeof(uint32_t) * std::max<uint64_t>(nlay, 1), s));
-    if (uniq) {
-        // 4. layers: stable sort of the distinct pairs by v << 32 | ~w, values u
-        rocprim::double_buffer<Key> wkeys(key2, ukey);
-        rocprim::double_buffer<uint32_t> vals(val, val2);
-        size_t tbytes = 0;
-        HIM_HIP(rocprim::radix_sort_pairs(nullptr, tbytes, wkeys, vals, (size_t)uniq, 0u, 32u + b, s));
-        HIM_CHECK(w.sort_tmp.reserve(std::max<size_t>(tbytes, 1), s));
-        HIM_HIP(rocprim::radix_sort_pairs(w.sort_tmp.ptr, tbytes, wkeys, vals, (size_t)uniq, 0u, 32u + b, s));
-        HIM_HIP(hipMemcpyAsync(g->lay_nb.ptr, vals.current(), sizeof(uint32_t) * uniq, hipMemcpyDeviceToDevice, s));
-        // 5. layer ends
-        const uint32_t utiles = (uint32_t)div_up(uniq, kTile);
-        hipLaunchKernelGGL(k_end_count, dim3(utiles), dim3(kBlock), 0, s, uniq, wkeys.current(), tile_cnt);
-        HIM_CHECK(scan_u32_to_u64(tile_cnt, tile_off, utiles, 0, w.tmp, s));
-        hipLaunchKernelGGL(k_end_write, dim3(utiles), dim3(kBlock), 0, s, uniq, wkeys.current(), tile_off,
-                           g->lay_nb_off.as<Key>(), g->lay_ly_end.as<uint32_t>());
+    if (total) {
+        const Key *nb_off = g->lay_nb_off.as<Key>();
+        uint32_t *nb = g->lay_nb.as<uint32_t>();
+        hipLaunchKernelGGL(k_head_write, dim3(tiles), dim3(kBlock), 0, s, total, tiles, b, keys.current(), tile_off,
+                           vr, w.run_start.as<uint32_t>());
+        hipLaunchKernelGGL(k_last_write, dim3(tiles), dim3(kBlock), 0, s, total, b, keys.current(), tile_off, vr,
+                           nb_off, nb);
+        hipLaunchKernelGGL(k_last_layer, dim3((uint32_t)div_up(n, kBlock)), dim3(kBlock), 0, s, n,
+                           g->deg.as<uint32_t>(), g->l.as<uint32_t>(), vr, g->lay_ly_off.as<Key>(), has_last,
+                           g->lay_ly_end.as<uint32_t>());
+        HIM_CHECK(scan_u32_to_u64(has_last, w.base.as<uint64_t>(), n, 0, w.tmp, s));
+        if (runs) {
+            // 4. the longer runs by v and descending w, in the spent key buffer's
+            // halves (at most total / 2 runs); values u
+            uint32_t *val = w.pair_val.as<uint32_t>();
+            hipLaunchKernelGGL(k_wkeys, dim3(grid_for(runs)), dim3(kBlock), 0, s, runs, total, b, wb, keys.current(),
+                               w.run_start.as<uint32_t>(), keys.alternate(), val);
+            rocprim::double_buffer<Key> wkeys(keys.alternate(), keys.alternate() + total / 2);
+            rocprim::double_buffer<uint32_t> vals(val, val + runs1);
+            size_t tbytes = 0;
+            HIM_HIP(rocprim::radix_sort_pairs(nullptr, tbytes, wkeys, vals, (size_t)runs, 0u, wb + b, s));
+            HIM_CHECK(w.sort_tmp.reserve(std::max<size_t>(tbytes, 1), s));
+            HIM_HIP(rocprim::radix_sort_pairs(w.sort_tmp.ptr, tbytes, wkeys, vals, (size_t)runs, 0u, wb + b, s));
+            hipLaunchKernelGGL(k_first_write, dim3(grid_for(runs)), dim3(kBlock), 0, s, runs, wb, wkeys.current(),
+                               vals.current(), vr, nb_off, nb);
+            // 5. their layers' ends
+            const uint32_t rtiles = (uint32_t)div_up(runs, kTile);
+            hipLaunchKernelGGL(k_end_count, dim3(rtiles), dim3(kBlock), 0, s, runs, wkeys.current(), tile_cnt);
+            HIM_CHECK(scan_u32_to_u64(tile_cnt, tile_off, rtiles, 0, w.tmp, s));
+            hipLaunchKernelGGL(k_end_write, dim3(rtiles), dim3(kBlock), 0, s, runs, wb, wkeys.current(), tile_off, vr,
+                               w.base.as<uint64_t>(), g->lay_ly_end.as<uint32_t>());
+        }
     }
     HIM_HIP(hipGetLastError());
     // host tables: ln(l + 1) for l <= lmax, and e^-P(L_i) with
