@@ -80,13 +80,38 @@ constexpr uint64_t kSlotBudget = 48ull << 30; // bytes of slot lists + bitmaps
 // counter s & 1 while its k_expand clears the other one for superstep s + 1.
 // kPlanned counts the frontier entries k_plan has taken (summed queue heads),
 // the progress measure of the host loop.
+// Counters that waves add to while others are added to lie 128 bytes apart:
+// additions to one line are done one after another, about 7.5 ns each.
+constexpr uint32_t kCtrLine = 16;
+enum Ctr {
+    kWork = 0,
+    kBump = kCtrLine,
+    kBigCount = 2 * kCtrLine,
+    kFreeNext = 3 * kCtrLine,
+    kDefCount = 4 * kCtrLine,
+    kItems = 5 * kCtrLine,
+    kItemsOther,
+    kPlanned = 6 * kCtrLine,
+    kNumCtr = 7 * kCtrLine
+};
+// Sums that every wave adds to once per launch, in kStatLines copies behind the
+// counters, added up on the host.  (6144 waves with two sums each on the
+// counters' own line: 0.09 ms of every superstep.)
 // kPhiloxA and kPhilox count the Philox4x32-10 blocks k_rr_light and k_expand
 // drew (lane blocks whose coins were needed); kBytesMs and kPhiloxMs are
 // bundled mode's algorithmic bytes and blocks.
-enum Ctr {
-    kWork = 0, kBump, kBigCount, kFreeNext, kDefCount, kItems, kItemsOther, kBytesA, kBytesB, kPlanned, kPhilox,
-    kBytesMs, kPhiloxMs, kPhiloxA, kNumCtr
-};
+enum Stat { kBytesA = 0, kBytesB, kPhilox, kPhiloxA, kBytesMs, kPhiloxMs };
+constexpr uint32_t kStatLines = 64;
+constexpr uint32_t kCtrWords = kNumCtr + kStatLines * kCtrLine;
+
+__device__ __forceinline__ void stat_add(unsigned long long *ctr, Stat which, uint64_t x) {
+    if (x) atomicAdd(&ctr[kNumCtr + (blockIdx.x % kStatLines) * kCtrLine + which], (unsigned long long)x);
+}
+uint64_t stat_sum(const unsigned long long *ctr, Stat which) {
+    uint64_t x = 0;
+    for (uint32_t l = 0; l < kStatLines; ++l) x += ctr[kNumCtr + l * kCtrLine + which];
+    return x;
+}
 
 // One graph of a launch group.
 // vrec[v] = (first incidence, incidences, threshold, Philox blocks) and irec[e]
@@ -151,6 +176,8 @@ struct RRArgs {
     uint32_t ntasks, qlog;
     uint32_t heavy, budget, chunk, seg, prefilter_min;   // execution parameters
     uint32_t slot_n, slot_words;     // slot list length and bitmap words (largest graph)
+    uint32_t take, stage_step;       // launch indices and stage entries a wave reserves at a time
+    uint32_t free0;                  // first slot no wave owns
     uint64_t count;                  // launch indices [0, count)
     uint64_t out_base;               // per-id array index of launch index 0
     unsigned long long *ctr;         // Ctr block
@@ -757,6 +784,41 @@ __device__ __forceinline__ uint64_t expand(const GraphView &G, Lds &L, uint64_t 
     return wave_sum(bytes);
 }
 
+// A wave's launch indices: kWork hands out a.take at a time, after the first
+// ones, which go by wave number.
+struct WorkShare {
+    uint64_t at = ~0ull, end = 0;
+    __device__ __forceinline__ uint64_t next(const RRArgs &a) {
+        if (at == ~0ull) {
+            at = ((uint64_t)blockIdx.x * kWavesPerWG + uni(threadIdx.x / kWave)) * a.take;
+            end = at + a.take;
+        } else if (at == end) {
+            unsigned long long got = 0;
+            if (lane_id() == 0) got = atomicAdd(&a.ctr[kWork], (unsigned long long)a.take);
+            at = (uint64_t)gridDim.x * kWavesPerWG * a.take + uni64(wave_bcast64(got, 0));
+            end = at + a.take;
+        }
+        return at++;
+    }
+};
+
+// A wave's room in the stage, a.stage_step entries or a set at a time.
+struct StageRoom {
+    uint64_t at = 0, end = 0;
+    __device__ __forceinline__ uint64_t take(const RRArgs &a, uint32_t size) {
+        if (end - at < size) {
+            const uint32_t step = max(size, a.stage_step);
+            unsigned long long got = 0;
+            if (lane_id() == 0) got = atomicAdd(&a.ctr[kBump], (unsigned long long)step);
+            at = uni64(wave_bcast64(got, 0));
+            end = at + step;
+        }
+        const uint64_t off = at;
+        at += size;
+        return off;
+    }
+};
+
 // Record a finished set's per-id outputs.
 __device__ __forceinline__ void record_set(const RRArgs &a, uint64_t idx, uint64_t off, uint32_t size, uint32_t root) {
     const uint64_t o = a.out_base + idx;
@@ -810,11 +872,10 @@ __global__ __launch_bounds__(kWG) void k_rr_light(RRArgs a) {
     wave_sync();
     bool can_defer = true;
     uint64_t bytes_done = 0, px = 0;
-
+    WorkShare work;
+    StageRoom room;
     for (;;) {
-        unsigned long long idx = 0;
-        if (lane == 0) idx = atomicAdd(&a.ctr[kWork], 1ull);
-        idx = uni64(wave_bcast64(idx, 0));
+        const uint64_t idx = work.next(a);
         if (idx >= a.count) break;
         const uint32_t task = task_of(a, idx);
         const SetRef S = set_ref(a, task, idx);
@@ -848,7 +909,7 @@ __global__ __launch_bounds__(kWG) void k_rr_light(RRArgs a) {
                 // hand the set over to phase B and continue with a fresh slot
                 uint32_t fresh_slot = 0;
                 if (lane == 0) fresh_slot = (uint32_t)atomicAdd(&a.ctr[kFreeNext], 1ull);
-                fresh_slot = wave_bcast(fresh_slot, 0);
+                fresh_slot = wave_bcast(fresh_slot, 0) + a.free0;
                 if (fresh_slot < a.slot_total) {
                     if (lane == 0) {
                         const uint32_t dd = (uint32_t)atomicAdd(&a.ctr[kDefCount], 1ull);
@@ -891,9 +952,7 @@ __global__ __launch_bounds__(kWG) void k_rr_light(RRArgs a) {
         const uint32_t size = app.size;
 
         // ---- output: ascending members into the stage --------------------
-        unsigned long long off = 0;
-        if (lane == 0) off = atomicAdd(&a.ctr[kBump], (unsigned long long)size);
-        off = wave_bcast64(off, 0);
+        const uint64_t off = room.take(a, size);
         wave_sync();
         if (off + size <= a.stage_cap) {
             if (size <= kSortMax) {
@@ -946,9 +1005,9 @@ __global__ __launch_bounds__(kWG) void k_rr_light(RRArgs a) {
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
         wave_sync();
     }
-    if (lane == 0 && bytes_done) atomicAdd(&a.ctr[kBytesA], bytes_done);
+    if (lane == 0) stat_add(a.ctr, kBytesA, bytes_done);
     px = wave_sum(px);
-    if (lane == 0 && px) atomicAdd(&a.ctr[kPhiloxA], (unsigned long long)px);
+    if (lane == 0) stat_add(a.ctr, kPhiloxA, px);
 }
 
 // ---- linear-threshold model ------------------------------------------------
@@ -989,10 +1048,10 @@ __global__ __launch_bounds__(kWG) void k_lt_walk(RRArgs a) {
     }
     wave_sync();
     uint64_t bytes_done = 0, px = 0;
+    WorkShare work;
+    StageRoom room;
     for (;;) {
-        unsigned long long idx = 0;
-        if (lane == 0) idx = atomicAdd(&a.ctr[kWork], 1ull);
-        idx = uni64(wave_bcast64(idx, 0));
+        const uint64_t idx = work.next(a);
         if (idx >= a.count) break;
         const uint32_t task = task_of(a, idx);
         const SetRef S = set_ref(a, task, idx);
@@ -1063,9 +1122,7 @@ __global__ __launch_bounds__(kWG) void k_lt_walk(RRArgs a) {
         }
 
         // ---- output: ascending members into the stage, as in phase A -----
-        unsigned long long off = 0;
-        if (lane == 0) off = atomicAdd(&a.ctr[kBump], (unsigned long long)size);
-        off = wave_bcast64(off, 0);
+        const uint64_t off = room.take(a, size);
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");   // lane 0's list and bitmap stores
         if (off + size <= a.stage_cap) {
             if (size <= kSortMax) {
@@ -1113,8 +1170,8 @@ __global__ __launch_bounds__(kWG) void k_lt_walk(RRArgs a) {
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
         wave_sync();
     }
-    if (lane == 0 && bytes_done) atomicAdd(&a.ctr[kBytesA], bytes_done);
-    if (lane == 0 && px) atomicAdd(&a.ctr[kPhiloxA], (unsigned long long)px);
+    if (lane == 0) stat_add(a.ctr, kBytesA, bytes_done);
+    if (lane == 0) stat_add(a.ctr, kPhiloxA, px);
 }
 
 // ---- stratified setting -------------------------------------------------------
@@ -1202,10 +1259,10 @@ __global__ __launch_bounds__(kWG) void k_layered(RRArgs a, uint32_t *__restrict_
     }
     wave_sync();
     uint64_t bytes_done = 0, px = 0;
+    WorkShare work;
+    StageRoom room;
     for (;;) {
-        unsigned long long idx = 0;
-        if (lane == 0) idx = atomicAdd(&a.ctr[kWork], 1ull);
-        idx = uni64(wave_bcast64(idx, 0));
+        const uint64_t idx = work.next(a);
         if (idx >= a.count) break;
         const uint32_t task = task_of(a, idx);
         const SetRef S = set_ref(a, task, idx);
@@ -1314,9 +1371,7 @@ __global__ __launch_bounds__(kWG) void k_layered(RRArgs a, uint32_t *__restrict_
         }
 
         // ---- output: ascending members into the stage, as in phase A -----
-        unsigned long long off = 0;
-        if (lane == 0) off = atomicAdd(&a.ctr[kBump], (unsigned long long)size);
-        off = wave_bcast64(off, 0);
+        const uint64_t off = room.take(a, size);
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
         if (off + size <= a.stage_cap) {
             if (size <= kSortMax) {
@@ -1366,8 +1421,8 @@ __global__ __launch_bounds__(kWG) void k_layered(RRArgs a, uint32_t *__restrict_
     }
     bytes_done = wave_sum(bytes_done);
     px = wave_sum(px);
-    if (lane == 0 && bytes_done) atomicAdd(&a.ctr[kBytesA], bytes_done);
-    if (lane == 0 && px) atomicAdd(&a.ctr[kPhiloxA], (unsigned long long)px);
+    if (lane == 0) stat_add(a.ctr, kBytesA, bytes_done);
+    if (lane == 0) stat_add(a.ctr, kPhiloxA, px);
 }
 
 // ---- phase B ---------------------------------------------------------------
@@ -1598,9 +1653,9 @@ __global__ __launch_bounds__(kWG) void k_expand(const RRArgs *__restrict__ ap, u
                                                        0u, 1u);
         }
     }
-    if (lane == 0 && bytes_done) atomicAdd(&a.ctr[kBytesB], bytes_done);
+    if (lane == 0) stat_add(a.ctr, kBytesB, bytes_done);
     px = wave_sum(px);
-    if (lane == 0 && px) atomicAdd(&a.ctr[kPhilox], (unsigned long long)px);
+    if (lane == 0) stat_add(a.ctr, kPhilox, px);
 }
 
 // One workgroup per deferred set: ascending members into the stage, per-id
@@ -1693,7 +1748,16 @@ constexpr uint32_t kMsOutVerts = 4096;   // vertices per output block (16 per th
 // kMsFetch: next work item of the running expansion (waves fetch items one at
 // a time; item costs vary with hyperedge sizes).
 enum MsCtr {
-    kMsCur = 0, kMsNext, kMsItems, kMsPending, kMsLevelDone, kMsDone, kMsEpoch, kMsOverflow, kMsFetch, kMsNumCtr
+    kMsCur = 0,   // the ones that waves add to: a line each
+    kMsNext = kCtrLine,
+    kMsItems = 2 * kCtrLine,
+    kMsPending = 3 * kCtrLine,
+    kMsFetch = 4 * kCtrLine,
+    kMsLevelDone = 5 * kCtrLine,
+    kMsDone,
+    kMsEpoch,
+    kMsOverflow,
+    kMsNumCtr = 6 * kCtrLine
 };
 
 struct MsArgs {
@@ -1712,8 +1776,7 @@ struct MsArgs {
     uint32_t *batch_epoch;              // per 64 frontier entries: level in which they were planned
     uint64_t list_cap;                  // entries of each list
     unsigned long long *ctr;            // MsCtr
-    unsigned long long *bytes;          // algorithmic bytes (RR counter block)
-    unsigned long long *philox;         // Philox blocks drawn (RR counter block)
+    unsigned long long *stats;          // the RR counter block: algorithmic bytes, Philox blocks drawn
     uint4 *items;
     uint32_t *vcnt;                     // output: per (bundle, vertex block, set) counts
     uint32_t nvb;                       // vertex blocks per bundle
@@ -1971,7 +2034,7 @@ __global__ __launch_bounds__(kWG) void k_ms_plan(MsArgs m) {
     }
     if (lane == 0 && planned) atomicSub(&m.ctr[kMsPending], planned);
     bytes = wave_sum(bytes);
-    if (lane == 0 && bytes) atomicAdd(m.bytes, bytes);
+    if (lane == 0) stat_add(m.stats, kBytesMs, bytes);
 }
 
 // Marks the wave's buffered live channels in nxt, those that lead to a member
@@ -2304,7 +2367,7 @@ __global__ __launch_bounds__(kWG) void k_ms_expand(MsArgs m) {
     ms_resolve(m, G, L, npend, nlive);
     ms_flush(m, L, nlive);
     px = wave_sum(px);
-    if (lane == 0 && px) atomicAdd(m.philox, (unsigned long long)px);
+    if (lane == 0) stat_add(m.stats, kPhiloxMs, px);
 }
 
 // Output, pass 1: per (bundle, block of kMsOutVerts vertices) member counts
@@ -2562,7 +2625,7 @@ int ensure_workspace(RRWorkspace &ws, uint32_t n_max, hipStream_t s, LaunchShape
         HIM_CHECK(ws.lists.reserve(sizeof(uint32_t) * (size_t)slots * ws.slot_n, s));
         HIM_CHECK(ws.bitmaps.reserve(sizeof(uint32_t) * (size_t)slots * words, s));
         HIM_HIP(hipMemsetAsync(ws.bitmaps.ptr, 0, sizeof(uint32_t) * (size_t)slots * words, s));
-        HIM_CHECK(ws.counters.reserve(sizeof(unsigned long long) * kNumCtr, s));
+        HIM_CHECK(ws.counters.reserve(sizeof(unsigned long long) * kCtrWords, s));
         // deferred-set arrays for as many sets as there are slots (phase A may
         // run fewer waves than the occupancy allows, leaving more spare slots)
         const size_t ndef = slots;
@@ -2684,17 +2747,16 @@ int event_pair(RRWorkspace &ws) {
 hipEvent_t *batch_events(RRWorkspace &ws, uint64_t k) { return &ws.events[4 + (size_t)(k & 1u) * kBatchEv]; }
 
 // Pinned host staging of the RR workspace, in 64-bit words: counter-block
-// copies (two superstep batches in flight, the end of a launch group), the
-// spare-slot cursor, then per-call regions (graph and task descriptors, the
+// copies (two superstep batches in flight, the end of a launch group), bundled
+// mode's first counter, then per-call regions (graph and task descriptors, the
 // pools' new totals).  Copies from and to it are asynchronous; the host
 // touches a region only after waiting for the copy that uses it.
-constexpr size_t kHostCtr = 16;
+constexpr size_t kHostCtr = kNumCtr;
 constexpr size_t kHostBatch = 0;   // + (k & 1) * kHostCtr for batch k
 constexpr size_t kHostFinal = 2 * kHostCtr;
-constexpr size_t kHostFreeNext = 3 * kHostCtr;
-constexpr size_t kHostArgs = 4 * kHostCtr;   // the grid-wide phase's RRArgs on their way to the device
+constexpr size_t kHostMsStart = kHostFinal + kCtrWords;
+constexpr size_t kHostArgs = kHostMsStart + kCtrLine;   // the grid-wide phase's RRArgs on their way to the device
 constexpr size_t kHostFixed = kHostArgs + (sizeof(RRArgs) + 7) / 8;
-static_assert(kNumCtr <= kHostCtr, "counter block");
 
 int ensure_host(RRWorkspace &ws, size_t words) {
     if (ws.host_words >= words) return HYPERIM_OK;
@@ -2782,12 +2844,6 @@ int run_launch(RRWorkspace &ws, RRStats &st, const hyperim_tuning &tune, RRArgs 
     *reinterpret_cast<RRArgs *>(h + kHostArgs) = a;
     HIM_HIP(hipMemcpyAsync(ws.args_dev.ptr, h + kHostArgs, sizeof(RRArgs), hipMemcpyHostToDevice, s));
     const RRArgs *ap = ws.args_dev.as<RRArgs>();
-    // fresh work counter, deferred list and spare-slot cursor (spare slots
-    // follow the launched waves' own slots)
-    h[kHostFreeNext] = (unsigned long long)grid * kWavesPerWG;
-    HIM_HIP(hipMemsetAsync(ctr + kWork, 0, sizeof(unsigned long long), s));
-    HIM_HIP(hipMemsetAsync(ctr + kDefCount, 0, sizeof(unsigned long long), s));
-    HIM_HIP(hipMemcpyAsync(ctr + kFreeNext, h + kHostFreeNext, sizeof(unsigned long long), hipMemcpyHostToDevice, s));
     HIM_CHECK(event_pair(ws));
     auto light = shape.lds ? (gaps ? k_rr_light<true, true> : k_rr_light<true, false>)
                            : (gaps ? k_rr_light<false, true> : k_rr_light<false, false>);
@@ -2889,7 +2945,6 @@ int run_launch(RRWorkspace &ws, RRStats &st, const hyperim_tuning &tune, RRArgs 
             HIM_HIP(hipEventRecord(E[1], s));
             return HYPERIM_OK;
         };
-        HIM_HIP(hipMemsetAsync(ctr + kItems, 0, 2 * sizeof(unsigned long long), s));
         HIM_CHECK(issue(0));
         uint64_t planned_before = 0;
         for (;;) {
@@ -2927,7 +2982,7 @@ int run_launch(RRWorkspace &ws, RRStats &st, const hyperim_tuning &tune, RRArgs 
         HIM_HIP(hipGetLastError());
         st.launches += 1;
     }
-    HIM_HIP(hipMemcpyAsync(h + kHostFinal, ctr, sizeof(unsigned long long) * kNumCtr, hipMemcpyDeviceToHost, s));
+    HIM_HIP(hipMemcpyAsync(h + kHostFinal, ctr, sizeof(unsigned long long) * kCtrWords, hipMemcpyDeviceToHost, s));
     const int rc = tail();
     HIM_HIP(hipStreamSynchronize(s));
     HIM_CHECK(rc);
@@ -2959,7 +3014,7 @@ int run_lt_launch(RRWorkspace &ws, RRStats &st, const RRArgs &a, const LaunchSha
         hipExtLaunchKernelGGL(k_lt_walk<false>, dim3(grid), dim3(kWG), 0, s, ws.events[0], ws.events[1], 0u, a);
     HIM_HIP(hipGetLastError());
     st.launches += 1;
-    HIM_HIP(hipMemcpyAsync(h + kHostFinal, a.ctr, sizeof(unsigned long long) * kNumCtr, hipMemcpyDeviceToHost, s));
+    HIM_HIP(hipMemcpyAsync(h + kHostFinal, a.ctr, sizeof(unsigned long long) * kCtrWords, hipMemcpyDeviceToHost, s));
     const int rc = tail();
     HIM_HIP(hipStreamSynchronize(s));
     HIM_CHECK(rc);
@@ -2986,7 +3041,7 @@ int run_layered_launch(RRWorkspace &ws, RRStats &st, const RRArgs &a, const Laun
                               ws.picks.as<uint32_t>());
     HIM_HIP(hipGetLastError());
     st.launches += 1;
-    HIM_HIP(hipMemcpyAsync(h + kHostFinal, a.ctr, sizeof(unsigned long long) * kNumCtr, hipMemcpyDeviceToHost, s));
+    HIM_HIP(hipMemcpyAsync(h + kHostFinal, a.ctr, sizeof(unsigned long long) * kCtrWords, hipMemcpyDeviceToHost, s));
     const int rc = tail();
     HIM_HIP(hipStreamSynchronize(s));
     HIM_CHECK(rc);
@@ -3052,8 +3107,7 @@ int run_ms_launch(RRWorkspace &ws, RRStats &st, const hyperim_tuning &tune, RRAr
     m.batch_epoch = ws.ms_batch.as<uint32_t>();
     m.list_cap = list_cap;
     m.ctr = ws.ms_ctr.as<unsigned long long>();
-    m.bytes = a.ctr + kBytesMs;
-    m.philox = a.ctr + kPhiloxMs;
+    m.stats = a.ctr;
     m.items = a.items;
     m.vcnt = ws.ms_vcnt.as<uint32_t>();
     m.nvb = nvb;
@@ -3062,8 +3116,8 @@ int run_ms_launch(RRWorkspace &ws, RRStats &st, const hyperim_tuning &tune, RRAr
     HIM_HIP(hipMemsetAsync(m.nxt, 0, sizeof(unsigned long long) * nbundles * stride, s));
     HIM_HIP(hipMemsetAsync(m.batch_epoch, 0, sizeof(uint32_t) * div_up(list_cap, kWave), s));
     HIM_HIP(hipMemsetAsync(m.ctr, 0, sizeof(unsigned long long) * kMsNumCtr, s));
-    ws.host[kHostFreeNext + 1] = 1;
-    HIM_HIP(hipMemcpyAsync(m.ctr + kMsLevelDone, ws.host + kHostFreeNext + 1, sizeof(unsigned long long),
+    ws.host[kHostMsStart] = 1;
+    HIM_HIP(hipMemcpyAsync(m.ctr + kMsLevelDone, ws.host + kHostMsStart, sizeof(unsigned long long),
                            hipMemcpyHostToDevice, s));
     HIM_CHECK(event_pair(ws));
     HIM_HIP(hipEventRecord(ws.events[0], s));
@@ -3161,7 +3215,7 @@ int run_ms_launch(RRWorkspace &ws, RRStats &st, const hyperim_tuning &tune, RRAr
     hipLaunchKernelGGL(k_ms_record, dim3((uint32_t)div_up(a.count, kWG)), dim3(kWG), 0, s, m, a);
     hipLaunchKernelGGL(k_ms_write, dim3(out_grid), dim3(kWG), 0, s, m, a);
     HIM_HIP(hipGetLastError());
-    HIM_HIP(hipMemcpyAsync(ws.host + kHostFinal, a.ctr, sizeof(unsigned long long) * kNumCtr, hipMemcpyDeviceToHost,
+    HIM_HIP(hipMemcpyAsync(ws.host + kHostFinal, a.ctr, sizeof(unsigned long long) * kCtrWords, hipMemcpyDeviceToHost,
                            s));
     HIM_HIP(hipEventRecord(ws.events[3], s));
     const int rc = tail();
@@ -3443,6 +3497,10 @@ int rr_generate_into(RRWorkspace &ws, RRStats &st, const std::vector<RRTask> &ta
         a.big_ids = ws.big_ids.as<uint64_t>();
         const uint32_t grid =
             form == 0 ? grid_a : (uint32_t)std::min<uint64_t>(grid_a, div_up(a.count, kWavesPerWG));
+        // Index by index where a wave has few; eight grabs a wave or more, so
+        // that the last ones are short.
+        a.take = (uint32_t)std::clamp<uint64_t>(a.count / ((uint64_t)grid * kWavesPerWG * 8), 1, 8);
+        a.free0 = grid * kWavesPerWG;
         // a graph whose sets were never deferred before is checked after phase
         // A, a small one (marks in LDS) until one of its sets was
         bool expect_defer = false;
@@ -3468,7 +3526,8 @@ int rr_generate_into(RRWorkspace &ws, RRStats &st, const std::vector<RRTask> &ta
         for (int attempt = 0; attempt < 2 && !staged; ++attempt) {
             a.stage = ws.stage.as<uint32_t>();
             a.stage_cap = ws.stage.bytes / sizeof(uint32_t);
-            HIM_HIP(hipMemsetAsync(ctr, 0, sizeof(unsigned long long) * kNumCtr, s));
+            a.stage_step = (uint32_t)std::min<uint64_t>(256, a.stage_cap >> 18);   // at most 1/32 of it unused
+            HIM_HIP(hipMemsetAsync(ctr, 0, sizeof(unsigned long long) * kCtrWords, s));
             RRStats run{};
             if (ms)
                 HIM_CHECK(run_ms_launch(ws, run, tune, a, shape, tasks[slices[0].task].g, tdesc[0], trace,
@@ -3495,12 +3554,13 @@ int rr_generate_into(RRWorkspace &ws, RRStats &st, const std::vector<RRTask> &ta
             for (const Slice &sl : slices) tasks[sl.task].g->rr_defer = (double)run.deferred / (double)a.count;
             if (bump <= a.stage_cap) {
                 st.deferred += run.deferred;
-                st.bytes_light += hf[kBytesA];
-                st.bytes_heavy += hf[kBytesB];
-                st.bytes_bundled += hf[kBytesMs];
-                st.philox += hf[kPhiloxA] + hf[kPhilox] + hf[kPhiloxMs];
-                st.philox_light += hf[kPhiloxA];
-                st.philox_bundled += hf[kPhiloxMs];
+                const uint64_t px_light = stat_sum(hf, kPhiloxA), px_bundled = stat_sum(hf, kPhiloxMs);
+                st.bytes_light += stat_sum(hf, kBytesA);
+                st.bytes_heavy += stat_sum(hf, kBytesB);
+                st.bytes_bundled += stat_sum(hf, kBytesMs);
+                st.philox += px_light + stat_sum(hf, kPhilox) + px_bundled;
+                st.philox_light += px_light;
+                st.philox_bundled += px_bundled;
                 staged = true;
             } else {
                 HIM_CHECK(ws.stage.reserve(sizeof(uint32_t) * (size_t)(bump + bump / 4 + 1024), s, false));
