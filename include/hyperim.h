@@ -450,7 +450,8 @@ int hyperim_workspace_release(void);
  *                  sets of at least this many members (0xFFFFFFFF: never;
  *                  the scattered mark loads cost more than the coins they
  *                  save on the workloads measured);
- *   steps_per_sync: grid-wide supersteps launched between host checks (8);
+ *   steps_per_sync: grid-wide supersteps launched between host checks (8; from
+ *                  8 on, a quarter as many after the first check);
  *   stage_mib:     staging memory a generation pass aims at: launch groups
  *                  are cut so that their members fit (16384 MiB, min 64);
  *   blocks_a:      per-set phase workgroups per compute unit, at most the

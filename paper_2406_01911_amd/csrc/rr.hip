@@ -1560,6 +1560,15 @@ __global__ __launch_bounds__(kWG) void k_plan(const RRArgs *__restrict__ ap, uin
     if (lane == 0 && taken) atomicAdd(&a.ctr[kPlanned], (unsigned long long)taken);
 }
 
+// The counters a batch of supersteps leaves, into pinned host memory: one more
+// small kernel of the batch, where a copy engine's transfer kept the next batch
+// waiting for 18 us.
+__global__ __launch_bounds__(kWG) void k_publish(const unsigned long long *__restrict__ ctr,
+                                                  unsigned long long *__restrict__ host) {
+    for (uint32_t i = threadIdx.x; i < kNumCtr; i += blockDim.x) host[i] = ctr[i];
+    __threadfence_system();
+}
+
 template <bool kGaps>
 __global__ __launch_bounds__(kWG) void k_expand(const RRArgs *__restrict__ ap, uint32_t parity) {
     const RRArgs a = *ap;
@@ -2726,7 +2735,7 @@ int wait_event(hipEvent_t e, const char *what) {
 // Events of the RR workspace: [0], [1] start and end of phase A, [2], [3] of
 // the closing k_finish (bundled mode: of the whole group); superstep batch
 // slot b (two batches in flight) owns kBatchEv events from 4 + b * kBatchEv:
-// batch start, batch end (after its counter copy), then a start/end pair per
+// batch start (the first batch's only), batch end (after its counter copy), then a start/end pair per
 // k_expand launch when kernel times are asked for.  Events that time one
 // kernel are stamped by its launch
 // (hipExtLaunchKernelGGL): stream markers between dependent kernels would
@@ -2827,8 +2836,8 @@ int captured_batch(RRWorkspace &ws, const uint64_t (&key)[8], Record &&record, h
 
 // One launch group: phase A over `a`'s tasks, then phase B over the sets it
 // deferred, then the deferred sets' output.  Per-id outputs land at
-// a.out_base + launch index.  Supersteps go in batches of steps_per_sync, and
-// the next batch is queued before the host reads the frontier count at the end
+// a.out_base + launch index.  Supersteps go in batches of steps_per_sync (the
+// later ones may be shorter), and the next batch is queued before the host reads the frontier count at the end
 // of the last one, so the device never waits for the host between batches
 // (the batch queued after the frontier ran out finds no work).  The closing
 // counter block lands in ws.host + kHostFinal; `tail` may queue more work
@@ -2861,20 +2870,33 @@ int run_launch(RRWorkspace &ws, RRStats &st, const hyperim_tuning &tune, RRArgs 
         ndef = h[kHostBatch + kDefCount];
         phase_b = ndef != 0;
     }
-    int batch = trace ? 1 : (int)std::min<uint32_t>(std::max<uint32_t>(tune.steps_per_sync, 1), kMaxBatch);
+    int first = trace ? 1 : (int)std::min<uint32_t>(std::max<uint32_t>(tune.steps_per_sync, 1), kMaxBatch);
     // captured batches replay the same parities every time: an even batch
     // starts every replay on counter parity 0.  Launches timed one by one
     // (events stamped by the launch itself) are not captured: an event
     // recorded inside a graph does not time against one recorded outside.
     const bool use_graphs = graphs && !trace && !time_kernels && !ws.graphs_off;
-    if (use_graphs && (batch & 1)) batch = std::min(batch + 1, kMaxBatch);
+    if (use_graphs && (first & 1)) first = std::min(first + 1, kMaxBatch);
+    // Most traversals are over, or nearly, after a first batch of 8 or more, and
+    // each superstep queued beyond the end costs 9 us: the later batches are a
+    // quarter as long (even).  777 sets of a 10000-vertex graph, first 8: 592 us
+    // with later batches of 8, 549 of 4, 530 of 2; 4096 sets of a 1e5-vertex
+    // graph 1.94, 1.90 and 1.90 ms.  Shorter first batches stay as asked: halving
+    // 4 cost 0.7 % where there were 17 supersteps to do.
+    const int later = first < 8 ? first : first / 4 & ~1;
+    auto batch_size = [&](uint64_t k) { return k == 0 ? first : later; };
+    auto batch_start = [&](uint64_t k) { return k == 0 ? 0ull : (uint64_t)first + (k - 1) * (uint64_t)later; };
+    float ms_before = 0.f;
     auto account = [&](uint64_t k) -> int {
+        const int batch = batch_size(k);
         hipEvent_t *E = batch_events(ws, k);
         float ms = 0.f;
-        // first k_plan .. last k_expand (or the batch's counter copy)
-        HIM_HIP(hipEventElapsedTime(&ms, E[0], time_kernels ? E[3 + 2 * (batch - 1)] : E[1]));
-        st.ms_bfs += ms;
-        st.ms_heavy += ms;
+        // first k_plan of the first batch .. last k_expand (or the batch's
+        // counter copy), less the batches before: one event between batches
+        HIM_HIP(hipEventElapsedTime(&ms, batch_events(ws, 0)[0], time_kernels ? E[3 + 2 * (batch - 1)] : E[1]));
+        st.ms_bfs += ms - ms_before;
+        st.ms_heavy += ms - ms_before;
+        ms_before = ms;
         for (int i = 0; time_kernels && i < batch; ++i) {
             float me = 0.f;
             HIM_HIP(hipEventElapsedTime(&me, E[2 + 2 * i], E[3 + 2 * i]));
@@ -2898,6 +2920,7 @@ int run_launch(RRWorkspace &ws, RRStats &st, const hyperim_tuning &tune, RRArgs 
                                          kWavesPerWG),
                                   4096));
         auto issue = [&](uint64_t kb) -> int {
+            const int batch = batch_size(kb);
             hipEvent_t *E = batch_events(ws, kb);
             unsigned long long *dst = h + kHostBatch + (kb & 1u) * kHostCtr;
             if (use_graphs) {
@@ -2914,12 +2937,12 @@ int run_launch(RRWorkspace &ws, RRStats &st, const hyperim_tuning &tune, RRArgs 
                             hipLaunchKernelGGL(k_plan, dim3(plan_grid_all), dim3(kWG), 0, c, ap, parity);
                             hipLaunchKernelGGL(expand_k, dim3(grid_b), dim3(kWG), 0, c, ap, parity);
                         }
-                        return hipMemcpyAsync(dst, ctr, sizeof(unsigned long long) * kNumCtr, hipMemcpyDeviceToHost,
-                                              c) == hipSuccess;
+                        hipLaunchKernelGGL(k_publish, dim3(1), dim3(kWG), 0, c, ctr, dst);
+                        return hipGetLastError() == hipSuccess;
                     },
                     &ex));
                 if (ex) {
-                    HIM_HIP(hipEventRecord(E[0], s));
+                    if (kb == 0) HIM_HIP(hipEventRecord(E[0], s));
                     HIM_HIP(hipGraphLaunch(ex, s));
                     HIM_HIP(hipEventRecord(E[1], s));
                     return HYPERIM_OK;
@@ -2929,8 +2952,8 @@ int run_launch(RRWorkspace &ws, RRStats &st, const hyperim_tuning &tune, RRArgs 
             const uint32_t plan_grid =
                 (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(div_up(plan_sets, kWavesPerWG), 4096));
             for (int i = 0; i < batch; ++i) {
-                const uint32_t parity = (uint32_t)((kb * (uint64_t)batch + (uint64_t)i) & 1u);
-                hipExtLaunchKernelGGL(k_plan, dim3(plan_grid), dim3(kWG), 0, s, i == 0 ? E[0] : nullptr, nullptr,
+                const uint32_t parity = (uint32_t)((batch_start(kb) + (uint64_t)i) & 1u);
+                hipExtLaunchKernelGGL(k_plan, dim3(plan_grid), dim3(kWG), 0, s, kb == 0 && i == 0 ? E[0] : nullptr, nullptr,
                                       0u, ap, parity);
                 // timed: the launch itself stamps its start and end events (no
                 // stream markers between the kernels)
@@ -2940,8 +2963,8 @@ int run_launch(RRWorkspace &ws, RRStats &st, const hyperim_tuning &tune, RRArgs 
                 else
                     hipLaunchKernelGGL(expand_k, dim3(grid_b), dim3(kWG), 0, s, ap, parity);
             }
+            hipLaunchKernelGGL(k_publish, dim3(1), dim3(kWG), 0, s, ctr, dst);
             HIM_HIP(hipGetLastError());
-            HIM_HIP(hipMemcpyAsync(dst, ctr, sizeof(unsigned long long) * kNumCtr, hipMemcpyDeviceToHost, s));
             HIM_HIP(hipEventRecord(E[1], s));
             return HYPERIM_OK;
         };
@@ -2953,12 +2976,12 @@ int run_launch(RRWorkspace &ws, RRStats &st, const hyperim_tuning &tune, RRArgs 
             const unsigned long long *hb = h + kHostBatch + (k & 1u) * kHostCtr;
             ndef = hb[kDefCount];
             plan_sets = std::max<uint64_t>(ndef, 1);
-            const uint32_t last = (uint32_t)(((k + 1) * (uint64_t)batch - 1) & 1u);
+            const uint32_t last = (uint32_t)((batch_start(k + 1) - 1) & 1u);
             const uint64_t items = hb[kItems + last];
             HIM_CHECK(account(k));
             if (trace)
                 fprintf(stderr, "[hyperim] superstep %llu: %llu items, %llu entries planned\n",
-                        (unsigned long long)((k + 1) * (uint64_t)batch), (unsigned long long)items,
+                        (unsigned long long)batch_start(k + 1), (unsigned long long)items,
                         (unsigned long long)hb[kPlanned]);
             // the deferred sets hold at most slot_n members each
             const int chk = phase_b_check(planned_before, hb[kPlanned], items,
