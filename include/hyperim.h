@@ -433,7 +433,10 @@ int hyperim_session_stats_get(hyperim_session s, hyperim_session_stats *out);
 void hyperim_session_free(hyperim_session s);
 
 /* The RR-generation workspace is shared by every graph of a device and kept
- * between calls: its current size on the current device, and its release. */
+ * between calls: its current size on the current device, and its release.
+ * Freed device memory of any handle is kept for the next allocation, at most
+ * 1 GiB per device beyond that size; the release, or an allocation that fails,
+ * gives it back too. */
 int hyperim_workspace_info(size_t *bytes);
 int hyperim_workspace_release(void);
 

@@ -35,6 +35,8 @@ void clear_error_detail();
 struct DevBuf {
     void *ptr = nullptr;
     size_t bytes = 0;
+    size_t block = 0;   // of the allocation behind it (a kept block may be larger)
+    int dev = 0;
     DevBuf() = default;
     DevBuf(const DevBuf &) = delete;
     DevBuf &operator=(const DevBuf &) = delete;
@@ -44,6 +46,9 @@ struct DevBuf {
     template <typename T>
     T *as() const { return static_cast<T *>(ptr); }
 };
+
+// Bytes of freed device blocks that the library keeps for its next allocations.
+size_t cached_bytes(int device);
 
 // Workspace of RR generation: one per device, shared by every graph on it
 // (calls that use it hold its lock).

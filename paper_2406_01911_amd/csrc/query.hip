@@ -753,6 +753,9 @@ int hyperim_select_seeds_batch(const hyperim_query *queries, uint32_t count, con
     // (its graphs, the shared workspaces), less a reserve
     size_t free_b = 0, total_b = 0;
     HIM_HIP(hipMemGetInfo(&free_b, &total_b));
+    int device = 0;
+    HIM_HIP(hipGetDevice(&device));
+    free_b += cached_bytes(device);   // given back when an allocation fails
     std::vector<hyperim_graph> gs;
     size_t held = device_shared_bytes();
     for (uint32_t i = 0; i < count; ++i)
