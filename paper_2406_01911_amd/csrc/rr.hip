@@ -1450,7 +1450,13 @@ __device__ __forceinline__ uint32_t owner_of(uint32_t hscan, uint32_t q) {
     return scan_owner([hscan](uint32_t k) { return (uint32_t)__shfl((int)hscan, (int)k, kWave); }, q);
 }
 constexpr uint32_t kShareMax = 16;   // waves that may share one item
-constexpr uint32_t kContLevels = 8;  // levels a wave may expand past its item
+// Levels a wave may expand past its item: many where other items keep the waves
+// busy anyway, few where the superstep waits for its longest chain, up to 4
+// items per wave.  8 against 3 there: 777 sets of a 10000-vertex graph 527 and
+// 461 us, 4096 of a 1e5-vertex one 1.89 and 1.84 ms, a serving session 236 and
+// 225 ms; with 3 everywhere eight mixed instances lost 1.2 %.  The gap models'
+// thin supersteps gain nothing from fewer.
+constexpr uint32_t kContLevels = 8, kContFew = 3;
 
 // Queue entries a planning wave takes per reservation of items, in batches of
 // 64: the reservations of all waves meet at one counter, at 7.5 ns each (sets
@@ -1594,6 +1600,7 @@ __global__ __launch_bounds__(kWG) void k_expand(const RRArgs *__restrict__ ap, u
     const uint64_t waves = (uint64_t)gridDim.x * kWavesPerWG;
     uint32_t W = 1;
     while (W < kShareMax && 2ull * W * nitems <= waves) W <<= 1;
+    const uint32_t levels = kGaps || nitems > 4ull * waves ? kContLevels : kContFew;
     const uint64_t gw = (uint64_t)blockIdx.x * kWavesPerWG + wv, groups = waves / W;
     const uint32_t w = (uint32_t)(gw & (W - 1));
     const uint32_t lane = lane_id();
@@ -1646,7 +1653,7 @@ __global__ __launch_bounds__(kWG) void k_expand(const RRArgs *__restrict__ ap, u
         // kContLevels levels) and marks their queue entries expanded, so the
         // thin tail of a traversal does not take one superstep per level.
         // Nobody else reads those entries before the next superstep.
-        for (uint32_t lev = 0; G.n <= kExpanded && lev < kContLevels; ++lev) {
+        for (uint32_t lev = 0; G.n <= kExpanded && lev < levels; ++lev) {
             const uint32_t cn = app.count;
             if (cn == 0 || cn > kWave) break;
             wave_sync();
