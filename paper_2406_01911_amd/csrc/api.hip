@@ -209,7 +209,7 @@ DevCtx *device_ctx(int device) {
 }
 }  // namespace
 
-DeviceLock::DeviceLock(int device) {
+DeviceLock::DeviceLock(int device) : idle(true) {
     DevCtx *c = device_ctx(device);
     c->mu.lock();
     rr = &c->rr;
@@ -218,7 +218,21 @@ DeviceLock::DeviceLock(int device) {
     lock = c;
 }
 
-DeviceLock::~DeviceLock() { static_cast<DevCtx *>(lock)->mu.unlock(); }
+DeviceLock::DeviceLock(int device, hipStream_t s) : DeviceLock(device) {
+    stream = s;
+    idle = false;
+}
+
+int DeviceLock::drain() {
+    HIM_HIP(hipStreamSynchronize(stream));
+    idle = true;
+    return HYPERIM_OK;
+}
+
+DeviceLock::~DeviceLock() {
+    if (!idle) (void)hipStreamSynchronize(stream);
+    static_cast<DevCtx *>(lock)->mu.unlock();
+}
 
 void GreedyWorkspace::release() {
     for (DevBuf *x : {&zeroed, &round, &inv_off, &inv, &out, &big, &flags, &counters, &scan_tmp, &params}) x->release();
@@ -348,7 +362,7 @@ size_t pool_bytes(const hyperim_pool_s &p) { return p.off_b.bytes + p.roots_b.by
 // (tasks with an empty id range are skipped).
 int generate_into(const std::vector<RRTask> &tasks, const std::vector<hyperim_pool> &pools, uint32_t qlog, int form,
                   uint64_t max_entries, hipStream_t s, RRStats &st, std::vector<int> *pool_status,
-                  bool time_kernels, bool graphs) {
+                  bool time_kernels, bool graphs, hipEvent_t end) {
     std::vector<RRTask> live;
     std::vector<hyperim_pool> dst;
     std::vector<size_t> which;
@@ -362,14 +376,20 @@ int generate_into(const std::vector<RRTask> &tasks, const std::vector<hyperim_po
             was_empty.push_back(pools[i]->count == 0);
         }
     if (pool_status) pool_status->assign(tasks.size(), HYPERIM_OK);
-    if (live.empty()) return HYPERIM_OK;
+    if (live.empty()) {
+        if (end) HIM_HIP(hipEventRecord(end, s));
+        HIM_HIP(hipStreamSynchronize(s));
+        return HYPERIM_OK;
+    }
     int device = 0;
     HIM_HIP(hipGetDevice(&device));
-    DeviceLock lk(device);
+    DeviceLock lk(device, s);
     std::vector<int> status;
     const uint64_t stage_budget = (uint64_t)std::max<uint32_t>(live[0].g->tune.stage_mib, 64) << 20;
     HIM_CHECK(rr_generate_into(*lk.rr, st, live, dst, qlog, form, max_entries, stage_budget, s, status,
                                time_kernels, graphs));
+    if (end) HIM_HIP(hipEventRecord(end, s));
+    HIM_CHECK(lk.drain());   // the last group's sets are on their way from the workspace to the pools
     int first_fail = HYPERIM_OK;
     for (size_t i = 0; i < live.size(); ++i) {
         if (was_empty[i] && dst[i]->count) dst[i]->id_begin = live[i].id_begin;
@@ -449,8 +469,10 @@ int hyperim_build_graph(uint32_t n, uint32_t m, const uint32_t *he_off, const ui
         HIM_CHECK(g->he_mem.reserve(sizeof(uint32_t) * ((uint64_t)nnz + 4), s));   // read 4 at a time
         HIM_HIP(hipMemcpyAsync(g->he_off.ptr, he_off, sizeof(uint32_t) * ((size_t)m + 1), kind, s));
         if (nnz) HIM_HIP(hipMemcpyAsync(g->he_mem.ptr, he_mem, sizeof(uint32_t) * (size_t)nnz, kind, s));
-        DeviceLock lk(g->device);
-        return graph_build_device(g, *lk.prep, s);
+        DeviceLock lk(g->device, s);
+        HIM_CHECK(graph_build_device(g, *lk.prep, s));
+        lk.idle = true;   // it ends with a wait
+        return HYPERIM_OK;
     }();
     if (rc != HYPERIM_OK) {
         release_graph(g);
@@ -465,7 +487,7 @@ int hyperim_stratify(hyperim_graph g, void *stream, hyperim_strata_info *out) {
     if (!g) return HYPERIM_EINVAL;
     g_detail.clear();
     {
-        DeviceLock lk(g->device);
+        DeviceLock lk(g->device, as_stream(stream));
         HIM_CHECK(stratify_device(g, *lk.prep, as_stream(stream)));
     }
     if (out) *out = g->info;
@@ -490,7 +512,7 @@ int hyperim_route(hyperim_graph g, uint32_t on, void *stream, uint32_t *n_r1) {
     g->route_on = false;   // set once the tables are built (a failed build leaves the graph undivided)
     uint32_t n1 = 0;
     if (on) {
-        DeviceLock lk(g->device);
+        DeviceLock lk(g->device, as_stream(stream));
         HIM_CHECK(route_build(g, *lk.prep, as_stream(stream), &n1));
         g->route_on = true;
     }
@@ -582,7 +604,6 @@ int hyperim_generate_rr(hyperim_graph g, uint64_t seed, uint32_t instance, uint3
     pool->seed = seed;
     pool->instance = instance;
     pool->tag = pool_tag;
-    HIM_HIP(hipStreamSynchronize(as_stream(stream)));
     return HYPERIM_OK;
 }
 
@@ -620,7 +641,6 @@ int hyperim_generate_rr_batch(const hyperim_rr_task *tasks, uint32_t count, uint
         p->instance = tasks[i].instance;
         p->tag = tasks[i].pool_tag;
     }
-    HIM_HIP(hipStreamSynchronize(as_stream(stream)));
     return HYPERIM_OK;
 }
 
@@ -668,8 +688,10 @@ int hyperim_greedy(hyperim_graph g, hyperim_pool pool, uint64_t theta, uint32_t 
         return HYPERIM_EINVAL;
     }
     HIM_CHECK(check_device(g));
-    DeviceLock lk(g->device);
-    return greedy_device(*lk.gr, g, pool, theta, k, as_stream(stream), seeds, gains);
+    DeviceLock lk(g->device, as_stream(stream));
+    HIM_CHECK(greedy_device(*lk.gr, g, pool, theta, k, as_stream(stream), seeds, gains));
+    lk.idle = true;   // it ends with a wait
+    return HYPERIM_OK;
 }
 
 int hyperim_coverage(hyperim_graph g, hyperim_pool pool, uint64_t theta, const uint32_t *seeds, uint32_t k,
@@ -688,8 +710,9 @@ int hyperim_coverage(hyperim_graph g, hyperim_pool pool, uint64_t theta, const u
     if (k) HIM_HIP(hipMemcpyAsync(d.ptr, seeds, sizeof(uint32_t) * k, hipMemcpyHostToDevice, s));
     int rc;
     {
-        DeviceLock lk(g->device);
+        DeviceLock lk(g->device, s);
         rc = coverage_device(*lk.gr, g, pool, theta, d.as<uint32_t>(), k, s, covered);
+        lk.idle = rc == HYPERIM_OK;   // it ends with a wait
     }
     d.release();
     return rc;

@@ -143,14 +143,20 @@ struct PrepWorkspace {
 };
 
 // The device's shared workspaces (RR generation, greedy / coverage,
-// stratification), locked for the holder's lifetime.
+// stratification), locked for the holder's lifetime.  The holder's stream is
+// waited for before the lock goes to the next one, who may use another stream:
+// drain() waits, and the destructor does where nobody has (an early return).
 struct DeviceLock {
     RRWorkspace *rr;
     GreedyWorkspace *gr;
     PrepWorkspace *prep;
     void *lock;
-    explicit DeviceLock(int device);
+    hipStream_t stream = nullptr;
+    bool idle;   // nothing of the workspaces is in use on the stream
+    explicit DeviceLock(int device);                  // queues no work
+    DeviceLock(int device, hipStream_t s);
     ~DeviceLock();
+    int drain();
     DeviceLock(const DeviceLock &) = delete;
     DeviceLock &operator=(const DeviceLock &) = delete;
 };
@@ -258,12 +264,13 @@ struct RRTask;
 // Generate tasks[i] into pools[i] (one generation pass; tasks with empty
 // ranges skipped).  With pool_status, a pool that would exceed max_entries
 // gets HYPERIM_ECAPACITY there and the others are still filled; without it
-// that status is returned.
+// that status is returned.  Returns after the stream has drained.
 // time_kernels: time every expansion-kernel launch (RRStats::ms_expand).
 // graphs: replay captured superstep batches (HIP graphs) where the device allows.
+// end (may be null): recorded behind the pass's work.
 int generate_into(const std::vector<RRTask> &tasks, const std::vector<hyperim_pool> &pools, uint32_t qlog, int form,
                   uint64_t max_entries, hipStream_t s, RRStats &st, std::vector<int> *pool_status,
-                  bool time_kernels = false, bool graphs = true);
+                  bool time_kernels = false, bool graphs = true, hipEvent_t end = nullptr);
 
 // ---- launchers (graph.hip) --------------------------------------------------
 int graph_build_device(hyperim_graph g, PrepWorkspace &w, hipStream_t s);

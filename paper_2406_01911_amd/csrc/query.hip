@@ -359,9 +359,8 @@ struct Engine {
         float ms = 0.f;
         HIM_HIP(hipEventRecord(ev.a, stream));
         HIM_CHECK(generate_into(tasks, dst, opt.qlog, (int)opt.form, opt.max_entries, stream, st, &status,
-                                (opt.flags & HYPERIM_FLAG_KERNEL_TIMES) != 0, (opt.flags & HYPERIM_FLAG_NO_GRAPHS) == 0));
-        HIM_HIP(hipEventRecord(ev.b, stream));
-        HIM_HIP(hipEventSynchronize(ev.b));
+                                (opt.flags & HYPERIM_FLAG_KERNEL_TIMES) != 0, (opt.flags & HYPERIM_FLAG_NO_GRAPHS) == 0,
+                                ev.b));
         HIM_HIP(hipEventElapsedTime(&ms, ev.a, ev.b));
         for (size_t i = 0; i < pps.size(); ++i) {
             if (status[i] == HYPERIM_OK)
@@ -484,9 +483,8 @@ struct Engine {
             HIM_HIP(hipEventRecord(ev.a, s));
             std::vector<int> pool_status;
             HIM_CHECK(generate_into(tasks, dst, o.qlog, (int)o.form, o.max_entries, s, st, &pool_status,
-                                    (o.flags & HYPERIM_FLAG_KERNEL_TIMES) != 0, (o.flags & HYPERIM_FLAG_NO_GRAPHS) == 0));
-            HIM_HIP(hipEventRecord(ev.b, s));
-            HIM_HIP(hipEventSynchronize(ev.b));
+                                    (o.flags & HYPERIM_FLAG_KERNEL_TIMES) != 0, (o.flags & HYPERIM_FLAG_NO_GRAPHS) == 0,
+                                    ev.b));
             HIM_HIP(hipEventElapsedTime(&ms_rr, ev.a, ev.b));
             add_stats(total, st, ms_rr);
             for (size_t t = 0; t < tasks.size(); ++t)
@@ -519,7 +517,7 @@ struct Engine {
             uint64_t lambda2 = 0;
             std::vector<uint64_t> ub(o.bound == 0 ? (size_t)k + 1 : 0, 0ull);
             {
-                DeviceLock lk(device);
+                DeviceLock lk(device, s);
                 HIM_HIP(hipEventRecord(ev.a, s));
                 HIM_CHECK(greedy_device(*lk.gr, g, &q->pp->r[0], theta, k, s, q->seeds.data(), q->gains.data(),
                                         o.bound == 0 ? ub.data() : nullptr));
@@ -527,6 +525,7 @@ struct Engine {
                                           &lambda2));
                 HIM_HIP(hipEventRecord(ev.b, s));
                 HIM_HIP(hipEventSynchronize(ev.b));
+                lk.idle = true;
             }
             HIM_HIP(hipEventElapsedTime(&ms, ev.a, ev.b));
             res.ms_greedy += ms;

@@ -1,0 +1,84 @@
+// Host-code checks of libhyperim.so over the stand-in runtime: one scenario per
+// run (argv[1]); prints "ok ..." or says what is wrong and exits with 1.
+#include <hip/hip_runtime_api.h>
+#include <stdint.h>
+#include <stdio.h>
+#include <string.h>
+
+#include <thread>
+#include <vector>
+
+#include "fake_hip.h"
+#include "hyperim.h"
+
+namespace {
+
+#define NEED(cond, ...)                               \
+    do {                                              \
+        if (!(cond)) {                                \
+            printf("line %d: %s: ", __LINE__, #cond); \
+            printf(__VA_ARGS__);                      \
+            printf("\n");                             \
+            return 1;                                 \
+        }                                             \
+    } while (0)
+
+hipStream_t stream(int i) { return reinterpret_cast<hipStream_t>((uintptr_t)(16 * (i + 1))); }
+
+// n vertices in hyperedges of two.
+hyperim_graph pairs(uint32_t n, hipStream_t s, uint32_t model = HYPERIM_MODEL_CONST) {
+    std::vector<uint32_t> off(n / 2 + 1), mem(n / 2 * 2);
+    for (uint32_t e = 0; e <= n / 2; ++e) off[e] = 2 * e;
+    for (uint32_t v = 0; v < mem.size(); ++v) mem[v] = v;
+    hyperim_prob p{model, 0.5f};
+    hyperim_graph g = nullptr;
+    if (hyperim_build_graph(n, n / 2, off.data(), mem.data(), 0, p, s, &g) != HYPERIM_OK) return nullptr;
+    if (hyperim_stratify(g, s, nullptr) != HYPERIM_OK) return nullptr;
+    return g;
+}
+
+// The shared workspace is one stream's at a time: no call queues work on its
+// stream while an earlier call's work waits on another.
+int streams() {
+    constexpr int kThreads = 3, kCalls = 20;
+    hyperim_graph g[kThreads];
+    hyperim_pool p[kThreads], q[kThreads];
+    for (int t = 0; t < kThreads; ++t) {
+        g[t] = pairs(50000 + 1000 * t, stream(t));
+        NEED(g[t], "graph");
+        NEED(hyperim_pool_create(g[t], nullptr, 0, 0, &p[t]) == HYPERIM_OK, "pool");
+        NEED(hyperim_pool_create(g[t], nullptr, 0, 0, &q[t]) == HYPERIM_OK, "pool");
+    }
+    (void)hipDeviceSynchronize();
+    fake::sync_us = 300;
+    fake::watch = true;
+    int bad[kThreads] = {};
+    std::vector<std::thread> ts;
+    for (int t = 0; t < kThreads; ++t)
+        ts.emplace_back([&, t] {
+            for (uint64_t i = 0; i < kCalls; ++i) {
+                bad[t] |= hyperim_generate_rr(g[t], 7, 0, 0, 100 * i, 100 * i + 100, p[t], stream(t));
+                hyperim_rr_task task{g[t], q[t], 7, 0, 1, 100 * i, 100 * i + 100};
+                bad[t] |= hyperim_generate_rr_batch(&task, 1, (uint32_t)(i & 1), stream(t));
+                uint32_t seeds[2];
+                uint64_t gains[2], cov;
+                bad[t] |= hyperim_greedy(g[t], p[t], 100, 2, stream(t), seeds, gains);
+                bad[t] |= hyperim_stratify(g[t], stream(t), nullptr);
+            }
+        });
+    for (auto &x : ts) x.join();
+    fake::watch = false;
+    for (int t = 0; t < kThreads; ++t) NEED(bad[t] == 0, "thread %d: a call failed", t);
+    NEED(fake::overlaps == 0, "%ld times", fake::overlaps.load());
+    printf("ok %ld launches\n", fake::launches.load());
+    return 0;
+}
+
+}  // namespace
+
+int main(int argc, char **argv) {
+    const char *what = argc > 1 ? argv[1] : "";
+    if (!strcmp(what, "streams")) return streams();
+    printf("unknown scenario '%s'\n", what);
+    return 2;
+}
