@@ -2625,11 +2625,39 @@ int slot_layout(uint32_t n_max, SlotLayout *out) {
     return HYPERIM_OK;
 }
 
-// Slots sized for graphs of up to n_max vertices (re-created when a larger
-// graph arrives).
-int ensure_workspace(RRWorkspace &ws, uint32_t n_max, hipStream_t s, LaunchShape *shape) {
-    const bool lds = n_max <= kLdsBitmapWords * 32u;
+// Allocates what ensure_workspace lays out for graphs of up to n_max vertices;
+// the workspace counts as laid out (ws.grid) once everything is there and the
+// bitmaps are clear.
+int lay_out(RRWorkspace &ws, uint32_t n_max, hipStream_t s) {
     const uint32_t words = (uint32_t)(((uint64_t)n_max + 31u) / 32u);
+    SlotLayout L;
+    HIM_CHECK(slot_layout(n_max, &L));
+    HIM_CHECK(ws.lists.reserve(sizeof(uint32_t) * (size_t)L.slots * n_max, s));
+    HIM_CHECK(ws.bitmaps.reserve(sizeof(uint32_t) * (size_t)L.slots * words, s));
+    HIM_CHECK(ws.counters.reserve(sizeof(unsigned long long) * kCtrWords, s));
+    // deferred-set arrays for as many sets as there are slots (phase A may
+    // run fewer waves than the occupancy allows, leaving more spare slots)
+    const size_t ndef = L.slots;
+    HIM_CHECK(ws.def_idx.reserve(sizeof(uint64_t) * ndef, s));
+    HIM_CHECK(ws.def_u32.reserve(sizeof(uint32_t) * 5 * ndef, s));
+    HIM_CHECK(ws.items.reserve(sizeof(uint4) * (size_t)kItemCap, s));
+    HIM_CHECK(ws.args_dev.reserve(sizeof(RRArgs), s));
+    HIM_HIP(hipMemsetAsync(ws.bitmaps.ptr, 0, sizeof(uint32_t) * (size_t)L.slots * words, s));
+    ws.grid = (uint32_t)L.grid;
+    ws.grid_lds = (uint32_t)L.grid_lds;
+    ws.waves = (uint32_t)L.waves;
+    ws.slots = (uint32_t)L.slots;
+    ws.grid_b = (uint32_t)L.grid_b;
+    ws.cus = L.cus;
+    ws.slot_n = n_max;
+    ws.slot_words = words;
+    return HYPERIM_OK;
+}
+
+// Slots sized for graphs of up to n_max (at least 1) vertices, re-created when a
+// larger graph arrives.  When the memory for them is not there, nothing of them
+// stays and the next call starts over.
+int ensure_workspace(RRWorkspace &ws, uint32_t n_max, hipStream_t s, LaunchShape *shape) {
     if (ws.grid != 0 && ws.slot_n < n_max) {
         HIM_HIP(hipStreamSynchronize(s));
         ws.lists.release();
@@ -2637,29 +2665,14 @@ int ensure_workspace(RRWorkspace &ws, uint32_t n_max, hipStream_t s, LaunchShape
         ws.grid = 0;
     }
     if (ws.grid == 0) {
-        SlotLayout L;
-        HIM_CHECK(slot_layout(n_max, &L));
-        const uint64_t grid = L.grid, waves = L.waves, slots = L.slots;
-        ws.grid = (uint32_t)grid;
-        ws.waves = (uint32_t)waves;
-        ws.slots = (uint32_t)slots;
-        ws.grid_b = (uint32_t)L.grid_b;
-        ws.cus = L.cus;
-        ws.slot_n = std::max<uint32_t>(n_max, 1);
-        ws.slot_words = words;
-        ws.grid_lds = (uint32_t)L.grid_lds;
-        HIM_CHECK(ws.lists.reserve(sizeof(uint32_t) * (size_t)slots * ws.slot_n, s));
-        HIM_CHECK(ws.bitmaps.reserve(sizeof(uint32_t) * (size_t)slots * words, s));
-        HIM_HIP(hipMemsetAsync(ws.bitmaps.ptr, 0, sizeof(uint32_t) * (size_t)slots * words, s));
-        HIM_CHECK(ws.counters.reserve(sizeof(unsigned long long) * kCtrWords, s));
-        // deferred-set arrays for as many sets as there are slots (phase A may
-        // run fewer waves than the occupancy allows, leaving more spare slots)
-        const size_t ndef = slots;
-        HIM_CHECK(ws.def_idx.reserve(sizeof(uint64_t) * ndef, s));
-        HIM_CHECK(ws.def_u32.reserve(sizeof(uint32_t) * 5 * ndef, s));
-        HIM_CHECK(ws.items.reserve(sizeof(uint4) * (size_t)kItemCap, s));
-        HIM_CHECK(ws.args_dev.reserve(sizeof(RRArgs), s));
+        const int rc = lay_out(ws, n_max, s);
+        if (rc != HYPERIM_OK) {
+            ws.lists.release();
+            ws.bitmaps.release();
+            return rc;
+        }
     }
+    const bool lds = n_max <= kLdsBitmapWords * 32u;
     shape->grid = lds ? ws.grid_lds : ws.grid;
     shape->slots = ws.slots;
     shape->grid_b = ws.grid_b;

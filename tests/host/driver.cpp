@@ -74,11 +74,53 @@ int streams() {
     return 0;
 }
 
+// Memory that runs out at the i-th allocation of a generation call: the call
+// says so, and the next one, with memory again, finds or makes everything that
+// a first call makes.
+int workspace_nomem() {
+    hyperim_graph g = pairs(50000, nullptr);
+    NEED(g, "graph");
+    auto generate = [&]() {
+        hyperim_pool p = nullptr;
+        fake::fail_from = -1;
+        if (hyperim_pool_create(g, nullptr, 0, 0, &p) != HYPERIM_OK) return -100;
+        const int rc = hyperim_generate_rr(g, 7, 0, 0, 0, 500, p, nullptr);
+        hyperim_pool_free(p);
+        return rc;
+    };
+    NEED(generate() == HYPERIM_OK, "first run");   // (sizes the stage by a guess; later ones know the sets)
+    NEED(hyperim_workspace_release() == HYPERIM_OK, "release");
+    NEED(generate() == HYPERIM_OK, "clean run");
+    size_t want = 0, got = 0;
+    hyperim_workspace_info(&want);
+    int failed = 0;
+    for (long i = 0;; ++i) {
+        NEED(hyperim_workspace_release() == HYPERIM_OK, "release");
+        hyperim_pool p = nullptr;
+        NEED(hyperim_pool_create(g, nullptr, 0, 0, &p) == HYPERIM_OK, "pool");
+        fake::fail_from = fake::mallocs + i;
+        const int rc = hyperim_generate_rr(g, 7, 0, 0, 0, 500, p, nullptr);
+        fake::fail_from = -1;
+        hyperim_pool_free(p);
+        if (rc == HYPERIM_OK) break;
+        NEED(rc == HYPERIM_ENOMEM, "allocation %ld: status %d", i, rc);
+        ++failed;
+        NEED(generate() == HYPERIM_OK, "after a failure of allocation %ld", i);
+        hyperim_workspace_info(&got);
+        NEED(got == want, "after a failure of allocation %ld: %zu bytes of workspace instead of %zu", i, got, want);
+    }
+    NEED(failed > 10, "%d allocations failed", failed);
+    hyperim_graph_free(g);
+    printf("ok %d\n", failed);
+    return 0;
+}
+
 }  // namespace
 
 int main(int argc, char **argv) {
     const char *what = argc > 1 ? argv[1] : "";
     if (!strcmp(what, "streams")) return streams();
+    if (!strcmp(what, "workspace_nomem")) return workspace_nomem();
     printf("unknown scenario '%s'\n", what);
     return 2;
 }

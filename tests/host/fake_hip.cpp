@@ -47,6 +47,11 @@ struct Config {
 thread_local Config config;
 }  // namespace
 
+bool fake::live(const void *p) {
+    std::lock_guard<std::mutex> l(mu);
+    return blocks.count(const_cast<void *>(p)) != 0;
+}
+
 #define FAKE extern "C" __attribute__((visibility("default")))
 
 FAKE hipError_t __hipPushCallConfiguration(dim3 g, dim3 b, size_t sh, hipStream_t s) {

@@ -14,4 +14,5 @@ extern std::atomic<bool> watch;                 // count `overlaps` ...
 extern std::atomic<long> overlaps;              // ... work queued while another stream had some left
 extern std::atomic<int> sync_us;                // how long waiting for a busy stream takes
 extern std::atomic<void (*)()> on_device_sync;  // called within every hipDeviceSynchronize
+bool live(const void *p);                       // whether p is the start of a block not freed yet
 }  // namespace fake

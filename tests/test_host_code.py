@@ -33,3 +33,7 @@ def _run(exe, scenario):
 
 def test_workspace_belongs_to_one_stream_at_a_time(driver):
     _run(driver, "streams")
+
+
+def test_workspace_after_memory_ran_out(driver):
+    _run(driver, "workspace_nomem")
