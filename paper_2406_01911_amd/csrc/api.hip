@@ -173,21 +173,21 @@ int pool_reserve(hyperim_pool p, uint64_t ids, uint64_t entries, hipStream_t s) 
     }
     if (need_ids > p->id_cap) {
         const uint64_t ic = std::max<uint64_t>(need_ids, p->id_cap * 2);
+        // each pointer follows its buffer at once: the next one may not be had
         HIM_CHECK(p->off_b.reserve(sizeof(uint64_t) * (ic + 1), s, true));
+        p->off = p->off_b.as<uint64_t>();
         HIM_CHECK(p->roots_b.reserve(sizeof(uint32_t) * ic, s, true));
+        p->roots = p->roots_b.as<uint32_t>();
         p->id_cap = ic;
     }
     if (need_mem > p->mem_cap) {
         const uint64_t mc = std::max<uint64_t>(need_mem, p->mem_cap + p->mem_cap / 2);
         HIM_CHECK(p->mem_b.reserve(sizeof(uint32_t) * std::max<uint64_t>(mc, 1), s, true));
+        p->mem = p->mem_b.as<uint32_t>();
         p->mem_cap = mc;
     }
-    p->off = p->off_b.as<uint64_t>();
-    p->roots = p->roots_b.as<uint32_t>();
-    p->mem = p->mem_b.as<uint32_t>();
     return HYPERIM_OK;
 }
-
 
 // Per-device RR workspace (created on first use, kept until the process ends
 // or hyperim_workspace_release).

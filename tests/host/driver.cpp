@@ -115,12 +115,48 @@ int workspace_nomem() {
     return 0;
 }
 
+// Memory that runs out while a pool grows: the pool keeps what it held, at
+// addresses that are still its own, and takes the sets when asked again.
+int pool_nomem() {
+    hyperim_graph g = pairs(4000, nullptr);
+    NEED(g, "graph");
+    int failed = 0;
+    for (long i = 0;; ++i) {
+        hyperim_pool p = nullptr;
+        NEED(hyperim_pool_create(g, nullptr, 0, 0, &p) == HYPERIM_OK, "pool");
+        NEED(hyperim_generate_rr(g, 7, 0, 0, 0, 900, p, nullptr) == HYPERIM_OK, "first ids");
+        NEED(hyperim_workspace_release() == HYPERIM_OK, "release");   // freed blocks do not stay either
+        fake::fail_from = fake::mallocs + i;
+        const int rc = hyperim_generate_rr(g, 7, 0, 0, 900, 60000, p, nullptr);
+        fake::fail_from = -1;
+        NEED(hyperim_workspace_release() == HYPERIM_OK, "release");
+        const uint64_t *off = nullptr;
+        const uint32_t *mem = nullptr, *roots = nullptr;
+        uint64_t count = 0;
+        NEED(hyperim_pool_view(p, &off, &mem, &roots, nullptr, &count) == HYPERIM_OK, "view");
+        NEED(fake::live(off) && fake::live(mem) && fake::live(roots), "storage after a failure of allocation %ld", i);
+        if (rc != HYPERIM_OK) {
+            NEED(rc == HYPERIM_ENOMEM && count == 900, "allocation %ld: status %d, %llu sets", i, rc,
+                 (unsigned long long)count);
+            NEED(hyperim_generate_rr(g, 7, 0, 0, 900, 60000, p, nullptr) == HYPERIM_OK, "again");
+            ++failed;
+        }
+        hyperim_pool_free(p);
+        if (rc == HYPERIM_OK) break;
+    }
+    NEED(failed > 10, "%d allocations failed", failed);
+    hyperim_graph_free(g);
+    printf("ok %d\n", failed);
+    return 0;
+}
+
 }  // namespace
 
 int main(int argc, char **argv) {
     const char *what = argc > 1 ? argv[1] : "";
     if (!strcmp(what, "streams")) return streams();
     if (!strcmp(what, "workspace_nomem")) return workspace_nomem();
+    if (!strcmp(what, "pool_nomem")) return pool_nomem();
     printf("unknown scenario '%s'\n", what);
     return 2;
 }

@@ -37,3 +37,7 @@ def test_workspace_belongs_to_one_stream_at_a_time(driver):
 
 def test_workspace_after_memory_ran_out(driver):
     _run(driver, "workspace_nomem")
+
+
+def test_pool_after_memory_ran_out(driver):
+    _run(driver, "pool_nomem")
