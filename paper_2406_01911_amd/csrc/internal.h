@@ -190,6 +190,7 @@ struct hyperim_graph_s {
     // lay_ln[l] = ln(l + 1), lay_expm[l (l - 1) / 2 + i - 1] = e^-P(L_i)
     hyperim::DevBuf lay_nb_off, lay_nb, lay_ly_off, lay_ly_end, lay_ln, lay_expm;
     uint32_t lay_lmax = 0;
+    bool lay_ready = false;    // all of them are there
     bool stratified = false;
     uint32_t strat_lmax = 0;   // largest l_v (set by stratify)
     // division of the RR sets into R1 / R2 (Section 4.1; hyperim_route):

@@ -425,6 +425,7 @@ int layers_build_device(hyperim_graph g, PrepWorkspace &w, uint32_t lmax, hipStr
     HIM_HIP(hipMemcpyAsync(g->lay_expm.ptr, expm.data(), sizeof(double) * expm.size(), hipMemcpyHostToDevice, s));
     HIM_HIP(hipStreamSynchronize(s));   // ln and expm are the copies' sources
     g->lay_lmax = lmax;
+    g->lay_ready = true;
     return HYPERIM_OK;
 }
 

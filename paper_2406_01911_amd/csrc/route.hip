@@ -69,8 +69,8 @@ int route_build(hyperim_graph g, PrepWorkspace &w, hipStream_t s, uint32_t *n1) 
     *n1 = 0;
     g->routed = false;
     const uint32_t n = g->n;
-    if (!g->lay_nb_off.ptr) {
-        if (!g->chan.ptr) {
+    if (!g->lay_ready) {
+        if (!g->layered()) {   // those have it from the start
             DevBuf cnt, tmp;
             HIM_CHECK(channel_prefix(g, cnt, tmp, s));
             HIM_HIP(hipStreamSynchronize(s));

@@ -26,14 +26,14 @@ namespace {
 hipStream_t stream(int i) { return reinterpret_cast<hipStream_t>((uintptr_t)(16 * (i + 1))); }
 
 // n vertices in hyperedges of two.
-hyperim_graph pairs(uint32_t n, hipStream_t s, uint32_t model = HYPERIM_MODEL_CONST) {
+hyperim_graph pairs(uint32_t n, hipStream_t s, uint32_t model = HYPERIM_MODEL_CONST, bool stratify = true) {
     std::vector<uint32_t> off(n / 2 + 1), mem(n / 2 * 2);
     for (uint32_t e = 0; e <= n / 2; ++e) off[e] = 2 * e;
     for (uint32_t v = 0; v < mem.size(); ++v) mem[v] = v;
     hyperim_prob p{model, 0.5f};
     hyperim_graph g = nullptr;
     if (hyperim_build_graph(n, n / 2, off.data(), mem.data(), 0, p, s, &g) != HYPERIM_OK) return nullptr;
-    if (hyperim_stratify(g, s, nullptr) != HYPERIM_OK) return nullptr;
+    if (stratify && hyperim_stratify(g, s, nullptr) != HYPERIM_OK) return nullptr;
     return g;
 }
 
@@ -150,6 +150,53 @@ int pool_nomem() {
     return 0;
 }
 
+// Memory that runs out while the layer tables are built: a later call builds
+// them again instead of taking what there is of them.
+int tables_nomem() {
+    // route: tables of a coin graph; stratify: of a stratified-setting graph,
+    // which generates nothing until a call succeeds
+    for (uint32_t model : {HYPERIM_MODEL_CONST, HYPERIM_MODEL_LAYERED}) {
+        const bool route = model == HYPERIM_MODEL_CONST;
+        size_t want = 0;
+        int failed = 0;
+        for (long i = -1;; ++i) {   // -1: nothing fails
+            NEED(hyperim_workspace_release() == HYPERIM_OK, "release");   // no block of an earlier graph
+            hyperim_graph g = pairs(4000, nullptr, model, route);
+            NEED(g, "graph");
+            auto call = [&]() {
+                return route ? hyperim_route(g, 1, nullptr, nullptr) : hyperim_stratify(g, nullptr, nullptr);
+            };
+            int rc = HYPERIM_OK;
+            if (i >= 0) {
+                fake::fail_from = fake::mallocs + i;
+                rc = call();
+                fake::fail_from = -1;
+            }
+            const bool last = i >= 0 && rc == HYPERIM_OK;
+            if (rc != HYPERIM_OK) {
+                ++failed;
+                NEED(rc == HYPERIM_ENOMEM, "allocation %ld: status %d", i, rc);
+                if (!route) {
+                    hyperim_pool p = nullptr;
+                    NEED(hyperim_pool_create(g, nullptr, 0, 0, &p) == HYPERIM_OK, "pool");
+                    NEED(hyperim_generate_rr(g, 7, 0, 0, 0, 5, p, nullptr) == HYPERIM_ESTATE, "allocation %ld", i);
+                    hyperim_pool_free(p);
+                }
+            }
+            if (!last) NEED(call() == HYPERIM_OK, "allocation %ld", i);
+            NEED(hyperim_workspace_release() == HYPERIM_OK, "release");
+            if (i < 0) want = fake::live_blocks();
+            NEED(fake::live_blocks() == want, "after a failure of allocation %ld: a graph of %zu arrays instead of %zu",
+                 i, fake::live_blocks(), want);
+            hyperim_graph_free(g);
+            if (last) break;
+        }
+        NEED(failed > 5, "%d allocations failed", failed);
+    }
+    printf("ok both models\n");
+    return 0;
+}
+
 }  // namespace
 
 int main(int argc, char **argv) {
@@ -157,6 +204,7 @@ int main(int argc, char **argv) {
     if (!strcmp(what, "streams")) return streams();
     if (!strcmp(what, "workspace_nomem")) return workspace_nomem();
     if (!strcmp(what, "pool_nomem")) return pool_nomem();
+    if (!strcmp(what, "tables_nomem")) return tables_nomem();
     printf("unknown scenario '%s'\n", what);
     return 2;
 }

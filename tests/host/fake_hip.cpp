@@ -47,6 +47,10 @@ struct Config {
 thread_local Config config;
 }  // namespace
 
+size_t fake::live_blocks() {
+    std::lock_guard<std::mutex> l(mu);
+    return blocks.size();
+}
 bool fake::live(const void *p) {
     std::lock_guard<std::mutex> l(mu);
     return blocks.count(const_cast<void *>(p)) != 0;

@@ -41,3 +41,7 @@ def test_workspace_after_memory_ran_out(driver):
 
 def test_pool_after_memory_ran_out(driver):
     _run(driver, "pool_nomem")
+
+
+def test_layer_tables_after_memory_ran_out(driver):
+    _run(driver, "tables_nomem")
