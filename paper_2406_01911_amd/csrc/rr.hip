@@ -176,7 +176,7 @@ struct RRArgs {
     uint32_t ntasks, qlog;
     uint32_t heavy, budget, chunk, seg, prefilter_min;   // execution parameters
     uint32_t slot_n, slot_words;     // slot list length and bitmap words (largest graph)
-    uint32_t take, stage_step;       // launch indices and stage entries a wave reserves at a time
+    uint32_t take, stage_step;       // launch indices and stage entries a wave reserves at a time (0: a set's)
     uint32_t free0;                  // first slot no wave owns
     uint64_t count;                  // launch indices [0, count)
     uint64_t out_base;               // per-id array index of launch index 0
@@ -812,16 +812,21 @@ struct WorkShare {
     }
 };
 
-// A wave's room in the stage, a.stage_step entries or a set at a time.
+// A wave's room in the stage: a.stage_step entries at a time for sets of at most
+// an eighth of that, so that less than an eighth of a step is left when the next
+// one does not fit; larger sets reserve their own.  (Reservations meet at one
+// counter, at 7.5 ns each.)
 struct StageRoom {
     uint64_t at = 0, end = 0;
     __device__ __forceinline__ uint64_t take(const RRArgs &a, uint32_t size) {
-        if (end - at < size) {
-            const uint32_t step = max(size, a.stage_step);
+        const bool own = size > a.stage_step / 8u;
+        if (own || end - at < size) {
             unsigned long long got = 0;
-            if (lane_id() == 0) got = atomicAdd(&a.ctr[kBump], (unsigned long long)step);
-            at = uni64(wave_bcast64(got, 0));
-            end = at + step;
+            if (lane_id() == 0) got = atomicAdd(&a.ctr[kBump], (unsigned long long)(own ? size : a.stage_step));
+            got = uni64(wave_bcast64(got, 0));
+            if (own) return got;
+            at = got;
+            end = at + a.stage_step;
         }
         const uint64_t off = at;
         at += size;
@@ -3579,7 +3584,11 @@ int rr_generate_into(RRWorkspace &ws, RRStats &st, const std::vector<RRTask> &ta
         for (int attempt = 0; attempt < 2 && !staged; ++attempt) {
             a.stage = ws.stage.as<uint32_t>();
             a.stage_cap = ws.stage.bytes / sizeof(uint32_t);
-            a.stage_step = (uint32_t)std::min<uint64_t>(256, a.stage_cap >> 18);   // at most 1/32 of it unused
+            // Of the stage, what the waves have left at the end is at most 1/32
+            // (8192 waves), what they left between steps at most a seventh of
+            // the members staged that way.  A second attempt leaves nothing:
+            // it needs no more than the first one asked for.
+            a.stage_step = attempt ? 0u : (uint32_t)std::min<uint64_t>(256, a.stage_cap >> 18);
             HIM_HIP(hipMemsetAsync(ctr, 0, sizeof(unsigned long long) * kCtrWords, s));
             RRStats run{};
             if (ms)
