@@ -398,8 +398,10 @@ int hyperim_select_seeds_batch(const hyperim_query *queries, uint32_t count, con
  * Admission (at each step, in submission order) keeps the device bytes of
  * the graphs in use, the resident pools, the greedy workspaces and the RR
  * workspace within hbm_budget (0 = the device's memory less 8 GiB), using a
- * learned members-per-RR-set estimate; idle pools are evicted least recently
- * used first; a running query whose next round does not fit waits; a query
+ * learned members-per-RR-set estimate.  What does not fit is made to: freed
+ * memory kept for the next allocation and the scratch of graph preparation are
+ * given back, RR slots of graphs up to 32768 vertices are laid out in less
+ * memory, and idle pools are evicted least recently used first; a running query whose next round does not fit waits; a query
  * that cannot fit even alone fails with HYPERIM_ECAPACITY.  Results are those
  * of hyperim_select_seeds on the query alone.  `opt` applies to every query
  * (theta_fixed, form, qlog, max_entries, flags).  A session handle must not

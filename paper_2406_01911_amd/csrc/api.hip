@@ -109,6 +109,10 @@ size_t cached_bytes(int device) {
     return c->held;
 }
 
+void flush_cached(int device) {
+    if (BlockCache *c = block_cache(device)) c->flush();
+}
+
 int DevBuf::reserve(size_t need, hipStream_t s, bool keep) {
     if (need <= bytes && ptr) return HYPERIM_OK;
     size_t want = std::max<size_t>(need, bytes + bytes / 2);
@@ -253,6 +257,12 @@ void RRWorkspace::drop_graphs() {
     batch_graphs.clear();
 }
 
+void RRWorkspace::drop_slots() {
+    lists.release();
+    bitmaps.release();
+    grid = 0;
+}
+
 void RRWorkspace::release() {
     drop_graphs();
     if (capture) (void)hipStreamDestroy(capture);
@@ -290,7 +300,7 @@ size_t GreedyWorkspace::bytes() const {
 }
 
 SharedBytes shared_bytes() {
-    SharedBytes b{0, 0, 0, 0, 0};
+    SharedBytes b;
     int device = 0;
     if (hipGetDevice(&device) != hipSuccess) return b;
     DeviceLock lk(device);
@@ -299,7 +309,19 @@ SharedBytes shared_bytes() {
     b.greedy = lk.gr->bytes();
     b.prep = lk.prep->bytes();
     b.total = b.slots + b.stage + b.greedy + b.prep;
+    b.lean = lk.rr->lean;
+    b.slot_n = lk.rr->grid ? lk.rr->slot_n : 0;
     return b;
+}
+
+void release_shared(bool slots) {
+    int device = 0;
+    if (hipGetDevice(&device) != hipSuccess) return;
+    DeviceLock lk(device);
+    lk.prep->release();
+    if (!slots) return;
+    lk.rr->drop_slots();
+    lk.rr->stage.release();
 }
 
 size_t graph_bytes(hyperim_graph g) {
@@ -362,7 +384,7 @@ size_t pool_bytes(const hyperim_pool_s &p) { return p.off_b.bytes + p.roots_b.by
 // (tasks with an empty id range are skipped).
 int generate_into(const std::vector<RRTask> &tasks, const std::vector<hyperim_pool> &pools, uint32_t qlog, int form,
                   uint64_t max_entries, hipStream_t s, RRStats &st, std::vector<int> *pool_status,
-                  bool time_kernels, bool graphs, hipEvent_t end) {
+                  bool time_kernels, bool graphs, hipEvent_t end, bool lean) {
     std::vector<RRTask> live;
     std::vector<hyperim_pool> dst;
     std::vector<size_t> which;
@@ -387,7 +409,7 @@ int generate_into(const std::vector<RRTask> &tasks, const std::vector<hyperim_po
     std::vector<int> status;
     const uint64_t stage_budget = (uint64_t)std::max<uint32_t>(live[0].g->tune.stage_mib, 64) << 20;
     HIM_CHECK(rr_generate_into(*lk.rr, st, live, dst, qlog, form, max_entries, stage_budget, s, status,
-                               time_kernels, graphs));
+                               time_kernels, graphs, lean));
     if (end) HIM_HIP(hipEventRecord(end, s));
     HIM_CHECK(lk.drain());   // the last group's sets are on their way from the workspace to the pools
     int first_fail = HYPERIM_OK;
@@ -765,7 +787,7 @@ int hyperim_workspace_release(void) {
     lk.rr->release();
     lk.gr->release();
     lk.prep->release();
-    if (BlockCache *c = block_cache(device)) c->flush();
+    flush_cached(device);
     return HYPERIM_OK;
 }
 

@@ -47,8 +47,10 @@ struct DevBuf {
     T *as() const { return static_cast<T *>(ptr); }
 };
 
-// Bytes of freed device blocks that the library keeps for its next allocations.
+// Bytes of freed device blocks that the library keeps for its next allocations,
+// and their return to the device.
 size_t cached_bytes(int device);
+void flush_cached(int device);
 
 // Workspace of RR generation: one per device, shared by every graph on it
 // (calls that use it hold its lock).
@@ -60,6 +62,7 @@ struct RRWorkspace {
     uint32_t cus = 0;            // compute units of the device
     uint32_t slot_n = 0, slot_words = 0;  // slot list length / bitmap words (largest graph so far)
     uint32_t grid_lds = 0;       // ... with bitmaps in LDS (launches of small graphs only)
+    bool lean = false;           // laid out in less memory than usual
     DevBuf lists;                // slots * slot_n     : member list / BFS queue per slot
     DevBuf bitmaps;              // slots * slot_words : visited bitmap per slot
     DevBuf def_idx;              // deferred sets: launch index (uint64)
@@ -89,6 +92,7 @@ struct RRWorkspace {
     hipStream_t capture = nullptr;   // stream the batches are captured on
     bool graphs_off = false;         // capture failed on this device: launch kernels directly
     void drop_graphs();
+    void drop_slots();
     unsigned long long *host = nullptr;  // pinned host staging: counter copies, descriptors, totals
     size_t host_words = 0;
     size_t bytes() const;        // device memory held
@@ -254,9 +258,14 @@ int pool_init_owned(hyperim_graph g, hyperim_pool p, hipStream_t s);
 // Current bytes of the device's shared workspaces: RR slots (lists and
 // bitmaps), RR stage and per-set arrays, greedy / coverage.
 struct SharedBytes {
-    size_t slots, stage, greedy, prep, total;
+    size_t slots = 0, stage = 0, greedy = 0, prep = 0, total = 0;
+    bool lean = false;        // the slots' layout
+    uint32_t slot_n = 0;      // vertices of the largest graph it serves
 };
 SharedBytes shared_bytes();
+// Give back what graph preparation keeps for its next call, and with `slots`
+// the RR slots and the stage (the next generation makes them again).
+void release_shared(bool slots);
 void pool_clear(hyperim_pool p);                           // empty, keeps storage
 void pool_release(hyperim_pool p);                         // empty, frees owned storage
 size_t pool_bytes(const hyperim_pool_s &p);
@@ -266,12 +275,13 @@ struct RRTask;
 // ranges skipped).  With pool_status, a pool that would exceed max_entries
 // gets HYPERIM_ECAPACITY there and the others are still filled; without it
 // that status is returned.  Returns after the stream has drained.
+// lean: if the workspace is laid out anew, in less memory (see rr_slot_bytes).
 // time_kernels: time every expansion-kernel launch (RRStats::ms_expand).
 // graphs: replay captured superstep batches (HIP graphs) where the device allows.
 // end (may be null): recorded behind the pass's work.
 int generate_into(const std::vector<RRTask> &tasks, const std::vector<hyperim_pool> &pools, uint32_t qlog, int form,
                   uint64_t max_entries, hipStream_t s, RRStats &st, std::vector<int> *pool_status,
-                  bool time_kernels = false, bool graphs = true, hipEvent_t end = nullptr);
+                  bool time_kernels = false, bool graphs = true, hipEvent_t end = nullptr, bool lean = false);
 
 // ---- launchers (graph.hip) --------------------------------------------------
 int graph_build_device(hyperim_graph g, PrepWorkspace &w, hipStream_t s);
@@ -312,12 +322,13 @@ struct RRTask {
 // bytes.  pool_status[i] = HYPERIM_ECAPACITY when pools[i] would exceed
 // max_entries (its remaining sets are dropped; the other pools go on).
 // Bytes of slot lists and bitmaps the workspace holds for graphs of up to
-// n_max vertices.
-size_t rr_slot_bytes(uint32_t n_max);
+// n_max vertices; lean: as little as it gets along with (graphs whose marks
+// fit LDS; the same for others).
+size_t rr_slot_bytes(uint32_t n_max, bool lean);
 int rr_generate_into(RRWorkspace &ws, RRStats &st, const std::vector<RRTask> &tasks,
                      const std::vector<hyperim_pool> &pools, uint32_t qlog, int form, uint64_t max_entries,
                      uint64_t stage_budget, hipStream_t s, std::vector<int> &pool_status, bool time_kernels,
-                     bool graphs);
+                     bool graphs, bool lean);
 // Make room in pool p for `ids` more ids and `entries` more members.
 int pool_reserve(hyperim_pool p, uint64_t ids, uint64_t entries, hipStream_t s);
 // Work of the pool's first theta sets, summed over their members v:

@@ -227,9 +227,11 @@ size_t device_shared_bytes() {
 // time.  With a finite budget, queries are admitted in submission order while
 // the estimated device bytes fit (see hyperim_session_create).
 struct Engine {
+    int device = 0;
     hipStream_t stream = nullptr;
     hyperim_options opt{};
     size_t budget = ~(size_t)0;
+    bool lean = false;   // small graphs' RR slots in less memory: the budget asked for it
     uint64_t steps = 0;
     std::deque<QueryRun *> waiting;
     std::vector<QueryRun *> active;   // admission order
@@ -282,6 +284,7 @@ struct Engine {
         uint32_t n_max = 0;      // largest graph of the step (RR slots)
         double stage = 0.0;      // staged bytes of the step
         double greedy = 0.0;     // largest greedy index of the step
+        double stage_cap = 0.0;  // what the graphs' tunings allow the stage
     };
     size_t own_growth(const QueryRun *q, Shared &need) const {
         const uint64_t theta = q->next_theta(opt);
@@ -298,37 +301,42 @@ struct Engine {
             if (bytes > cur) b += bytes - cur + 4.0 * (double)pp->r[x].total;
             need.stage += 4.0 * 1.3 * add + 24.0 * (double)(theta - pp->have[x]);
         }
-        // entries of the index, an eighth more for the big sets' directory; per
-        // set stamps and lists; per vertex counts, their copy, offsets, flags
-        need.greedy = std::max(need.greedy, 4.0 * 1.13 * (double)theta * m + 17.0 * (double)theta + 31.0 * n);
+        // entries of the index (the big sets' directory takes an eighth of what
+        // these would); per set stamps and lists; per vertex counts, their copy
+        // and list, cursors, offsets, flags
+        need.greedy = std::max(need.greedy, 4.0 * 1.1 * (double)theta * m + 16.0 * (double)theta + 26.0 * n);
         need.n_max = std::max(need.n_max, q->q.graph->n);
+        need.stage_cap = std::max(need.stage_cap,
+                                  (double)((uint64_t)std::max<uint32_t>(q->q.graph->tune.stage_mib, 64) << 20));
         if (!pp->allocated && !pp->users) b += (double)graph_bytes(q->q.graph);
         return (size_t)b;
     }
 
     // Growth of the shared workspaces beyond what they hold now.
-    size_t shared_growth(const Shared &need, const SharedBytes &have, hyperim_graph g) const {
-        const double stage_cap = (double)((uint64_t)std::max<uint32_t>(g->tune.stage_mib, 64) << 20);
-        const double slots = (double)rr_slot_bytes(need.n_max);
+    size_t shared_growth(const Shared &need, const SharedBytes &have) const {
+        const double slots = (double)rr_slot_bytes(need.n_max, lean);
         double b = std::max(0.0, slots - (double)have.slots);
-        b += std::max(0.0, std::min(need.stage, stage_cap) - (double)have.stage);
+        b += std::max(0.0, std::min(need.stage, need.stage_cap) - (double)have.stage);
         b += std::max(0.0, need.greedy - (double)have.greedy);
         return (size_t)b;
     }
 
     // Free idle pools, least recently used first, until `need` more bytes fit.
     bool make_room(size_t &used, size_t need) {
-        while (used + need > budget) {
+        bool fits = used + need <= budget;
+        while (!fits) {
             PoolPair *victim = nullptr;
             for (auto &pp : pools)
                 if (pp->users == 0 && pp->allocated && (!victim || pp->last_step < victim->last_step))
                     victim = pp.get();
-            if (!victim) return false;
+            if (!victim) break;
             const size_t b = victim->bytes();
             victim->release();
             used -= std::min(used, b);
+            fits = used + need <= budget;
         }
-        return true;
+        flush_cached(device);   // the pools' memory, back to the device
+        return fits;
     }
 
     // A first sample of R1 (ids [0, Q)) for waiting queries on graphs without
@@ -360,7 +368,7 @@ struct Engine {
         HIM_HIP(hipEventRecord(ev.a, stream));
         HIM_CHECK(generate_into(tasks, dst, opt.qlog, (int)opt.form, opt.max_entries, stream, st, &status,
                                 (opt.flags & HYPERIM_FLAG_KERNEL_TIMES) != 0, (opt.flags & HYPERIM_FLAG_NO_GRAPHS) == 0,
-                                ev.b));
+                                ev.b, lean));
         HIM_HIP(hipEventElapsedTime(&ms, ev.a, ev.b));
         for (size_t i = 0; i < pps.size(); ++i) {
             if (status[i] == HYPERIM_OK)
@@ -484,7 +492,7 @@ struct Engine {
             std::vector<int> pool_status;
             HIM_CHECK(generate_into(tasks, dst, o.qlog, (int)o.form, o.max_entries, s, st, &pool_status,
                                     (o.flags & HYPERIM_FLAG_KERNEL_TIMES) != 0, (o.flags & HYPERIM_FLAG_NO_GRAPHS) == 0,
-                                    ev.b));
+                                    ev.b, lean));
             HIM_HIP(hipEventElapsedTime(&ms_rr, ev.a, ev.b));
             add_stats(total, st, ms_rr);
             for (size_t t = 0; t < tasks.size(); ++t)
@@ -498,8 +506,6 @@ struct Engine {
                 }
             }
         }
-        int device = 0;
-        HIM_HIP(hipGetDevice(&device));
         for (QueryRun *q : live) {
             size_t i = 0;
             while (pps[i] != q->pp) ++i;
@@ -583,25 +589,60 @@ struct Engine {
     // Admit what fits and run one round; `finished` receives the queries that
     // ended in this step (done or failed).
     int step(std::vector<QueryRun *> &finished, size_t *ran) {
+        HIM_HIP(hipGetDevice(&device));
         steps += 1;
         total.rounds = (uint32_t)steps;
-        size_t used = bounded() ? resident() : 0;
-        if (bounded()) HIM_CHECK(pilot(used));
-        if (bounded()) used = resident();
         std::vector<QueryRun *> run;
         Shared need;
-        const SharedBytes have = bounded() ? shared_bytes() : SharedBytes{0, 0, 0, 0, 0};
-        size_t shared_so_far = 0;
+        // bytes in use, the shared workspaces among them, and freed blocks kept
+        // beside them; what the queries admitted so far add on their own
+        SharedBytes have;
+        size_t used = 0, cached = 0, own_sum = 0;
+        auto look = [&]() {
+            used = resident();
+            have = shared_bytes();
+            cached = cached_bytes(device);
+        };
+        // While over() says that the budget does not hold: give back what nobody
+        // needs now -- freed blocks kept for the next allocation, the scratch of
+        // graph preparation -- then lay small graphs' RR slots out in less memory,
+        // from now on (n: the largest graph they are to serve).
+        auto save = [&](uint32_t n, auto &&over) {
+            if (over() && (cached || have.prep)) {
+                release_shared(false);
+                flush_cached(device);
+                look();
+            }
+            n = std::max(n, have.slot_n);
+            if (over() && rr_slot_bytes(n, true) < rr_slot_bytes(n, false) && (!lean || (have.slots && !have.lean))) {
+                lean = true;
+                if (have.slots && !have.lean) release_shared(true);
+                flush_cached(device);
+                look();
+            }
+        };
+        if (bounded()) {
+            look();
+            Shared slots;
+            for (const QueryRun *q : waiting) slots.n_max = std::max(slots.n_max, q->q.graph->n);
+            for (const QueryRun *q : active) slots.n_max = std::max(slots.n_max, q->q.graph->n);
+            save(slots.n_max, [&]() { return used + cached + shared_growth(slots, have) > budget; });
+            HIM_CHECK(pilot(used + cached + shared_growth(slots, have)));
+            look();
+        }
         auto fits = [&](QueryRun *q) {
             if (!bounded()) return true;
             Shared trial = need;
-            const size_t own = own_growth(q, trial);
-            const size_t shared = shared_growth(trial, have, q->q.graph);
-            const size_t delta = own + (shared > shared_so_far ? shared - shared_so_far : 0);
-            if (used + delta > budget && !make_room(used, delta)) return false;
+            const size_t own = own_sum + own_growth(q, trial);
+            auto over = [&]() { return used + cached + own + shared_growth(trial, have) > budget; };
+            save(trial.n_max, over);
+            if (over()) {
+                const bool room = make_room(used, own + shared_growth(trial, have));
+                cached = 0;
+                if (!room) return false;
+            }
             need = trial;
-            used += delta;
-            shared_so_far = std::max(shared, shared_so_far);
+            own_sum = own;
             return true;
         };
         // running queries first, in admission order

@@ -2598,13 +2598,18 @@ struct LaunchShape {
 
 // Slot layout for graphs of up to n_max vertices: phase A grid (from
 // occupancy), slots (phase A waves plus spare slots for deferred sets, within
-// kSlotBudget bytes) and the phase B grid.
+// kSlotBudget bytes) and the phase B grid.  80 slots per compute unit are four
+// for each wave of five workgroups there.
+// Lean, for graphs whose marks fit LDS: the bytes of 12 lists per compute unit,
+// a quarter of the slots spare (a set that finds none stays with its wave).
+// 32768 vertices: 2.8 GB of slots, 0.4 GB lean.
+constexpr uint32_t kSlotsPerCu = 80, kLeanListsPerCu = 12;
 struct SlotLayout {
     uint64_t grid, grid_lds, waves, slots, grid_b, bytes;
     uint32_t cus;
 };
 
-int slot_layout(uint32_t n_max, SlotLayout *out) {
+int slot_layout(uint32_t n_max, bool lean, SlotLayout *out) {
     int per_cu_lds = 0, per_cu_glb = 0, per_cu_b = 0, cus = 0, dev = 0;
     HIM_HIP(hipGetDevice(&dev));
     HIM_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
@@ -2615,14 +2620,18 @@ int slot_layout(uint32_t n_max, SlotLayout *out) {
     const uint64_t per_slot = (uint64_t)n_max * 4u + words * 4u;
     const uint64_t max_slots = std::max<uint64_t>(kSlotBudget / std::max<uint64_t>(per_slot, 1), 2 * kWavesPerWG);
     uint64_t grid = (uint64_t)cus * (uint64_t)std::max(per_cu_glb, 1);
+    uint64_t slots = std::min<uint64_t>(max_slots, (uint64_t)cus * kSlotsPerCu);
     // phase A keeps at least half of the slots spare for deferred sets
-    grid = std::min<uint64_t>(grid, max_slots / (2 * kWavesPerWG));
+    grid = std::min<uint64_t>(grid, slots / (2 * kWavesPerWG));
+    if (lean && n_max <= kLdsBitmapWords * 32u) {
+        const uint64_t few = (uint64_t)cus * kLeanListsPerCu * n_max * 4u / std::max<uint64_t>(per_slot, 1);
+        slots = std::min(slots, std::max<uint64_t>(few, 2 * kWavesPerWG));
+        grid = std::min(grid, slots / 4u * 3u / kWavesPerWG);
+    }
     grid = std::max<uint64_t>(grid, 1);
-    const uint64_t waves = grid * kWavesPerWG;
-    const uint64_t slots = std::min<uint64_t>(max_slots, 4 * waves);
     out->grid_lds = std::min<uint64_t>(grid, (uint64_t)cus * (uint64_t)std::max(per_cu_lds, 1));
     out->grid = grid;
-    out->waves = waves;
+    out->waves = grid * kWavesPerWG;
     out->slots = slots;
     out->grid_b = (uint64_t)cus * (uint64_t)std::max(per_cu_b, 1);
     out->bytes = slots * per_slot;
@@ -2633,10 +2642,10 @@ int slot_layout(uint32_t n_max, SlotLayout *out) {
 // Allocates what ensure_workspace lays out for graphs of up to n_max vertices;
 // the workspace counts as laid out (ws.grid) once everything is there and the
 // bitmaps are clear.
-int lay_out(RRWorkspace &ws, uint32_t n_max, hipStream_t s) {
+int lay_out(RRWorkspace &ws, uint32_t n_max, bool lean, hipStream_t s) {
     const uint32_t words = (uint32_t)(((uint64_t)n_max + 31u) / 32u);
     SlotLayout L;
-    HIM_CHECK(slot_layout(n_max, &L));
+    HIM_CHECK(slot_layout(n_max, lean, &L));
     HIM_CHECK(ws.lists.reserve(sizeof(uint32_t) * (size_t)L.slots * n_max, s));
     HIM_CHECK(ws.bitmaps.reserve(sizeof(uint32_t) * (size_t)L.slots * words, s));
     HIM_CHECK(ws.counters.reserve(sizeof(unsigned long long) * kCtrWords, s));
@@ -2656,24 +2665,23 @@ int lay_out(RRWorkspace &ws, uint32_t n_max, hipStream_t s) {
     ws.cus = L.cus;
     ws.slot_n = n_max;
     ws.slot_words = words;
+    ws.lean = lean && n_max <= kLdsBitmapWords * 32u;
     return HYPERIM_OK;
 }
 
 // Slots sized for graphs of up to n_max (at least 1) vertices, re-created when a
-// larger graph arrives.  When the memory for them is not there, nothing of them
-// stays and the next call starts over.
-int ensure_workspace(RRWorkspace &ws, uint32_t n_max, hipStream_t s, LaunchShape *shape) {
-    if (ws.grid != 0 && ws.slot_n < n_max) {
+// larger graph arrives or a caller that need not save finds a lean layout.  When
+// the memory for them is not there, nothing of them stays and the next call
+// starts over.
+int ensure_workspace(RRWorkspace &ws, uint32_t n_max, bool lean, hipStream_t s, LaunchShape *shape) {
+    if (ws.grid != 0 && (ws.slot_n < n_max || (ws.lean && !lean))) {
         HIM_HIP(hipStreamSynchronize(s));
-        ws.lists.release();
-        ws.bitmaps.release();
-        ws.grid = 0;
+        ws.drop_slots();
     }
     if (ws.grid == 0) {
-        const int rc = lay_out(ws, n_max, s);
+        const int rc = lay_out(ws, n_max, lean, s);
         if (rc != HYPERIM_OK) {
-            ws.lists.release();
-            ws.bitmaps.release();
+            ws.drop_slots();
             return rc;
         }
     }
@@ -3337,15 +3345,15 @@ int compact_move(RRWorkspace &ws, hyperim_pool p, uint64_t first, uint64_t count
 
 }  // namespace
 
-size_t rr_slot_bytes(uint32_t n_max) {
+size_t rr_slot_bytes(uint32_t n_max, bool lean) {
     SlotLayout L;
-    return slot_layout(n_max, &L) == HYPERIM_OK ? (size_t)L.bytes : 0;
+    return slot_layout(n_max, lean, &L) == HYPERIM_OK ? (size_t)L.bytes : 0;
 }
 
 int rr_generate_into(RRWorkspace &ws, RRStats &st, const std::vector<RRTask> &tasks,
                      const std::vector<hyperim_pool> &pools, uint32_t qlog, int form, uint64_t max_entries,
                      uint64_t stage_budget, hipStream_t s, std::vector<int> &pool_status, bool time_kernels,
-                     bool graphs) {
+                     bool graphs, bool lean) {
     // HYPERIM_TRACE=1: synchronise after every grid-wide superstep and report
     // its item count and time on stderr (diagnostics; same results)
     static const bool trace = [] {
@@ -3379,7 +3387,7 @@ int rr_generate_into(RRWorkspace &ws, RRStats &st, const std::vector<RRTask> &ta
     for (const RRTask &t : tasks) count += t.id_end - t.id_begin;
     if (count == 0) return HYPERIM_OK;
     LaunchShape shape;
-    HIM_CHECK(ensure_workspace(ws, n_max, s, &shape));
+    HIM_CHECK(ensure_workspace(ws, n_max, lean, s, &shape));
 
     // launch shapes: the occupancy limits, capped per compute unit by the tuning
     auto capped = [&](uint32_t full, uint32_t per_cu) {

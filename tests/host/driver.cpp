@@ -197,6 +197,51 @@ int tables_nomem() {
     return 0;
 }
 
+// A session of 1 GiB answers queries on a graph of 30000 vertices, with a fresh
+// workspace and with one that another call left laid out generously; it stays
+// within its budget, and the next call without one lays the workspace out anew.
+int small_budget() {
+    const size_t budget = 1ull << 30;
+    hyperim_graph g = pairs(30000, nullptr);
+    NEED(g, "graph");
+    size_t full = 0, now = 0;
+    for (int warm = 0; warm < 2; ++warm) {
+        NEED(hyperim_workspace_release() == HYPERIM_OK, "release");
+        if (warm) {
+            hyperim_pool p = nullptr;
+            NEED(hyperim_pool_create(g, nullptr, 0, 0, &p) == HYPERIM_OK, "pool");
+            NEED(hyperim_generate_rr(g, 7, 0, 0, 0, 500, p, nullptr) == HYPERIM_OK, "generate");
+            hyperim_pool_free(p);
+            hyperim_workspace_info(&full);
+            NEED(full > budget, "%zu bytes", full);
+        }
+        fake::peak = 0;
+        hyperim_session s = nullptr;
+        NEED(hyperim_session_create(budget, nullptr, nullptr, &s) == HYPERIM_OK, "session");
+        uint64_t ticket = 0;
+        hyperim_query q{g, 2, 0, 0.5, 1.0, 7};
+        NEED(hyperim_session_submit(s, &q, &ticket) == HYPERIM_OK, "submit");
+        int rc = HYPERIM_PENDING;
+        uint32_t seeds[2];
+        for (int i = 0; i < 100 && rc == HYPERIM_PENDING; ++i) {
+            hyperim_session_stats st;
+            NEED(hyperim_session_step(s, &st) == HYPERIM_OK, "step");
+            NEED(st.bytes_resident <= budget, "%zu bytes resident", st.bytes_resident);
+            rc = hyperim_session_poll(s, ticket, seeds, nullptr, nullptr);
+        }
+        NEED(rc == HYPERIM_OK, "warm %d: status %d: %s", warm, rc, hyperim_strerror(rc));
+        NEED(fake::peak <= budget, "warm %d: %zu bytes allocated", warm, fake::peak.load());
+        hyperim_session_free(s);
+    }
+    uint32_t seeds[2];
+    NEED(hyperim_select_seeds(g, 2, 0.5, 1.0, 7, 0, nullptr, nullptr, seeds, nullptr, nullptr) == HYPERIM_OK, "alone");
+    hyperim_workspace_info(&now);
+    NEED(now >= full, "%zu bytes laid out, %zu before", now, full);
+    hyperim_graph_free(g);
+    printf("ok %zu\n", now);
+    return 0;
+}
+
 }  // namespace
 
 int main(int argc, char **argv) {
@@ -205,6 +250,7 @@ int main(int argc, char **argv) {
     if (!strcmp(what, "workspace_nomem")) return workspace_nomem();
     if (!strcmp(what, "pool_nomem")) return pool_nomem();
     if (!strcmp(what, "tables_nomem")) return tables_nomem();
+    if (!strcmp(what, "small_budget")) return small_budget();
     printf("unknown scenario '%s'\n", what);
     return 2;
 }

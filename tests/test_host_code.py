@@ -45,3 +45,7 @@ def test_pool_after_memory_ran_out(driver):
 
 def test_layer_tables_after_memory_ran_out(driver):
     _run(driver, "tables_nomem")
+
+
+def test_small_graph_within_a_small_budget(driver):
+    _run(driver, "small_budget")
