@@ -446,8 +446,9 @@ int hyperim_workspace_release(void);
  * setting produces the same bytes).  Zero fields keep their defaults.
  *   heavy:         a set whose next frontier batch holds a vertex with more
  *                  hyperedges than this moves to the grid-wide phase (1024);
- *   budget:        ... or once it has read this many incidences (262144;
- *                  a hyperedge of a vertex and each of its members count one);
+ *   budget:        ... or once it has read this many incidences (262144), or
+ *                  that many member positions of their hyperedges where it has
+ *                  read 262144 of those, too;
  *   chunk:         incidences per heavy-vertex work item (256);
  *   seg:           light incidences per frontier-segment work item (512,
  *                  raised to chunk if smaller);

@@ -75,6 +75,12 @@ constexpr uint64_t kSlotBudget = 48ull << 30; // bytes of slot lists + bitmaps
 // chunk and segment sizes, prefilter threshold, supersteps per sync) are
 // runtime values, see hyperim_tuning.
 
+// A set also leaves the per-set phase once it has read this many member
+// positions, or the incidence budget where that is larger: hyperedges of
+// hundreds of members reach them long before the incidences (sets on hyperedges
+// of up to 1000: the per-set phase of a serving session 450 ms without, 23 with).
+constexpr uint32_t kReach = 262144;
+
 // Counters (uint64 each) in the workspace counter block.
 // kItems and kItems + 1 alternate between supersteps: superstep s plans into
 // counter s & 1 while its k_expand clears the other one for superstep s + 1.
@@ -175,6 +181,7 @@ struct RRArgs {
     const TaskDesc *tasks;
     uint32_t ntasks, qlog;
     uint32_t heavy, budget, chunk, seg, prefilter_min;   // execution parameters
+    uint32_t reach;                  // member positions of a set in the per-set phase
     uint32_t slot_n, slot_words;     // slot list length and bitmap words (largest graph)
     uint32_t take, stage_step;       // launch indices and stage entries a wave reserves at a time (0: a set's)
     uint32_t free0;                  // first slot no wave owns
@@ -903,7 +910,7 @@ __global__ __launch_bounds__(kWG) void k_rr_light(RRArgs a) {
         LocalAppend app{list, 1u, G.n};
         if (S.pool == 0u) seed_forced(a.graphs[uni(a.tasks[task].graph)], root, bm, app);
         uint32_t head = 0;
-        uint64_t spent = 0;
+        uint64_t incidences = 0, positions = 0;   // read for this set
         bool deferred = false;
 
         while (head < app.size) {
@@ -920,7 +927,7 @@ __global__ __launch_bounds__(kWG) void k_rr_light(RRArgs a) {
                 d = r[1];
                 thr = r[2];
             }
-            if (can_defer && (spent > a.budget || __ballot(d > a.heavy) != 0)) {
+            if (can_defer && (incidences > a.budget || positions > a.reach || __ballot(d > a.heavy) != 0)) {
                 // hand the set over to phase B and continue with a fresh slot
                 uint32_t fresh_slot = 0;
                 if (lane == 0) fresh_slot = (uint32_t)atomicAdd(&a.ctr[kFreeNext], 1ull);
@@ -959,9 +966,9 @@ __global__ __launch_bounds__(kWG) void k_rr_light(RRArgs a) {
             const uint64_t bytes =
                 expand<kLdsBitmap, false, kGaps>(G, L, S.j, S.pool, S.key, bm, false, v, e0, d, thr, app, px);
             bytes_done += bytes;
-            // incidences read: hyperedges and member positions, from 12 bytes
-            // per hyperedge and 4 per position
-            spent += bytes / 4u - 2ull * wave_sum(d);
+            const uint32_t read = wave_sum(d);
+            incidences += read;
+            positions += bytes / 4u - 3ull * read;   // 12 bytes per incidence, 4 per position
         }
         if (deferred) continue;
         const uint32_t size = app.size;
@@ -3444,6 +3451,7 @@ int rr_generate_into(RRWorkspace &ws, RRStats &st, const std::vector<RRTask> &ta
     a.qlog = qlog;
     a.heavy = tune.heavy;
     a.budget = tune.budget;
+    a.reach = std::max(tune.budget, kReach);
     a.chunk = tune.chunk;
     a.seg = std::max(tune.seg, tune.chunk);
     a.prefilter_min = tune.prefilter_min;
