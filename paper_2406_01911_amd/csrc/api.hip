@@ -25,9 +25,10 @@ void clear_error_detail() { g_detail.clear(); }
 // every query, took longer than many of the kernels between them (a million
 // vertices under linear threshold, from the hypergraph to 100 seeds: 12.2 ms,
 // 9.7 now).  A freed block may still be in use on any stream, so it waits until
-// the device has been synchronised once after its release (`pending`); that
+// the device has been synchronised once after its release (`settled`); that
 // happens when such a block is wanted, for all of them together, as hipFree did
-// for each.
+// for each.  The lock is not held meanwhile, nor while memory goes back to the
+// device: threads on other streams allocate and free in the meantime.
 constexpr size_t kCacheBytes = 1ull << 30;
 constexpr int kMaxDevices = 256;
 namespace {
@@ -35,60 +36,73 @@ struct BlockCache {
     struct Block {
         void *p;
         size_t size;
+        uint64_t freed;   // the number of its release
     };
+    static constexpr size_t kBlocks = 1024;   // no allocation in here: handles are freed without one
     std::mutex mu;
-    std::vector<Block> idle, pending;   // oldest first
-    size_t held = 0;
+    Block blocks[kBlocks];   // oldest first
+    size_t count = 0, held = 0;
+    uint64_t releases = 0, settled = 0;   // blocks released up to `settled` are in use nowhere
 
-    // The smallest block of `from` that `want` fills to four fifths or more.
-    static bool pick(std::vector<Block> &from, size_t want, Block *out) {
-        size_t best = from.size();
-        for (size_t i = 0; i < from.size(); ++i)
-            if (from[i].size >= want && from[i].size <= want + want / 4 + 4096 &&
-                (best == from.size() || from[i].size < from[best].size))
-                best = i;
-        if (best == from.size()) return false;
-        *out = from[best];
-        from.erase(from.begin() + (ptrdiff_t)best);
-        return true;
+    void remove(size_t i) {   // (with the lock)
+        held -= blocks[i].size;
+        for (--count; i < count; ++i) blocks[i] = blocks[i + 1];
     }
+    // The smallest block that `want` fills to four fifths or more, a settled one
+    // if there is one.  False: none.
     bool take(size_t want, Block *out) {
-        std::lock_guard<std::mutex> l(mu);
-        if (!pick(idle, want, out)) {
-            if (!pick(pending, want, out)) return false;
-            if (hipDeviceSynchronize() != hipSuccess) {   // not now: a capture is under way, or worse
-                (void)hipGetLastError();
-                pending.push_back(*out);
-                return false;
-            }
-            idle.insert(idle.end(), pending.begin(), pending.end());
-            pending.clear();
+        std::unique_lock<std::mutex> l(mu);
+        size_t best = count;
+        for (size_t i = 0; i < count; ++i) {
+            const Block &b = blocks[i];
+            if (b.size < want || b.size > want + want / 4 + 4096) continue;
+            const bool now = b.freed <= settled;
+            if (best == count || (now && blocks[best].freed > settled) ||
+                (now == (blocks[best].freed <= settled) && b.size < blocks[best].size))
+                best = i;
         }
-        held -= out->size;
+        if (best == count) return false;
+        *out = blocks[best];
+        const uint64_t last = releases;
+        const bool wait = out->freed > settled;
+        remove(best);
+        l.unlock();
+        if (!wait) return true;
+        const bool ok = hipDeviceSynchronize() == hipSuccess;   // else: a capture is under way, or worse
+        if (!ok) {
+            (void)hipGetLastError();
+            give(out->p, out->size);
+            return false;
+        }
+        l.lock();
+        settled = std::max(settled, last);
         return true;
     }
-    void give(const Block &b) {
-        std::lock_guard<std::mutex> l(mu);
-        if (b.size > kCacheBytes / 2) {
-            (void)hipFree(b.p);
+    void give(void *p, size_t size) {
+        if (size <= kCacheBytes / 2) {
+            std::unique_lock<std::mutex> l(mu);
+            while (count == kBlocks || held + size > kCacheBytes) {
+                void *oldest = blocks[0].p;
+                remove(0);
+                l.unlock();
+                (void)hipFree(oldest);   // waits for the device by itself
+                l.lock();
+            }
+            blocks[count++] = {p, size, ++releases};
+            held += size;
             return;
         }
-        while (held + b.size > kCacheBytes) {
-            std::vector<Block> &from = idle.empty() ? pending : idle;
-            held -= from.front().size;
-            (void)hipFree(from.front().p);   // waits for the device by itself
-            from.erase(from.begin());
-        }
-        pending.push_back(b);
-        held += b.size;
+        (void)hipFree(p);
     }
     void flush() {
-        std::lock_guard<std::mutex> l(mu);
-        for (std::vector<Block> *v : {&idle, &pending}) {
-            for (const Block &b : *v) (void)hipFree(b.p);
-            v->clear();
+        std::unique_lock<std::mutex> l(mu);
+        while (count) {
+            void *last = blocks[count - 1].p;
+            remove(count - 1);
+            l.unlock();
+            (void)hipFree(last);
+            l.lock();
         }
-        held = 0;
     }
 };
 
@@ -97,7 +111,7 @@ BlockCache *block_cache(int device) {   // never destroyed: handles may be freed
     static BlockCache *caches[kMaxDevices];
     if (device < 0 || device >= kMaxDevices) return nullptr;
     std::lock_guard<std::mutex> l(mu);
-    if (!caches[device]) caches[device] = new BlockCache();
+    if (!caches[device]) caches[device] = new (std::nothrow) BlockCache();
     return caches[device];
 }
 }  // namespace
@@ -120,9 +134,9 @@ int DevBuf::reserve(size_t need, hipStream_t s, bool keep) {
     int device = 0;
     HIM_HIP(hipGetDevice(&device));
     BlockCache *cache = block_cache(device);
-    BlockCache::Block b{nullptr, want};
+    BlockCache::Block b{nullptr, want, 0};
     if (!cache || !cache->take(want, &b)) {
-        b = {nullptr, want};
+        b = {nullptr, want, 0};
         hipError_t e = hipMalloc(&b.p, want);
         if (e != hipSuccess) {
             (void)hipGetLastError();
@@ -155,7 +169,7 @@ int DevBuf::reserve(size_t need, hipStream_t s, bool keep) {
 void DevBuf::release() {
     if (ptr) {
         BlockCache *cache = block_cache(dev);
-        if (cache) cache->give({ptr, block});
+        if (cache) cache->give(ptr, block);
         else (void)hipFree(ptr);
     }
     ptr = nullptr;

@@ -3,13 +3,30 @@
 #include <hip/hip_runtime_api.h>
 #include <stdint.h>
 #include <stdio.h>
+#include <stdlib.h>
 #include <string.h>
 
+#include <chrono>
+#include <future>
+#include <new>
 #include <thread>
 #include <vector>
 
 #include "fake_hip.h"
 #include "hyperim.h"
+
+namespace {
+bool no_memory = false;   // of the host
+}
+
+void *operator new(size_t n) {
+    void *p = no_memory ? nullptr : malloc(n ? n : 1);
+    if (!p) throw std::bad_alloc();
+    return p;
+}
+void *operator new(size_t n, const std::nothrow_t &) noexcept { return no_memory ? nullptr : malloc(n ? n : 1); }
+void operator delete(void *p) noexcept { free(p); }
+void operator delete(void *p, size_t) noexcept { free(p); }
 
 namespace {
 
@@ -242,6 +259,61 @@ int small_budget() {
     return 0;
 }
 
+// A pool whose storage has the size of `ids` ids.
+hyperim_pool pool_of(hyperim_graph g, uint64_t ids) {
+    hyperim_pool p = nullptr;
+    if (hyperim_pool_create(g, nullptr, 0, 0, &p) != HYPERIM_OK) return nullptr;
+    if (hyperim_generate_rr(g, 7, 0, 0, 0, ids, p, nullptr) != HYPERIM_OK) return nullptr;
+    return p;
+}
+
+hyperim_pool freed_meanwhile = nullptr;
+std::future<void> other;
+bool stuck = false;
+
+// Freed blocks: a thread that waits for the device keeps nobody else from
+// freeing; what is freed during the wait is waited for again before it serves;
+// freeing needs no memory of the host.
+int blocks() {
+    hyperim_graph g = pairs(4000, nullptr);
+    NEED(g, "graph");
+    hyperim_pool a = pool_of(g, 40000), b = pool_of(g, 90000);
+    NEED(a && b, "pools");
+    NEED(hyperim_workspace_release() == HYPERIM_OK, "release");
+    hyperim_pool_free(a);
+    freed_meanwhile = b;
+    fake::on_device_sync = [] {
+        fake::on_device_sync = nullptr;
+        other = std::async(std::launch::async, [] { hyperim_pool_free(freed_meanwhile); });
+        stuck = other.wait_for(std::chrono::seconds(5)) != std::future_status::ready;
+    };
+    long syncs = fake::device_syncs;
+    a = pool_of(g, 40000);   // in a's blocks: the device is waited for, b is freed meanwhile
+    NEED(a && fake::device_syncs > syncs, "no wait");
+    NEED(!stuck, "a free waited for another thread's wait for the device");
+    syncs = fake::device_syncs;
+    const long mallocs = fake::mallocs;
+    b = pool_of(g, 90000);
+    // pool_create waits once by itself
+    NEED(b && fake::device_syncs > syncs + 1, "a block freed during a wait served without one");
+    NEED(fake::mallocs - mallocs < 8, "%ld allocations", fake::mallocs - mallocs);
+    std::vector<hyperim_pool> many;
+    for (int i = 0; i < 200; ++i) {
+        many.push_back(nullptr);
+        NEED(hyperim_pool_create(g, nullptr, 0, 0, &many.back()) == HYPERIM_OK, "pool");
+    }
+    no_memory = true;
+    for (hyperim_pool p : many) hyperim_pool_free(p);
+    no_memory = false;
+    // blocks are given back at the latest by the release
+    hyperim_pool_free(a);
+    hyperim_pool_free(b);
+    hyperim_graph_free(g);
+    NEED(hyperim_workspace_release() == HYPERIM_OK && fake::live_blocks() == 0, "%zu blocks left", fake::live_blocks());
+    printf("ok %ld waits\n", fake::device_syncs.load());
+    return 0;
+}
+
 }  // namespace
 
 int main(int argc, char **argv) {
@@ -251,6 +323,7 @@ int main(int argc, char **argv) {
     if (!strcmp(what, "pool_nomem")) return pool_nomem();
     if (!strcmp(what, "tables_nomem")) return tables_nomem();
     if (!strcmp(what, "small_budget")) return small_budget();
+    if (!strcmp(what, "blocks")) return blocks();
     printf("unknown scenario '%s'\n", what);
     return 2;
 }

@@ -49,3 +49,7 @@ def test_layer_tables_after_memory_ran_out(driver):
 
 def test_small_graph_within_a_small_budget(driver):
     _run(driver, "small_budget")
+
+
+def test_freed_blocks(driver):
+    _run(driver, "blocks")
