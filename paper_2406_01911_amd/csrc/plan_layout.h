@@ -1,13 +1,14 @@
 // Work-item layout of the grid-wide RR-generation planners (k_plan and
 // k_ms_plan) and the progress rules of the host loops that drive them.
 //
-// A planning wave takes up to 64 frontier entries.  Light entries (at most
-// `chunk` incidences of work) form segments of consecutive entries; a heavy
-// entry is cut into chunks of its incidence range.  The items of a batch are
-// the segments first, then the heavy chunks in lane order.  These helpers are
-// the arithmetic of that layout; the device planners call them with lane
-// shuffles as the scan reader, and the host model the CPU tests exercise
-// calls them with plain arrays.
+// A planning wave takes batches of 64 frontier entries, up to kPlanBatches of
+// them per reservation of items.  Light entries (at most `chunk` incidences of
+// work) form segments of consecutive entries; a heavy entry is cut into chunks
+// of its incidence range.  The items of a batch are the segments first, then the
+// heavy chunks in lane order.  These helpers are the arithmetic of that layout
+// and the rules of what does not fit the item buffer; the device planners call
+// them with lane shuffles as the scan reader, and the host model the CPU tests
+// exercise calls them with plain arrays.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -17,6 +18,20 @@ namespace hyperim {
 
 constexpr uint32_t kPlanItemCap = 1u << 22;          // work items per superstep
 constexpr uint32_t kPlanMaxItemsPerVertex = 1u << 20;  // per-set mode: chunks of one vertex at most
+// Queue entries a planning wave takes per reservation of items, in batches of
+// 64: the reservations of all waves meet at one counter, at 7.5 ns each (sets
+// with frontiers of thousands spent 0.38 ms a superstep on them).
+constexpr uint32_t kPlanBatches = 8;
+
+// What a planning wave does when `batches` batches need `need` items and the
+// buffer holds `cap`.  Per-set mode: reserve, or plan the first batch alone, or
+// (one batch already) its first entry, whose chunks always fit.  Bundled mode:
+// one reservation for all of them, or one per batch, whose items always fit.
+enum PlanFit : int { kPlanAll = 0, kPlanOneBatch = 1, kPlanOneEntry = 2 };
+__host__ __device__ __forceinline__ PlanFit plan_fit(uint32_t need, uint32_t batches, uint32_t cap) {
+    return need <= cap ? kPlanAll : batches > 1u ? kPlanOneBatch : kPlanOneEntry;
+}
+__host__ __device__ __forceinline__ bool plan_together(uint64_t need, uint32_t cap) { return need <= cap / 2u; }
 
 // ceil(a / b) without overflow for a near 2^32
 __host__ __device__ __forceinline__ uint32_t plan_div_up(uint32_t a, uint32_t b) {
@@ -42,7 +57,9 @@ __host__ __device__ __forceinline__ HeavySplit heavy_split(uint32_t deg, uint32_
 // member positions.  Where those are more than kPlanQuads per incidence, chunks
 // are cut shorter, so that they hold about chunk * kPlanQuads runs, and a light
 // vertex weighs its runs.  (Hyperedges of up to 1000 members, chunks by
-// incidences alone: an item took up to a millisecond of one wave.)
+// incidences alone: an item took up to a millisecond of one wave.)  An incidence
+// is not divided: a chunk of one, or a light vertex of one, may hold more runs
+// than that, as many as a hyperedge has.
 constexpr uint32_t kPlanQuads = 8;
 __host__ __device__ __forceinline__ uint32_t weighted_chunk(uint32_t deg, uint32_t quads, uint32_t chunk) {
     const uint64_t even = (uint64_t)kPlanQuads * deg;
@@ -70,9 +87,9 @@ __host__ __device__ __forceinline__ HeavySplit ms_heavy_split(uint32_t deg, uint
     return h;
 }
 
-// Segment of a light entry: floor(light incidences before it / seg).  With
-// every light weight <= seg, segments have no gaps and each holds fewer than
-// 2 seg incidences of work.
+// Segment of a light entry: floor(light weight before it / seg).  A segment
+// starts where this number changes (by one or more), so every entry is in one;
+// it holds less than seg and its last entry.
 __host__ __device__ __forceinline__ uint32_t segment_of(uint32_t light_incl, uint32_t light, uint32_t seg) {
     return (light_incl - light) / seg;
 }

@@ -333,28 +333,6 @@ struct LocalAppend {
     }
 };
 
-// Same with the size in global memory (phase B: many waves grow one set).
-struct SharedAppend {
-    uint32_t *list;
-    uint32_t *size;
-    uint32_t n;
-    __device__ __forceinline__ void push8(uint32_t mask, const uint32_t (&u)[8]) {
-        const uint32_t cnt = (uint32_t)__popc(mask);
-        const uint32_t incl = wave_incl_scan(cnt);
-        const uint32_t total = uni(wave_bcast(incl, kWave - 1));
-        if (total == 0) return;
-        uint32_t base = 0;
-        if (lane_id() == kWave - 1) base = atomicAdd(size, total);
-        uint32_t at = uni(wave_bcast(base, kWave - 1)) + incl - cnt;
-#pragma unroll
-        for (uint32_t t = 0; t < 8; ++t)
-            if ((mask >> t) & 1u) {
-                if (at < n) list[at] = u[t];
-                ++at;
-            }
-    }
-};
-
 // Member positions tested per lane and call: kQ Philox blocks of 4 coins.
 // One block per lane and pass keeps every lane's Philox work useful (most
 // hyperedges have few members, so the upper half of an 8-position run is
@@ -366,8 +344,9 @@ constexpr uint32_t kRun = 4 * kQ;
 // that appended it (continuation, below); readers of the queue mask it.
 constexpr uint32_t kExpanded = 0x80000000u;
 
-// SharedAppend that also records the first 64 members this wave appends, and
-// their queue positions, in the wave's LDS.
+// Same with the size in global memory (phase B: many waves grow one set); the
+// first 64 members this wave appends, and their queue positions, are also kept
+// in the wave's LDS.
 struct ContAppend {
     uint32_t *list;
     uint32_t *size;
@@ -1470,11 +1449,6 @@ constexpr uint32_t kShareMax = 16;   // waves that may share one item
 // thin supersteps gain nothing from fewer.
 constexpr uint32_t kContLevels = 8, kContFew = 3;
 
-// Queue entries a planning wave takes per reservation of items, in batches of
-// 64: the reservations of all waves meet at one counter, at 7.5 ns each (sets
-// with frontiers of thousands spent 0.38 ms a superstep on them).
-constexpr uint32_t kPlanBatches = 8;
-
 // k_plan and k_expand read their arguments from device memory, so that a
 // captured batch of supersteps serves every launch group.
 __global__ __launch_bounds__(kWG) void k_plan(const RRArgs *__restrict__ ap, uint32_t parity) {
@@ -1528,12 +1502,11 @@ __global__ __launch_bounds__(kWG) void k_plan(const RRArgs *__restrict__ ap, uin
                 need += (uint32_t)__popcll(firsts[b]) + wave_bcast(hscan[b], kWave - 1);
             }
             uint32_t entries = min(batches * kWave, size - head);
-            if (need > kItemCap) {
-                if (batches > 1u) {   // too many heavy chunks at once: plan one batch ...
+            if (const PlanFit fit = plan_fit(need, batches, kItemCap)) {
+                if (fit == kPlanOneBatch) {
                     most = 1u;
                     continue;
                 }
-                // ... or one vertex
                 entries = 1u;
                 if (lane > 0) hv[0] = 0u;
                 firsts[0] = 1ull;
@@ -1606,7 +1579,8 @@ __global__ __launch_bounds__(kWG) void k_expand(const RRArgs *__restrict__ ap, u
     const uint64_t nitems = min(a.ctr[kItems + parity], (unsigned long long)kItemCap);
     if (blockIdx.x == 0 && threadIdx.x == 0) a.ctr[kItems + (parity ^ 1u)] = 0ull;   // next superstep's counter
     uint64_t bytes_done = 0, px = 0;
-    // items have bounded cost (< seg + chunk incidences), so a static strided
+    // items cost about seg or chunk incidences (more where one hyperedge alone
+    // has more members than that), so a static strided
     // assignment balances well and needs no shared counter.  With fewer items
     // than waves (the thin tail of a traversal), W waves share each item.
     const uint64_t waves = (uint64_t)gridDim.x * kWavesPerWG;
@@ -2020,7 +1994,7 @@ __global__ __launch_bounds__(kWG) void k_ms_plan(MsArgs m) {
             need += batch_need[k];
         }
         if (todo == 0u) continue;
-        const bool together = need <= kItemCap / 2u;
+        const bool together = plan_together(need, kItemCap);
         unsigned long long base = 0;
         if (together) {
             if (lane == 0) base = atomicAdd(&m.ctr[kMsItems], (unsigned long long)need);

@@ -41,6 +41,7 @@ constexpr uint64_t kHubBudget = 2ull << 30;     // bytes of occurrences, counts 
 constexpr uint32_t kHubChunk = 512;             // a hub's incidences per workgroup and turn
 constexpr int kWavesPerBlock = kBlock / kWave;
 
+// The 32-bit finaliser of MurmurHash3 (Appleby, public domain).
 __device__ __forceinline__ uint32_t mix32(uint32_t x) {
     x ^= x >> 16;
     x *= 0x85EBCA6Bu;
