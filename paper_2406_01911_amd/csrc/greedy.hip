@@ -27,7 +27,7 @@
 // Bound by launches and latency on small pools, by reading entries on pools of
 // big sets.  100 rounds over 2048 sets of 85,000 members on average: 8.2 ms with
 // an inverted index of all sets and one histogram of 4096 bins per workgroup and
-// round, 1.9 ms now; a round over a million vertices and small sets with
+// round, 1.45 ms now; a round over a million vertices and small sets with
 // Equation (8): 48 us, 14 us now.
 #include <hip/hip_runtime.h>
 
@@ -57,13 +57,19 @@ __global__ void k_hist(const uint32_t *__restrict__ mem, uint64_t entries, uint3
         atomicAdd(&cnt[mem[e]], 1u);
 }
 
+// The sets above kBigSet members, how many, and (members not null) their members.
 __global__ void k_big_list(const uint64_t *__restrict__ off, uint64_t theta, uint64_t *__restrict__ list,
-                           unsigned long long *__restrict__ count) {
+                           unsigned long long *__restrict__ count, unsigned long long *__restrict__ members) {
     for (uint64_t j0 = (uint64_t)blockIdx.x * blockDim.x; j0 < theta; j0 += (uint64_t)gridDim.x * blockDim.x) {
         const uint64_t j = j0 + threadIdx.x;
-        const bool big = j < theta && off[j + 1] - off[j] > kBigSet;
+        const uint64_t size = j < theta ? off[j + 1] - off[j] : 0u;
+        const bool big = size > kBigSet;
         const uint64_t who = __ballot(big);
         if (who == 0ull) continue;
+        if (members) {
+            const uint64_t sum = wave_sum(big ? size : (uint64_t)0);
+            if (lane_id() == 0) atomicAdd(members, (unsigned long long)sum);
+        }
         unsigned long long base = 0;
         if (lane_id() == 0) base = atomicAdd(count, (unsigned long long)__popcll(who));
         base = wave_bcast64(base, 0);
@@ -72,13 +78,13 @@ __global__ void k_big_list(const uint64_t *__restrict__ off, uint64_t theta, uin
 }
 
 // body(e0, count) for the members [beg, end) of a set that kLanes lanes share:
-// kUnroll positions per lane and turn (e0, e0 + kLanes, ..., the first `count`
+// kTurn positions per lane and turn (e0, e0 + kLanes, ..., the first `count`
 // of them inside), so that a long set's reads are in flight together.
 constexpr uint32_t kUnroll = 4;
-template <uint32_t kLanes, class Body>
+template <uint32_t kLanes, uint32_t kTurn = kUnroll, class Body>
 __device__ __forceinline__ void for_members(uint64_t beg, uint64_t end, Body &&body) {
-    for (uint64_t e = beg + threadIdx.x % kLanes; e < end; e += kUnroll * kLanes)
-        body(e, (uint32_t)min((end - e + kLanes - 1u) / kLanes, (uint64_t)kUnroll));
+    for (uint64_t e = beg + threadIdx.x % kLanes; e < end; e += kTurn * kLanes)
+        body(e, (uint32_t)min((end - e + kLanes - 1u) / kLanes, (uint64_t)kTurn));
 }
 
 // take(set, member) for every member of the sets [0, theta) of at most kBigSet
@@ -145,6 +151,13 @@ __device__ __forceinline__ void range_counts(uint32_t *lds, uint32_t r, uint64_t
                                              const uint32_t *__restrict__ dir, const uint64_t *__restrict__ off,
                                              const uint32_t *__restrict__ mem, uint32_t *__restrict__ cnt,
                                              Pick &&pick) {
+    // sets of few neighbouring vertices leave most ranges empty
+    bool any = false;
+    for (uint64_t i = i0 + threadIdx.x; i < i1; i += kWG) {
+        const uint32_t *d = dir + pick(i) * (ranges + 1u) + r;
+        any |= d[0] != d[1];
+    }
+    if (!__syncthreads_or(any ? 1 : 0)) return;
     for (uint32_t x = threadIdx.x; x < kRange; x += kWG) lds[x] = 0u;
     __syncthreads();
     const uint32_t base = r * kRange;
@@ -152,8 +165,14 @@ __device__ __forceinline__ void range_counts(uint32_t *lds, uint32_t r, uint64_t
         const uint64_t b = pick(i);
         const uint32_t *m = mem + off[list[b]];
         const uint32_t *d = dir + b * (ranges + 1u) + r;
-        const uint32_t e1 = d[1];
-        for (uint32_t e = d[0] + lane_id(); e < e1; e += kWave) atomicAdd(&lds[m[e] - base], 1u);
+        for_members<kWave, 8>(d[0], d[1], [&](uint64_t e, uint32_t count) {
+            uint32_t u[8];
+#pragma unroll
+            for (uint32_t t = 0; t < 8; ++t) u[t] = t < count ? m[e + t * kWave] : base;
+#pragma unroll
+            for (uint32_t t = 0; t < 8; ++t)
+                if (t < count) atomicAdd(&lds[u[t] - base], 1u);
+        });
     }
     __syncthreads();
     for (uint32_t x = threadIdx.x; x < kRange && base + x < n; x += kWG)
@@ -199,7 +218,7 @@ struct GreedyParams {
     unsigned long long *slot_key;    // per k_scan workgroup: best key
     // big sets
     const uint64_t *big;
-    uint64_t nbig;
+    uint64_t nbig, big_mean;         // how many, and their members on average
     const uint32_t *dir;             // null: no ranges (n above kRange * kMaxRanges)
     uint32_t ranges;
     uint32_t *hit;                   // per k_cover workgroup and big set of its share: newly covered big sets
@@ -611,12 +630,16 @@ __global__ __launch_bounds__(kWG) void k_cover(const GreedyParams *__restrict__ 
     if (threadIdx.x == 0) P->hit_n[blockIdx.x] = found;
 }
 
-constexpr uint32_t kBigChunk = 1024;   // members of a big set per wave and turn
-// From this many newly covered sets on, k_sub counts them range by range in
-// LDS: a range's workgroups touch each of its counters at most once, which
-// pays from about the sets whose members outnumber the vertices.
-constexpr uint32_t kRangeSets = 64;
-constexpr uint32_t kSubSplit = 8;      // workgroups per range
+// From about this many members of newly covered sets on, k_sub counts them range
+// by range in LDS; below, device atomics on the counts themselves (about 35 a
+// nanosecond) cost less than a workgroup per range.  80 sets of 20,000
+// neighbouring vertices of a million in each of 50 rounds: 9.5 ms by ranges with
+// the members read one by one, 1.4 ms by atomics; 20 rounds over 3000 sets of
+// 9,500 of 10,000 vertices: 0.98 ms with 8 workgroups per range, 0.35 with as
+// many as there is work for.
+constexpr uint64_t kRangeMembers = 1u << 22;
+constexpr uint32_t kSubSplit = 8;      // workgroups per range at least ...
+constexpr uint32_t kSubSets = 16;      // ... more while each has about this many sets and workgroups are left
 
 // Takes the members of the newly covered big sets off the counts.  `workers`
 // workgroups of k_cover listed them, `per` big sets each.
@@ -641,7 +664,7 @@ __global__ __launch_bounds__(kWG) void k_sub(const GreedyParams *__restrict__ P,
         carry += all;
         __syncthreads();
     }
-    const uint32_t total = carry;
+    const uint64_t total = carry;
     if (total == 0u) return;
     const uint64_t per = div_up(P->nbig, workers);
     auto pick = [&](uint64_t i) -> uint64_t {   // i-th newly covered big set
@@ -652,27 +675,29 @@ __global__ __launch_bounds__(kWG) void k_sub(const GreedyParams *__restrict__ P,
         }
         return P->hit[lo * per + (i - (lo ? scan[lo - 1u] : 0u))];
     };
-    if (P->dir && total >= kRangeSets) {
-        const uint32_t ranges = P->ranges, jobs = ranges * kSubSplit;
+    if (P->dir && total * P->big_mean >= kRangeMembers) {
+        const uint32_t ranges = P->ranges;
+        const uint32_t split = max(kSubSplit, min(total / kSubSets, gridDim.x / ranges)), jobs = ranges * split;
         for (uint32_t job = blockIdx.x; job < jobs; job += gridDim.x) {
             const uint64_t c = job / ranges;
-            range_counts<-1>(lds, job % ranges, total * c / kSubSplit, total * (c + 1u) / kSubSplit, P->n, ranges,
-                             P->big, P->dir, P->off, P->mem, P->cnt, pick);
+            range_counts<-1>(lds, job % ranges, total * c / split, total * (c + 1u) / split, P->n, ranges, P->big,
+                             P->dir, P->off, P->mem, P->cnt, pick);
         }
         return;
     }
-    // chunks of the sets, one after another, over every wave of the grid
-    const uint64_t gw = (uint64_t)blockIdx.x * kWavesPerWG + wv, waves = (uint64_t)gridDim.x * kWavesPerWG;
-    uint64_t run = 0;   // chunks of earlier sets
-    for (uint32_t i = 0; i < total; ++i) {
-        const uint64_t j = P->big[pick(i)];
+    // every set in `parts` equal shares, a workgroup each, about two per workgroup
+    const uint64_t parts = min(max((uint64_t)2u * gridDim.x / total, (uint64_t)1), (uint64_t)gridDim.x);
+    for (uint64_t job = blockIdx.x; job < total * parts; job += gridDim.x) {
+        const uint64_t i = job / parts, p = job - i * parts, j = P->big[pick(i)];
         const uint64_t beg = P->off[j], size = P->off[j + 1] - beg;
-        const uint64_t chunks = div_up(size, kBigChunk);
-        for (uint64_t c = (gw + waves - run % waves) % waves; c < chunks; c += waves) {
-            const uint64_t e1 = min((c + 1u) * kBigChunk, size);
-            for (uint64_t e = c * kBigChunk + lane; e < e1; e += kWave) atomicSub(&P->cnt[P->mem[beg + e]], 1u);
-        }
-        run += chunks;
+        for_members<kWG>(beg + size * p / parts, beg + size * (p + 1u) / parts, [&](uint64_t e, uint32_t count) {
+            uint32_t u[kUnroll];
+#pragma unroll
+            for (uint32_t t = 0; t < kUnroll; ++t) u[t] = t < count ? P->mem[e + t * kWG] : 0u;
+#pragma unroll
+            for (uint32_t t = 0; t < kUnroll; ++t)
+                if (t < count) atomicSub(&P->cnt[u[t]], 1u);
+        });
     }
 }
 
@@ -766,10 +791,12 @@ uint32_t grid_for(uint64_t items, uint64_t per_block, uint32_t cap) {
 }
 
 // The sets of the pool prefix above kBigSet members: list, and their number at
-// ctr (zeroed by the caller).
-void big_list(hyperim_pool p, uint64_t theta, uint64_t *list, unsigned long long *ctr, hipStream_t s) {
+// ctr (zeroed by the caller), their members at `members` (likewise; may be null).
+void big_list(hyperim_pool p, uint64_t theta, uint64_t *list, unsigned long long *ctr, unsigned long long *members,
+              hipStream_t s) {
     if (theta)
-        hipLaunchKernelGGL(k_big_list, dim3(grid_for(theta, kWG, 4096)), dim3(kWG), 0, s, p->off, theta, list, ctr);
+        hipLaunchKernelGGL(k_big_list, dim3(grid_for(theta, kWG, 4096)), dim3(kWG), 0, s, p->off, theta, list, ctr,
+                           members);
 }
 
 // k_hits_small with a wave per set, or a quarter of one where the pool's sets
@@ -801,12 +828,13 @@ int greedy_device(GreedyWorkspace &w, hyperim_graph g, hyperim_pool p, uint64_t 
     HIM_CHECK(w.big.reserve(sizeof(uint64_t) * std::max<uint64_t>(theta, 1), s));
     HIM_CHECK(w.counters.reserve(4 * sizeof(unsigned long long), s));
     unsigned long long *ctr = w.counters.as<unsigned long long>();
-    HIM_HIP(hipMemsetAsync(ctr, 0, sizeof(unsigned long long), s));
-    big_list(p, theta, w.big.as<uint64_t>(), ctr, s);
-    uint64_t entries = 0, nbig = 0;
+    HIM_HIP(hipMemsetAsync(ctr, 0, 2 * sizeof(unsigned long long), s));
+    big_list(p, theta, w.big.as<uint64_t>(), ctr, ctr + 1, s);
+    uint64_t entries = 0, big[2] = {0, 0};
     HIM_HIP(hipMemcpyAsync(&entries, p->off + theta, sizeof(uint64_t), hipMemcpyDeviceToHost, s));
-    HIM_HIP(hipMemcpyAsync(&nbig, ctr, sizeof(uint64_t), hipMemcpyDeviceToHost, s));
+    HIM_HIP(hipMemcpyAsync(big, ctr, 2 * sizeof(uint64_t), hipMemcpyDeviceToHost, s));
     HIM_HIP(hipStreamSynchronize(s));
+    const uint64_t nbig = big[0];
 
     const uint32_t ranges = (uint32_t)div_up(n, kRange);
     const bool by_range = nbig && ranges <= kMaxRanges;
@@ -856,6 +884,7 @@ int greedy_device(GreedyWorkspace &w, hyperim_graph g, hyperim_pool p, uint64_t 
     hp.slot_key = reinterpret_cast<unsigned long long *>(ob + o_key);
     hp.big = w.big.as<uint64_t>();
     hp.nbig = nbig;
+    hp.big_mean = nbig ? big[1] / nbig : 0u;
     hp.dir = by_range ? reinterpret_cast<uint32_t *>(ob + o_dir) : nullptr;
     hp.ranges = ranges;
     hp.hit = reinterpret_cast<uint32_t *>(ob + o_hit);
@@ -930,7 +959,7 @@ int coverage_device(GreedyWorkspace &w, hyperim_graph g, hyperim_pool p, uint64_
     uint8_t *flags = w.flags.as<uint8_t>() + 256;
     HIM_HIP(hipMemsetAsync(ctr, 0, 256 + (size_t)n, s));
     hipLaunchKernelGGL(k_mark, dim3(grid_for(k, kWG, 65535)), dim3(kWG), 0, s, seeds_dev, k, n, flags);
-    big_list(p, theta, w.big.as<uint64_t>(), ctr + 1, s);
+    big_list(p, theta, w.big.as<uint64_t>(), ctr + 1, nullptr, s);
     if (theta) {
         launch_hits_small(p, theta, flags, ctr, s);
         hipLaunchKernelGGL(k_hits_big, dim3(grid_for(theta, kWavesPerWG, 1024)), dim3(kWG), 0, s, w.big.as<uint64_t>(),
@@ -1014,7 +1043,7 @@ extern "C" int hyperim_coverage_noalloc(hyperim_graph g, hyperim_pool pool, uint
     hipLaunchKernelGGL(k_zero_words, dim3(grid_for(words, kWG, 4096)), dim3(kWG), 0, s, ctr, words);
     if (k) hipLaunchKernelGGL(k_mark, dim3(grid_for(k, kWG, 65535)), dim3(kWG), 0, s, seeds_dev, k, g->n, flags);
     if (theta) {
-        big_list(pool, theta, list, ctr + 1, s);
+        big_list(pool, theta, list, ctr + 1, nullptr, s);
         launch_hits_small(pool, theta, flags, ctr, s);
         hipLaunchKernelGGL(k_hits_big, dim3(grid_for(theta, kWavesPerWG, 1024)), dim3(kWG), 0, s, list, ctr + 1,
                            pool->off, pool->mem, seeds_dev, k, flags, ctr);
