@@ -241,8 +241,9 @@ DeviceLock::DeviceLock(int device, hipStream_t s) : DeviceLock(device) {
     idle = false;
 }
 
-int DeviceLock::drain() {
-    HIM_HIP(hipStreamSynchronize(stream));
+int DeviceLock::drain(hipEvent_t end) {
+    if (end) HIM_HIP(hipEventSynchronize(end));
+    else HIM_HIP(hipStreamSynchronize(stream));
     idle = true;
     return HYPERIM_OK;
 }
@@ -424,8 +425,9 @@ int generate_into(const std::vector<RRTask> &tasks, const std::vector<hyperim_po
     const uint64_t stage_budget = (uint64_t)std::max<uint32_t>(live[0].g->tune.stage_mib, 64) << 20;
     HIM_CHECK(rr_generate_into(*lk.rr, st, live, dst, qlog, form, max_entries, stage_budget, s, status,
                                time_kernels, graphs, lean));
+    // the last group's sets are on their way from the workspace to the pools
     if (end) HIM_HIP(hipEventRecord(end, s));
-    HIM_CHECK(lk.drain());   // the last group's sets are on their way from the workspace to the pools
+    HIM_CHECK(lk.drain(end));
     int first_fail = HYPERIM_OK;
     for (size_t i = 0; i < live.size(); ++i) {
         if (was_empty[i] && dst[i]->count) dst[i]->id_begin = live[i].id_begin;

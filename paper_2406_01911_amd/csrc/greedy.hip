@@ -225,7 +225,7 @@ struct GreedyParams {
     uint32_t *hit_n;                 // per k_cover workgroup: how many
     // Equation (8)
     uint32_t *snap;                  // copy of the counts
-    uint32_t *above;                 // per k_scan workgroup and vertex of its share: counts >= lo
+    uint2 *above;                    // per k_scan workgroup, room for its share and kWG more: counts >= lo
     uint32_t *above_n;               // per k_scan workgroup: how many
     RoundState *state;
     unsigned long long *ub;          // k + 1 top-k sums, one per greedy prefix
@@ -235,7 +235,7 @@ struct GreedyParams {
 // that leaves a few times k of them above.
 constexpr uint32_t kSample = 4096;
 constexpr uint32_t kBins = 2048;
-constexpr uint32_t kTopList = 4096;   // listed counts held in LDS
+constexpr uint32_t kTopList = 4096;   // list entries held in LDS
 
 // Suffix search over an LDS histogram of kBins bins: the bin in which the
 // number of values in it and above reaches `need`, and the number above it.
@@ -293,11 +293,11 @@ __device__ __forceinline__ uint32_t bin_shift(uint32_t range) {
 }
 
 // The sum of the `k` largest of the values lo <= x <= max that visit(f) passes
-// to f (every thread visits its own), and the k-th largest of them; false when
-// there are fewer than k (then *sum is the sum of them all).  Levels of
-// kBins bins: the first spans all values, each further one the bin that holds
-// the k-th; then one pass adds what is larger.  Small counts fall into a few
-// bins: the lanes that share the first one's bin add once.  The whole
+// to f(x, c), c of each (every thread visits its own), and the k-th largest of
+// them; false when there are fewer than k (then *sum is the sum of them all).
+// Levels of kBins bins: the first spans all values, each further one the bin
+// that holds the k-th; then one pass adds what is larger.  Small counts fall
+// into a few bins: the lanes that share the first one's bin add once.  The whole
 // workgroup calls it.
 template <class Visit>
 __device__ __forceinline__ bool top_sum(uint32_t *hc, uint32_t lo, uint32_t max, uint32_t k, Visit &&visit,
@@ -308,11 +308,12 @@ __device__ __forceinline__ bool top_sum(uint32_t *hc, uint32_t lo, uint32_t max,
         const uint32_t sh = bin_shift(width);
         for (uint32_t i = threadIdx.x; i < kBins; i += kWG) hc[i] = 0u;
         __syncthreads();
-        visit([&](uint32_t x) {
+        visit([&](uint32_t x, uint32_t c) {
             if (x < base || x - base > width) return;
             const uint32_t b = (x - base) >> sh, b0 = uni(b);
-            const uint64_t same = __ballot(b == b0);
-            if (b != b0) atomicAdd(&hc[b], 1u);
+            const bool one = b == b0 && c == 1u;
+            const uint64_t same = __ballot(one);
+            if (!one) atomicAdd(&hc[b], c);
             else if (lane_rank(same) == 0u) atomicAdd(&hc[b0], (uint32_t)__popcll(same));
         });
         __syncthreads();
@@ -326,7 +327,7 @@ __device__ __forceinline__ bool top_sum(uint32_t *hc, uint32_t lo, uint32_t max,
     }
     const uint32_t floor = ok ? base : 0u;   // not ok only at the first level: all values count
     unsigned long long acc = 0;
-    visit([&](uint32_t x) { acc += x > floor ? x : 0u; });
+    visit([&](uint32_t x, uint32_t c) { acc += x > floor ? (unsigned long long)x * c : 0ull; });
     acc = block_sum(acc);
     *kth = base;
     *sum = ok ? acc + (unsigned long long)need * base : acc;
@@ -355,7 +356,7 @@ __global__ __launch_bounds__(kWG) void k_first_lo(const GreedyParams *__restrict
     const bool ok = top_sum(hc, 1u, uni(most), (uint32_t)min(rank, (uint64_t)m),
                             [&](auto &&f) {
 #pragma unroll
-                                for (uint32_t r = 0; r < kPer; ++r) f(x[r]);
+                                for (uint32_t r = 0; r < kPer; ++r) f(x[r], 1u);
                             },
                             &sum, &kth);
     if (threadIdx.x == 0) {
@@ -374,19 +375,32 @@ __device__ __forceinline__ unsigned long long argmax_key(uint32_t c, uint8_t cho
 // Reads the counts, 4 consecutive vertices per thread and load (cnt, chosen and
 // snap are 256-byte aligned; the last quad may be partial): the workgroup's
 // best key into its slot, and with kTopk the copy of the counts and the list
-// of those of at least lo.
+// of those of at least lo, as (count, how many): lo .. lo + kWG - 1 once each,
+// larger ones as they come, and on small graphs all of them.  (Small counts are shared by many vertices: a
+// million of them in hyperedges of ten, 100,000 sets, had 20,000 and more
+// counts listed one by one, 1.9 ms a round.)
 template <bool kTopk>
 __global__ __launch_bounds__(kWG) void k_scan(const GreedyParams *__restrict__ P) {
     __shared__ unsigned long long part[kWavesPerWG];
-    __shared__ uint32_t listed;
+    __shared__ uint32_t listed, many[kWG];
     if (threadIdx.x == 0) listed = 0u;
+    many[threadIdx.x] = 0u;
     __syncthreads();
     const uint32_t n = P->n, n4 = n / 4, quads = P->quads, lo = kTopk ? P->state->lo : 0u;
     const uint4 *__restrict__ cnt4 = reinterpret_cast<const uint4 *>(P->cnt);
     const uchar4 *__restrict__ chosen4 = reinterpret_cast<const uchar4 *>(P->chosen);
     uint4 *__restrict__ snap4 = reinterpret_cast<uint4 *>(P->snap);
-    uint32_t *above = P->above + (uint64_t)blockIdx.x * quads * 4u * kWG;
+    uint2 *above = P->above + (uint64_t)blockIdx.x * (quads * 4u + 1u) * kWG;
+    const bool merge = n > kTopList;   // else all counts fit where the list is read from
     unsigned long long m = 0;
+    auto list = [&](bool in, uint32_t x, uint32_t c) {   // (every lane of the wave)
+        const uint64_t who = __ballot(in);
+        if (who == 0ull) return;
+        uint32_t at = 0;
+        if (lane_id() == 0) at = atomicAdd(&listed, (uint32_t)__popcll(who));
+        at = wave_bcast(at, 0);
+        if (in) above[at + lane_rank(who)] = make_uint2(x, c);
+    };
     for (uint32_t i = 0; i < quads; ++i) {
         const uint64_t q = ((uint64_t)blockIdx.x * quads + i) * kWG + threadIdx.x;
         const uint64_t v = 4 * q;
@@ -410,15 +424,22 @@ __global__ __launch_bounds__(kWG) void k_scan(const GreedyParams *__restrict__ P
             const unsigned long long key = argmax_key(c[t], ch[t], (uint32_t)v + t);   // absent ones count as chosen
             m = key > m ? key : m;
             if (kTopk) {
-                const bool in = c[t] >= lo;   // lo is at least 1, absent counts are 0
-                const uint64_t who = __ballot(in);
-                if (who == 0ull) continue;
-                uint32_t at = 0;
-                if (lane_id() == 0) at = atomicAdd(&listed, (uint32_t)__popcll(who));
-                at = wave_bcast(at, 0);
-                if (in) above[at + lane_rank(who)] = c[t];
+                const uint32_t b = c[t] - lo;   // lo is at least 1, absent counts are 0
+                const bool in = c[t] >= lo, near = in && merge && b < (uint32_t)kWG;
+                if (near) {
+                    const uint32_t b0 = uni(b);
+                    const uint64_t same = __ballot(b == b0);
+                    if (b != b0) atomicAdd(&many[b], 1u);
+                    else if (lane_rank(same) == 0u) atomicAdd(&many[b0], (uint32_t)__popcll(same));
+                }
+                list(in && !near, c[t], 1u);
             }
         }
+    }
+    if (kTopk && merge) {
+        __syncthreads();
+        const uint32_t c = many[threadIdx.x];
+        list(c != 0u, lo + threadIdx.x, c);
     }
     m = wave_max(m);
     if (lane_id() == 0) part[threadIdx.x / kWave] = m;
@@ -453,9 +474,9 @@ __device__ void round_top_k(const GreedyParams *__restrict__ P, uint32_t slots, 
     __shared__ uint32_t hc[kBins];
     __shared__ uint32_t scan[kScanMax];   // inclusive scan of the list lengths
     __shared__ uint32_t part[kWavesPerWG];
-    __shared__ uint32_t val[kTopList];
+    __shared__ uint2 val[kTopList];
     const uint32_t k = P->k, n = P->n, lo = P->state->lo;
-    const uint32_t share = P->quads * 4u * kWG;
+    const uint32_t share = (P->quads * 4u + 1u) * kWG;
     uint32_t total = 0;
     for (uint32_t base = 0; base < slots; base += kWG) {
         const uint32_t i = base + threadIdx.x;
@@ -470,7 +491,7 @@ __device__ void round_top_k(const GreedyParams *__restrict__ P, uint32_t slots, 
         if (i < slots) scan[i] = before + incl;
         __syncthreads();
     }
-    auto listed = [&](uint32_t i) -> uint32_t {   // i-th listed count
+    auto listed = [&](uint32_t i) -> uint2 {   // i-th list entry
         uint32_t a = 0, b = slots - 1u;
         while (a < b) {
             const uint32_t mid = (a + b) / 2u;
@@ -488,7 +509,10 @@ __device__ void round_top_k(const GreedyParams *__restrict__ P, uint32_t slots, 
     const uint32_t most = (uint32_t)(key >> 32) ? (uint32_t)(key >> 32) - 1u : 0u;
     bool ok = top_sum(hc, lo, most, k,
                       [&](auto &&f) {
-                          for (uint32_t i = threadIdx.x; i < total; i += kWG) f(held ? val[i] : listed(i));
+                          for (uint32_t i = threadIdx.x; i < total; i += kWG) {
+                              const uint2 x = held ? val[i] : listed(i);
+                              f(x.x, x.y);
+                          }
                       },
                       &sum, &kth);
     bool missed = false;
@@ -501,12 +525,12 @@ __device__ void round_top_k(const GreedyParams *__restrict__ P, uint32_t slots, 
                          const uint32_t n4 = n / 4u;
                          for (uint32_t q = threadIdx.x; q < n4; q += kWG) {
                              const uint4 x = s4[q];
-                             f(x.x);
-                             f(x.y);
-                             f(x.z);
-                             f(x.w);
+                             f(x.x, 1u);
+                             f(x.y, 1u);
+                             f(x.z, 1u);
+                             f(x.w, 1u);
                          }
-                         if (threadIdx.x < n % 4u) f(P->snap[4u * n4 + threadIdx.x]);
+                         if (threadIdx.x < n % 4u) f(P->snap[4u * n4 + threadIdx.x], 1u);
                      },
                      &sum, &kth);
     }
@@ -852,7 +876,7 @@ int greedy_device(GreedyWorkspace &w, hyperim_graph g, hyperim_pool p, uint64_t 
     const size_t o_key = o.add(8ull * kScanMax), o_state = o.add(sizeof(RoundState)), o_ub = o.add(8ull * ((size_t)k + 1)),
                  o_hit_n = o.add(4ull * kCoverMax), o_above_n = o.add(4ull * kScanMax),
                  o_hit = o.add(4ull * div_up(nbig, workers) * workers), o_snap = o.add(topk ? 4ull * n : 0u),
-                 o_above = o.add(topk ? 16ull * kWG * quads * scan_grid : 0u),
+                 o_above = o.add(topk ? 8ull * kWG * (4ull * quads + 1u) * scan_grid : 0u),
                  o_dir = o.add(by_range ? 4ull * nbig * (ranges + 1u) : 0u);
     HIM_CHECK(w.zeroed.reserve(z.bytes, s));
     HIM_CHECK(w.round.reserve(o.bytes, s));
@@ -890,7 +914,7 @@ int greedy_device(GreedyWorkspace &w, hyperim_graph g, hyperim_pool p, uint64_t 
     hp.hit = reinterpret_cast<uint32_t *>(ob + o_hit);
     hp.hit_n = reinterpret_cast<uint32_t *>(ob + o_hit_n);
     hp.snap = reinterpret_cast<uint32_t *>(ob + o_snap);
-    hp.above = reinterpret_cast<uint32_t *>(ob + o_above);
+    hp.above = reinterpret_cast<uint2 *>(ob + o_above);
     hp.above_n = reinterpret_cast<uint32_t *>(ob + o_above_n);
     hp.state = reinterpret_cast<RoundState *>(ob + o_state);
     hp.ub = reinterpret_cast<unsigned long long *>(ob + o_ub);

@@ -149,7 +149,8 @@ struct PrepWorkspace {
 // The device's shared workspaces (RR generation, greedy / coverage,
 // stratification), locked for the holder's lifetime.  The holder's stream is
 // waited for before the lock goes to the next one, who may use another stream:
-// drain() waits, and the destructor does where nobody has (an early return).
+// drain() waits (for `end`, if the caller has recorded one behind all work), and
+// the destructor does where nobody has (an early return).
 struct DeviceLock {
     RRWorkspace *rr;
     GreedyWorkspace *gr;
@@ -160,7 +161,7 @@ struct DeviceLock {
     explicit DeviceLock(int device);                  // queues no work
     DeviceLock(int device, hipStream_t s);
     ~DeviceLock();
-    int drain();
+    int drain(hipEvent_t end = nullptr);
     DeviceLock(const DeviceLock &) = delete;
     DeviceLock &operator=(const DeviceLock &) = delete;
 };

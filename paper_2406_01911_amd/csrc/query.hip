@@ -304,7 +304,7 @@ struct Engine {
         // entries of the index (the big sets' directory takes an eighth of what
         // these would); per set stamps and lists; per vertex counts, their copy
         // and list, cursors, offsets, flags
-        need.greedy = std::max(need.greedy, 4.0 * 1.1 * (double)theta * m + 16.0 * (double)theta + 26.0 * n);
+        need.greedy = std::max(need.greedy, 4.0 * 1.1 * (double)theta * m + 16.0 * (double)theta + 32.0 * n);
         need.n_max = std::max(need.n_max, q->q.graph->n);
         need.stage_cap = std::max(need.stage_cap,
                                   (double)((uint64_t)std::max<uint32_t>(q->q.graph->tune.stage_mib, 64) << 20));

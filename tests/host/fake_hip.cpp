@@ -12,8 +12,10 @@
 #include <sys/mman.h>
 #include <unistd.h>
 
+#include <algorithm>
 #include <map>
 #include <mutex>
+#include <utility>
 
 namespace fake {
 std::atomic<size_t> total{288ull << 30}, used{0}, peak{0};
@@ -27,6 +29,7 @@ namespace {
 std::mutex mu;
 std::map<void *, size_t> blocks;
 std::map<hipStream_t, long> pending;   // work queued since the stream was last waited for
+std::map<hipEvent_t, std::pair<hipStream_t, long>> recorded;
 
 hipError_t queued(hipStream_t s) {
     std::lock_guard<std::mutex> l(mu);
@@ -176,9 +179,26 @@ FAKE hipError_t hipEventDestroy(hipEvent_t e) {
     free(e);
     return hipSuccess;
 }
-FAKE hipError_t hipEventRecord(hipEvent_t, hipStream_t s) { return queued(s); }
+FAKE hipError_t hipEventRecord(hipEvent_t e, hipStream_t s) {
+    const hipError_t rc = queued(s);
+    std::lock_guard<std::mutex> l(mu);
+    recorded[e] = {s, pending[s]};
+    return rc;
+}
 FAKE hipError_t hipEventQuery(hipEvent_t) { return hipSuccess; }
-FAKE hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
+FAKE hipError_t hipEventSynchronize(hipEvent_t e) {   // the work before the event is done
+    hipStream_t s;
+    {
+        std::lock_guard<std::mutex> l(mu);
+        s = recorded[e].first;
+        if (pending[s] == 0) return hipSuccess;
+    }
+    pause_us(fake::sync_us);
+    std::lock_guard<std::mutex> l(mu);
+    pending[s] -= std::min(pending[s], recorded[e].second);
+    recorded[e].second = 0;
+    return hipSuccess;
+}
 FAKE hipError_t hipEventElapsedTime(float *ms, hipEvent_t, hipEvent_t) {
     *ms = 0.f;
     return hipSuccess;
