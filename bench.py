@@ -354,17 +354,24 @@ def main():
     per_launch_s = k_ms * 1e-3 / max(k_launches, 1)
     alg_per_launch = k_bytes / max(k_launches, 1)
     px_per_launch = k_px / max(k_launches, 1)
-    hbm_achieved = alg_per_launch / per_launch_s / 1e9 if per_launch_s > 0 else 0.0
+    # algorithmic bytes a second: what a traversal that reads every member of
+    # every set by itself would move.  The kernels read members where a coin is
+    # live, and bundled sets share what they read, so this is no bandwidth and
+    # may exceed HBM's; the counters' traffic is one.
+    alg_rate = alg_per_launch / per_launch_s / 1e9 if per_launch_s > 0 else 0.0
     px_achieved = px_per_launch / per_launch_s if per_launch_s > 0 else 0.0
-    frac_hbm = hbm_achieved / HBM_PEAK_GBS
     frac_valu = px_achieved / PHILOX_PEAK_BLOCKS_PER_S
     traffic = kernel_traffic(kern, args.workload)
     # bound: counters below the algorithmic bytes mean the bytes come from
-    # caches and the integer ALU binds; without counters, the larger fraction
+    # caches or are not read at all, and the integer ALU binds; without
+    # counters, the larger fraction, unless the bytes cannot all have moved
     if traffic is not None:
+        hbm_achieved = traffic / per_launch_s / 1e9 if per_launch_s > 0 else 0.0
         bound = "alu" if traffic < alg_per_launch else "hbm"
     else:
-        bound = "alu" if frac_valu >= frac_hbm else "hbm"
+        hbm_achieved = alg_rate if alg_rate <= HBM_PEAK_GBS else None
+        bound = "hbm" if hbm_achieved is not None and hbm_achieved / HBM_PEAK_GBS > frac_valu else "alu"
+    frac_hbm = None if hbm_achieved is None else hbm_achieved / HBM_PEAK_GBS
     if bound == "alu":
         roof = {"bound": "alu", "achieved": px_achieved / 1e9, "peak": PHILOX_PEAK_BLOCKS_PER_S / 1e9,
                 "unit": "Gblocks/s (Philox4x32-10 on the VALU)", "frac": frac_valu}
@@ -379,6 +386,7 @@ def main():
         "frac_hbm": frac_hbm,
         "frac_valu": frac_valu,
         "alg_bytes_per_launch": alg_per_launch,
+        "alg_bytes_per_s": alg_rate * 1e9,
         "philox_blocks_per_launch": px_per_launch,
         "avg_launch_ms": per_launch_s * 1e3,
         "launches_per_step": k_launches,
@@ -420,8 +428,7 @@ def main():
         "rr_generation": {
             "kernels": "k_lt_walk" if lt else "k_layered" if layered else
                        "k_rr_light, k_plan, k_expand, k_finish, k_ms_*",
-            "achieved_GBps": kernel_bytes / (bfs_ms * 1e-3) / 1e9 if bfs_ms > 0 else 0.0,
-            "frac_hbm": kernel_bytes / (bfs_ms * 1e-3) / 1e9 / HBM_PEAK_GBS if bfs_ms > 0 else 0.0,
+            "alg_bytes_per_s": kernel_bytes / (bfs_ms * 1e-3) if bfs_ms > 0 else 0.0,
             "ms": bfs_ms,
             "launches_per_step": totals[-1]["bfs_launches"],
             "superstep_batches": "direct launches" if args.no_graphs else "captured HIP graphs, replayed",

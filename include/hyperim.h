@@ -176,7 +176,10 @@ typedef struct {
     uint64_t alg_bytes;     /* algorithmic bytes of RR generation (both pools):
                                sum over members v of 20 + 12 d(v) + 4 S(v),
                                d(v) = hyperedges of v, S(v) = their total size;
-                               filled with HYPERIM_FLAG_INCIDENCES            */
+                               filled with HYPERIM_FLAG_INCIDENCES.  A measure
+                               of the traversal, not of traffic: members are
+                               read where a channel is live, and bundled sets
+                               share what they read                           */
     double ms_bfs;          /* device time of the RR-generation kernels alone  */
     uint64_t bfs_launches;  /* number of RR-generation kernel launches         */
     double ms_light;        /* part of ms_bfs spent in the per-set phase       */

@@ -14,8 +14,8 @@
 // and member ids are read contiguously; one Philox4x32-10 block gives the 4
 // coins of a run; a live channel from an unvisited member sets its bit
 // (atomic OR) and the winner appends it with a ballot-ranked store.  A set
-// whose next batch holds a heavy vertex, or that has used up its incidence
-// budget, is handed over intact (slot, queue head, size) to phase B and the
+// whose next batch holds a heavy vertex, or that has read its share of
+// incidences or member positions, is handed over intact (slot, queue head, size) to phase B and the
 // wave takes a fresh slot.  Finished sets are written ascending to a staging
 // area.
 //
@@ -690,9 +690,9 @@ __device__ __forceinline__ uint64_t expand_gaps(const GraphView &G, Lds &L, uint
 // the longer hyperedges over the wave.  W waves (a power of two, wave w of them passing
 // w) may share one call: they split the batches of 64 incidences between
 // them, and when there are fewer batches than waves, each batch's runs too;
-// every run is tested by exactly one of them.  Returns the algorithmic
-// bytes of the incidences read (12 per incidence plus 4 per member
-// position), each counted by one wave, wave-uniform.
+// every run is tested by exactly one of them.  Returns the algorithmic bytes of
+// the incidences (12 each plus 4 per member position, read or not: members are
+// read where a coin is live), each counted by one wave, wave-uniform.
 template <bool kLds, bool kUniform, bool kGaps, class App, class Lds>
 __device__ __forceinline__ uint64_t expand(const GraphView &G, Lds &L, uint64_t j, uint32_t pool, uint2 key,
                                            uint32_t *bm, bool prefilter, uint32_t v, uint32_t e0, uint32_t d,
