@@ -249,7 +249,7 @@ int DeviceLock::drain(hipEvent_t end) {
 }
 
 DeviceLock::~DeviceLock() {
-    if (!idle) (void)hipStreamSynchronize(stream);
+    if (!idle && !rr->left) (void)hipStreamSynchronize(stream);
     static_cast<DevCtx *>(lock)->mu.unlock();
 }
 
@@ -272,6 +272,11 @@ void RRWorkspace::drop_graphs() {
     batch_graphs.clear();
 }
 
+bool RRWorkspace::settled() {
+    if (left && hipEventQuery(unfinished) == hipSuccess) left = false;
+    return !left;
+}
+
 void RRWorkspace::drop_slots() {
     lists.release();
     bitmaps.release();
@@ -288,6 +293,9 @@ void RRWorkspace::release() {
         x->release();
     for (hipEvent_t e : events) (void)hipEventDestroy(e);
     events.clear();
+    if (unfinished) (void)hipEventDestroy(unfinished);
+    unfinished = nullptr;
+    left = false;
     if (host) (void)hipHostFree(host);
     host = nullptr;
     host_words = 0;

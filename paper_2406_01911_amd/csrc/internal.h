@@ -91,6 +91,11 @@ struct RRWorkspace {
     std::vector<BatchGraph> batch_graphs;
     hipStream_t capture = nullptr;   // stream the batches are captured on
     bool graphs_off = false;         // capture failed on this device: launch kernels directly
+    // a call that gave up waiting leaves its work running, and this event behind
+    // it: nobody uses the workspace until it is done
+    hipEvent_t unfinished = nullptr;
+    bool left = false;
+    bool settled();
     void drop_graphs();
     void drop_slots();
     unsigned long long *host = nullptr;  // pinned host staging: counter copies, descriptors, totals
@@ -150,7 +155,8 @@ struct PrepWorkspace {
 // stratification), locked for the holder's lifetime.  The holder's stream is
 // waited for before the lock goes to the next one, who may use another stream:
 // drain() waits (for `end`, if the caller has recorded one behind all work), and
-// the destructor does where nobody has (an early return).
+// the destructor does where nobody has (an early return), unless the wait was
+// given up (RRWorkspace::left).
 struct DeviceLock {
     RRWorkspace *rr;
     GreedyWorkspace *gr;

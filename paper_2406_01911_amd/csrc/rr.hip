@@ -2731,8 +2731,9 @@ int read_ctr(hipStream_t s, const unsigned long long *dev, int idx, uint64_t *ou
 // Wait for an event of the superstep loops, but not forever: a batch that has
 // not finished after HYPERIM_WAIT_LIMIT_S seconds (default 600; a batch of
 // the largest workloads takes a few seconds) ends the call with HYPERIM_EHIP
-// naming the loop, instead of blocking the caller.
-int wait_event(hipEvent_t e, const char *what) {
+// naming the loop, instead of blocking the caller.  What runs on stream s then
+// keeps the workspace until it is done.
+int wait_event(RRWorkspace &ws, hipEvent_t e, hipStream_t s, const char *what) {
     static const double limit = [] {
         const char *v = getenv("HYPERIM_WAIT_LIMIT_S");
         const double x = v ? atof(v) : 0.0;
@@ -2748,6 +2749,8 @@ int wait_event(hipEvent_t e, const char *what) {
         }
         const double el = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
         if (el > limit) {
+            if (ws.unfinished || hipEventCreate(&ws.unfinished) == hipSuccess)
+                ws.left = hipEventRecord(ws.unfinished, s) == hipSuccess;
             set_error_detail(std::string(what) + " did not finish within the wait limit");
             return HYPERIM_EHIP;
         }
@@ -2996,7 +2999,7 @@ int run_launch(RRWorkspace &ws, RRStats &st, const hyperim_tuning &tune, RRArgs 
         uint64_t planned_before = 0;
         for (;;) {
             HIM_CHECK(issue(k + 1));   // queued before batch k is read
-            HIM_CHECK(wait_event(batch_events(ws, k)[1], "a grid-wide superstep batch"));
+            HIM_CHECK(wait_event(ws, batch_events(ws, k)[1], s, "a grid-wide superstep batch"));
             const unsigned long long *hb = h + kHostBatch + (k & 1u) * kHostCtr;
             ndef = hb[kDefCount];
             plan_sets = std::max<uint64_t>(ndef, 1);
@@ -3221,7 +3224,7 @@ int run_ms_launch(RRWorkspace &ws, RRStats &st, const hyperim_tuning &tune, RRAr
         HIM_HIP(hipGetLastError());
         steps += batch;
         HIM_HIP(hipEventRecord(E[1], s));
-        HIM_CHECK(wait_event(E[1], "a bundled superstep batch"));
+        HIM_CHECK(wait_event(ws, E[1], s, "a bundled superstep batch"));
         const uint64_t done = hm[kMsDone];
         // a level adds at least one new (set, member) pair, so levels are
         // bounded by the members of the group's sets
@@ -3343,6 +3346,10 @@ int rr_generate_into(RRWorkspace &ws, RRStats &st, const std::vector<RRTask> &ta
     }();
     pool_status.assign(tasks.size(), HYPERIM_OK);
     if (tasks.empty()) return HYPERIM_OK;
+    if (!ws.settled()) {
+        set_error_detail("an earlier generation call gave up waiting and its work still runs");
+        return HYPERIM_EHIP;
+    }
     // a launch group compacts its slices after one wait, so each task needs a
     // pool of its own
     std::vector<hyperim_pool> sorted(pools);

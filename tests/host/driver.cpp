@@ -314,6 +314,30 @@ int blocks() {
     return 0;
 }
 
+// A batch of supersteps that does not finish within the wait limit: the call
+// says so without waiting on, the next one leaves the workspace alone, and once
+// the work is done everything goes on.
+int wait_limit() {
+    setenv("HYPERIM_WAIT_LIMIT_S", "0.01", 1);
+    hyperim_graph g = pairs(50000, stream(0)), h = pairs(40000, stream(1));
+    hyperim_pool p = nullptr, q = nullptr;
+    NEED(g && h, "graphs");
+    NEED(hyperim_pool_create(g, nullptr, 0, 0, &p) == HYPERIM_OK, "pool");
+    NEED(hyperim_pool_create(h, nullptr, 0, 0, &q) == HYPERIM_OK, "pool");
+    fake::stalled = true;
+    NEED(hyperim_generate_rr(g, 7, 0, 0, 0, 100, p, stream(0)) == HYPERIM_EHIP, "the stalled call");
+    NEED(fake::blocked == 0, "it waited on");
+    const long launches = fake::launches;
+    NEED(hyperim_generate_rr(h, 7, 0, 0, 0, 100, q, stream(1)) == HYPERIM_EHIP, "the next call");
+    NEED(fake::launches == launches, "it used the workspace");
+    fake::stalled = false;
+    NEED(hyperim_generate_rr(h, 7, 0, 0, 0, 100, q, stream(1)) == HYPERIM_OK, "afterwards: %s", hyperim_strerror(-5));
+    NEED(hyperim_generate_rr(g, 7, 0, 0, 0, 100, p, stream(0)) == HYPERIM_OK, "afterwards");
+    NEED(hyperim_workspace_release() == HYPERIM_OK, "release");
+    printf("ok %ld launches\n", fake::launches.load());
+    return 0;
+}
+
 }  // namespace
 
 int main(int argc, char **argv) {
@@ -324,6 +348,7 @@ int main(int argc, char **argv) {
     if (!strcmp(what, "tables_nomem")) return tables_nomem();
     if (!strcmp(what, "small_budget")) return small_budget();
     if (!strcmp(what, "blocks")) return blocks();
+    if (!strcmp(what, "wait_limit")) return wait_limit();
     printf("unknown scenario '%s'\n", what);
     return 2;
 }

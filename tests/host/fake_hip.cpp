@@ -20,7 +20,8 @@
 namespace fake {
 std::atomic<size_t> total{288ull << 30}, used{0}, peak{0};
 std::atomic<long> mallocs{0}, fail_from{-1}, launches{0}, device_syncs{0}, overlaps{0};
-std::atomic<bool> watch{false};
+std::atomic<bool> watch{false}, stalled{false};
+std::atomic<long> blocked{0};
 std::atomic<int> sync_us{0};
 std::atomic<void (*)()> on_device_sync{nullptr};
 }  // namespace fake
@@ -140,6 +141,7 @@ FAKE hipError_t hipStreamSynchronize(hipStream_t s) {
         std::lock_guard<std::mutex> l(mu);
         if (pending[s] == 0) return hipSuccess;
     }
+    if (fake::stalled) ++fake::blocked;
     pause_us(fake::sync_us);
     std::lock_guard<std::mutex> l(mu);
     pending[s] = 0;
@@ -185,7 +187,7 @@ FAKE hipError_t hipEventRecord(hipEvent_t e, hipStream_t s) {
     recorded[e] = {s, pending[s]};
     return rc;
 }
-FAKE hipError_t hipEventQuery(hipEvent_t) { return hipSuccess; }
+FAKE hipError_t hipEventQuery(hipEvent_t) { return fake::stalled ? hipErrorNotReady : hipSuccess; }
 FAKE hipError_t hipEventSynchronize(hipEvent_t e) {   // the work before the event is done
     hipStream_t s;
     {

@@ -53,3 +53,7 @@ def test_small_graph_within_a_small_budget(driver):
 
 def test_freed_blocks(driver):
     _run(driver, "blocks")
+
+
+def test_work_that_does_not_finish(driver):
+    _run(driver, "wait_limit")
