@@ -20,7 +20,8 @@
 //
 // Equation (8) wants the sum of the k largest counts before each round (and
 // after the last).  k_scan also lists the counts of at least `lo`, a guess
-// below the k-th largest, and keeps a copy of all counts; one workgroup of
+// below the k-th largest (the values next to it once each, with how many
+// vertices share them), and keeps a copy of all counts; one workgroup of
 // k_cover selects the exact sum from the list while the others cover, or from
 // the copy when the guess was too high, and sets the next guess.
 //
